@@ -67,7 +67,12 @@ typedef enum {
 typedef enum { MAR_FP64 = 0, MAR_FP32 = 1 } mar_precision;
 
 /* MAR_FORM_PLAIN: one seed at a time (B = 1), one kernel launch per phase.
- * MAR_FORM_BATCHED: B seeds per block with seed-interleaved vectors. */
+ * MAR_FORM_BATCHED: B seeds per block with seed-interleaved vectors. On small
+ * row sets (cells of up to about 3072 rows, local regions of up to about ten
+ * hops) with a 4x4-block H and a tuning that asks for nothing of the blocks
+ * (every field of mar_tuning 0, eig_max_sweeps and two_streams 2 or 3 aside),
+ * one workgroup runs each seed's whole textbook recurrence instead; an
+ * autotuned block size does not apply there. */
 typedef enum { MAR_FORM_BATCHED = 0, MAR_FORM_PLAIN = 1 } mar_form;
 
 /* CGS2 schedules. Both run two classical Gram-Schmidt passes per new vector

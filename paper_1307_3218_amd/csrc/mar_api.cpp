@@ -101,6 +101,8 @@ struct mar_ctx {
 
     mar_tuning tune{};
     int32_t loc = -1;             // local-region hops of later solves (< 0: the full system)
+    int32_t loc_blocks = 0;       // block rows of the largest such region (0: not known, or too many for k_seed)
+    int32_t* d_loc = nullptr;     // device word for that count
     char* ws = nullptr;
     size_t ws_bytes = 0;
     char* ext_ws = nullptr;       // a caller's workspace for the current solve (nothing is allocated then)
@@ -402,7 +404,40 @@ struct Plan {
     int B;
     bool delayed;
     int variant;
+    bool seedwise = false;   // one workgroup per seed (small regions and cells) instead of seed blocks
 };
+
+// The launch shape of the one-workgroup-per-seed form.
+mar::SeedGeom seed_geom(const mar_ctx* c, int nu, mar_precision prec, int64_t ns) {
+    const size_t elem = prec == MAR_FP32 ? 4 : 8;
+    return mar::seed_geometry(c->H.n, c->H.nnz, (c->max_row + 3) / 4, c->loc, c->loc >= 0 ? c->loc_blocks : c->H.n, nu,
+                              elem, ns, c->n_cu);
+}
+
+// Whether a batched solve runs one workgroup per seed.
+bool use_seedwise(const mar_ctx* c, int nu, mar_precision prec, int64_t ns) {
+    const mar_tuning& t = c->tune;
+    // a tuning of the blocks' kernels asks for the blocks
+    if (t.seed_block || t.schedule != MAR_SCHED_AUTO || t.proj_wgs || t.slab_pad_kb || t.proj_variant || t.upd_q ||
+        t.support_off || t.two_streams == 1)
+        return false;
+    if (ns < 1 || !c->H.bsr || c->SH.nnz != c->H.nnz) return false;
+    const mar::SeedGeom g = seed_geom(c, nu, prec, ns);
+    if (!g.ok) return false;
+    // Where the line lies (ms per solve, one workgroup per seed / blocks, diamond cells and mixed-lattice regions):
+    //  * a few hundred to 2048 rows: FP32 nu = 30, 256 seeds: 0.42 / 1.60 at 256 rows, 0.84 / 2.03 at 2048; FP64
+    //    nu = 100, 1024 seeds: 24.6 / 88.8 at 1024 rows, 56 / 96 at 2048. Always taken up to 3072 rows.
+    //  * 4096 rows: one compute unit streams its seed's basis four times per step from the last-level cache, the
+    //    blocks stream all seeds' twice: FP32 nu = 30 (0.5 MB of basis) 6.3 / 9.6 for 1024 seeds, nu = 100 (1.6 MB)
+    //    55.9 / 58.2, 15.2 / 14.3 for 256; FP64 nu = 100 (3.3 MB) 116 / 134, nu = 200 (6.6 MB) 76 / 70 for 8 seeds.
+    //  * 8192 rows: FP32 nu = 30 13.0 / 11.9, nu = 100 116 / 98.
+    //  * local regions: a block of seeds streams the union of its regions, so the line lies further out: regions of
+    //    6 hops (226 blocks) FP32 nu = 100, 1024 seeds 12.0 / 84.5, 10 hops (about 900) 46 / 165, 12 hops (about
+    //    1500) 91 / 187, but nu = 12 4.3 / 3.8; FP64 10 hops with 8 seeds 9.9 / 9.2, with 64 14.5 / 24.8.
+    const double rows = 4.0 * g.nbcap, kbytes = nu * rows * (prec == MAR_FP32 ? 4 : 8);
+    if (c->loc >= 0) return rows <= 3072 || (nu >= 32 && (prec == MAR_FP32 || ns >= 32));
+    return rows <= 3072 || (rows <= 4096 && kbytes <= (prec == MAR_FP32 ? 1.0e6 : 4.0e6));
+}
 
 Plan plan_solve(const mar_ctx* c, int nu, mar_precision prec, mar_form form, int64_t n_seeds) {
     Plan pl;
@@ -416,6 +451,7 @@ Plan plan_solve(const mar_ctx* c, int nu, mar_precision prec, mar_form form, int
         auto t = c->tuned.find({nu, (int)prec});
         if (t != c->tuned.end()) pl.variant = t->second.second;
     }
+    pl.seedwise = form == MAR_FORM_BATCHED && use_seedwise(c, nu, prec, n_seeds);
     return pl;
 }
 
@@ -1034,6 +1070,82 @@ mar_status run_solve_delayed(mar_ctx* c, const int32_t* d_seeds, int64_t n_seeds
     return MAR_OK;
 }
 
+// One workgroup per seed: the Krylov phase of a chunk of seeds in one launch, then its eigensolves.
+template <typename T>
+mar_status run_seedwise(mar_ctx* c, const mar_request& r, hipStream_t s) {
+    const int nu = r.nu;
+    const int64_t n_seeds = r.n_seeds;
+    const double tau = sizeof(T) == 4 ? 1e-5 : 1e-12;
+    const bool acc64 = sizeof(T) == 4 && nu > mar::kUpdAcc64Nu;
+    const mar::SeedGeom g = seed_geom(c, nu, r.prec, n_seeds);
+    const size_t per = (size_t)nu * (nu + std::max(1, c->max_row)) * 8;
+    int64_t chunk = std::min<int64_t>(n_seeds, std::max<int64_t>(g.grid, (int64_t)(1e9 / (double)per)));
+    const bool own_e = r.d_e_seed == nullptr, own_n = r.d_n_seed == nullptr, own_nu = r.d_nu_eff == nullptr;
+    size_t oK = 0, oH = 0, oKp = 0, oNu = 0, oE = 0, oN = 0, oNuOut = 0, oPr = 0;
+    for (;;) {
+        size_t off = 0;
+        auto take = [&](size_t bytes) {
+            const size_t o = off;
+            off += align_up(bytes);
+            return o;
+        };
+        oK = take((size_t)g.grid * g.sstride * sizeof(T));
+        oH = take((size_t)chunk * nu * nu * 8);
+        oKp = take((size_t)chunk * nu * std::max(1, c->max_row) * 8);
+        oNu = take((size_t)chunk * 4);
+        oPr = take(c->es.mode == 2 ? (size_t)chunk * nu * 8 : 0);
+        oE = take(own_e ? (size_t)n_seeds * 8 : 0);
+        oN = take(own_n ? (size_t)n_seeds * 8 : 0);
+        oNuOut = take(own_nu ? (size_t)n_seeds * 4 : 0);
+        const mar_status st = ensure_ws(c, off);
+        if (st == MAR_OK) break;
+        if (!c->ext_ws || chunk <= 1) return st;   // a caller's workspace: shorter chunks
+        chunk = (chunk + 1) / 2;
+    }
+    char* w = c->ws_act;
+    double* h = (double*)(w + oH);
+    double* Kp = (double*)(w + oKp);
+    int32_t* nucp = (int32_t*)(w + oNu);
+    double* pref = c->es.mode == 2 ? (double*)(w + oPr) : nullptr;
+    double* e_seed = own_e ? (double*)(w + oE) : r.d_e_seed;
+    double* n_seed = own_n ? (double*)(w + oN) : r.d_n_seed;
+    int32_t* nu_out = own_nu ? (int32_t*)(w + oNuOut) : r.d_nu_eff;
+    for (int64_t at = 0; at < n_seeds; at += chunk) {
+        const int ns = (int)std::min<int64_t>(chunk, n_seeds - at);
+        const int32_t* seeds = r.d_seeds + at;
+        launch(c, s, P_UPD, [&] {
+            mar::SeedGeom gc = g;
+            gc.grid = std::min(g.grid, ns);
+            return mar::launch_seed<T>(gc, c->H, c->SH, c->M, c->diagS, seeds, ns, nu, c->loc, tau, (T*)(w + oK), c->Hrp,
+                                       c->max_row, h, Kp, nucp, pref ? c->es.vref : nullptr, pref, ns, acc64, s);
+        });
+        mar::EigExtra ex;
+        ex.eig_max_sweeps = c->tune.eig_max_sweeps > 0 ? c->tune.eig_max_sweeps : 40;
+        if (c->es.mode == 2) {
+            ex.mode = 2;
+            ex.pref = pref;
+            ex.pB = ns;
+            ex.win = c->es.lv;
+            ex.sigma = c->es.sigma;
+            ex.phi = c->es.phi + at;
+        }
+        launch(c, s, P_EIG, [&] {
+            return mar::launch_eig(ns, seeds, nu, h, nucp, Kp, c->Hrp, c->Hcol, c->Hval, c->SvalH, c->diagS, c->max_row,
+                                   r.mu, r.kT, r.d_rho, e_seed + at, n_seed + at, nu_out + at,
+                                   r.d_eps ? r.d_eps + at * nu : nullptr, r.d_weight ? r.d_weight + at * nu : nullptr,
+                                   c->zc_defer ? c->zc_defer + (size_t)at * nu * c->max_row : nullptr, ex, s);
+        });
+    }
+    if (!c->zc_defer && !c->es.mode)
+        launch(c, s, P_SUM, [&] { return mar::launch_sum(e_seed, n_seeds, r.d_e_band, s); });
+    if (c->refused) {
+        c->refused = false;
+        return set_err(c, MAR_ERR_STATE, "internal error: a launch was refused; solve not run");
+    }
+    HIP_OR(c, hipGetLastError());
+    return MAR_OK;
+}
+
 mar_status check_scalars(mar_ctx* c, int64_t n_seeds, int32_t nu, double mu, double kT, mar_precision prec,
                          mar_form form) {
     if (n_seeds < 0) return set_err(c, MAR_ERR_ARG, "n_seeds < 0");
@@ -1078,6 +1190,14 @@ mar_status dispatch_solve(mar_ctx* c, const mar_request& r, const Plan& pl, hipS
                                "least %d seeds (block %d)", vec, pl.B));
     }
     mar_status st;
+    if (pl.seedwise) {
+        // the blocks' default would have run two of them in flight here: mar_solve_many goes on refusing the context
+        hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+        if (!c->dry && !c->in_graph && !c->prof && c->es.mode == 0 && c->loc >= 6 && c->tune.two_streams == 0 &&
+            r.n_seeds > pl.B && hipStreamIsCapturing(s, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone)
+            c->ran_two_sets = true;
+        return r.prec == MAR_FP32 ? run_seedwise<float>(c, r, s) : run_seedwise<double>(c, r, s);
+    }
     if (r.prec == MAR_FP32)
         st = pl.delayed ? run_solve_delayed<float>(c, r.d_seeds, r.n_seeds, r.nu, r.mu, r.kT, pl.B, pl.variant,
                                                    r.d_rho, r.d_e_band, r.d_e_seed, r.d_n_seed, r.d_nu_eff,
@@ -1157,6 +1277,7 @@ void put_request(std::vector<char>& k, mar_ctx* c, const mar_request& r, const P
     put(k, pl.B);
     put(k, (int32_t)pl.delayed);
     put(k, pl.variant);
+    put(k, (int32_t)pl.seedwise);
     put(k, c->tune);
     put(k, c->loc);
     put(k, c->ws);
@@ -1229,6 +1350,7 @@ mar_status mar_create(int64_t M, const int64_t* H_rowptr, const int32_t* H_col, 
     if ((st = upload(c, &c->Hval, H_val, (size_t)c->nnzH)) != MAR_OK) return fail(st);
     if ((st = upload(c, &c->SvalH, svalH.data(), svalH.size())) != MAR_OK) return fail(st);
     if ((st = upload(c, &c->diagS, diag.data(), diag.size())) != MAR_OK) return fail(st);
+    if ((st = upload(c, &c->d_loc, (const int32_t*)nullptr, 1)) != MAR_OK) return fail(st);
     he = hipStreamCreate(&c->stream);
     if (he == hipSuccess) he = hipStreamCreateWithFlags(&c->stream2, hipStreamNonBlocking);
     if (he == hipSuccess) he = hipEventCreateWithFlags(&c->ev_fork, hipEventDisableTiming);
@@ -1862,6 +1984,17 @@ mar_status mar_set_local_region(mar_ctx* c, int32_t hops) {
     if (!c) return MAR_ERR_STATE;
     if (hops >= 0 && (!c->H.bsr || c->SH.nnz != c->H.nnz))
         return set_err(c, MAR_ERR_ARG, "a local region needs H with 4x4 block structure");
+    if (hops >= 0 && hops != c->loc) {
+        // the largest region's block rows: whether one workgroup can hold a seed's region
+        int32_t n = 0;
+        c->loc_blocks = 0;
+        if (hipSetDevice(c->device) == hipSuccess &&
+            mar::launch_region_max(c->H.n, c->H.ptr, c->H.idx, hops, mar::SEED_MAX_BLOCKS, c->d_loc, c->stream).wgs > 0 &&
+            hipMemcpyAsync(&n, c->d_loc, 4, hipMemcpyDeviceToHost, c->stream) == hipSuccess &&
+            hipStreamSynchronize(c->stream) == hipSuccess && n <= mar::SEED_MAX_BLOCKS)
+            c->loc_blocks = n;
+        (void)hipGetLastError();
+    }
     c->loc = hops < 0 ? -1 : hops;
     return MAR_OK;
 }
@@ -2012,7 +2145,12 @@ mar_status solve_async_ext(mar_ctx* c, const int32_t* d_seeds, int64_t n_seeds, 
         c->dry = true;
         st = dispatch_solve(c, r, pl, s);
         c->dry = false;
-        if (st == MAR_OK || !c->ext_short || !shrink || pl.B / 2 < min_b) break;
+        if (st == MAR_OK || !c->ext_short) break;
+        if (pl.seedwise) {   // the blocks may still fit
+            pl.seedwise = false;
+            continue;
+        }
+        if (!shrink || pl.B / 2 < min_b) break;
         pl.B /= 2;
     }
     if (st == MAR_OK) st = dispatch_solve(c, r, pl, s);

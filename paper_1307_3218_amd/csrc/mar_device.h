@@ -4,6 +4,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <atomic>
+
 namespace mar {
 
 // 16-byte vector of T: one global_load/store_dwordx4 per lane.
@@ -73,6 +75,68 @@ __device__ __forceinline__ int64_t xcd_chunk(int64_t bid, int64_t chunk) {
     return ((l / chunk) * NX + x) * chunk + l % chunk;
 }
 
+// 1/x and 1/sqrt(x) (x > 0, normal) from the hardware estimates and two Newton steps each (full FP64
+// precision: the estimates carry about 23 bits and each step doubles them).
+__device__ __forceinline__ double recip(double x) {
+    double y = __builtin_amdgcn_rcp(x);
+    double e = fma(-x, y, 1.0);
+    y = fma(y, e, y);
+    e = fma(-x, y, 1.0);
+    return fma(y, e, y);
+}
+__device__ __forceinline__ double rsqrt_nr(double x) {
+    double y = __builtin_amdgcn_rsq(x);
+    double e = fma(-x * y, y, 1.0);
+    y = fma(0.5 * y, e, y);
+    e = fma(-x * y, y, 1.0);
+    return fma(0.5 * y, e, y);
+}
+
+// Moves between lanes without LDS. dpp_move<CTRL>(v): v of the lane that the DPP control names (0xb1: lane ^ 1, 0x4e:
+// lane ^ 2, 0x141: 7 - lane within eight lanes, 0x140: 15 - lane within a row of 16, 0x128: lane ^ 8).
+template <int CTRL>
+__device__ __forceinline__ double dpp_move(double v) {
+    const uint64_t x = __builtin_bit_cast(uint64_t, v);
+    const unsigned lo = (unsigned)__builtin_amdgcn_update_dpp(0, (int)(unsigned)x, CTRL, 0xf, 0xf, false);
+    const unsigned hi = (unsigned)__builtin_amdgcn_update_dpp(0, (int)(unsigned)(x >> 32), CTRL, 0xf, 0xf, false);
+    return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+// Lanes 0..31: a + a of lane + 32; lanes 32..63: b + b of lane - 32.
+__device__ __forceinline__ double swap_add32(double a, double b) {
+    const uint64_t x = __builtin_bit_cast(uint64_t, a), y = __builtin_bit_cast(uint64_t, b);
+    const auto lo = __builtin_amdgcn_permlane32_swap((unsigned)x, (unsigned)y, false, false);
+    const auto hi = __builtin_amdgcn_permlane32_swap((unsigned)(x >> 32), (unsigned)(y >> 32), false, false);
+    return __builtin_bit_cast(double, ((uint64_t)hi[0] << 32) | lo[0]) +
+           __builtin_bit_cast(double, ((uint64_t)hi[1] << 32) | lo[1]);
+}
+// Lanes with bit 4 clear: a + a of lane + 16; the others: b + b of lane - 16.
+__device__ __forceinline__ double swap_add16(double a, double b) {
+    const uint64_t x = __builtin_bit_cast(uint64_t, a), y = __builtin_bit_cast(uint64_t, b);
+    const auto lo = __builtin_amdgcn_permlane16_swap((unsigned)x, (unsigned)y, false, false);
+    const auto hi = __builtin_amdgcn_permlane16_swap((unsigned)(x >> 32), (unsigned)(y >> 32), false, false);
+    return __builtin_bit_cast(double, ((uint64_t)hi[0] << 32) | lo[0]) +
+           __builtin_bit_cast(double, ((uint64_t)hi[1] << 32) | lo[1]);
+}
+__device__ __forceinline__ float swap_add32(float a, float b) {
+    const auto r = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(unsigned, a), __builtin_bit_cast(unsigned, b), false, false);
+    const unsigned x = r[0], y = r[1];   // (a bit cast of the vector's element itself reads element 0)
+    return __builtin_bit_cast(float, x) + __builtin_bit_cast(float, y);
+}
+__device__ __forceinline__ float swap_add16(float a, float b) {
+    const auto r = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(unsigned, a), __builtin_bit_cast(unsigned, b), false, false);
+    const unsigned x = r[0], y = r[1];   // (a bit cast of the vector's element itself reads element 0)
+    return __builtin_bit_cast(float, x) + __builtin_bit_cast(float, y);
+}
+// Sum over a wavefront, the same bits in every lane (each exchange adds the same two operands in both lanes).
+__device__ __forceinline__ double wave_sum(double v) {
+    v += dpp_move<0xb1>(v);
+    v += dpp_move<0x4e>(v);
+    v += dpp_move<0x141>(v);
+    v += dpp_move<0x140>(v);
+    v = swap_add16(v, v);
+    return swap_add32(v, v);
+}
+
 // Workgroup reduction of per-seed partial sums (fixed order, deterministic).
 // Thread t holds vals[v][i] for seed (t % P) * SW + i. For every v and every
 // seed b in [0, P*SW) the sum over the workgroup's 256 threads is passed to
@@ -123,6 +187,17 @@ __device__ __forceinline__ void wg_seed_reduce(A (&vals)[NV][SW], A* lds, F&& em
         }
         __syncthreads();
     }
+}
+
+// Lets kernel f use up to 160 KB of dynamic LDS. The attribute belongs to the current device, so it is
+// set once per device (bit d of done for device d; concurrent first calls both set it, which is harmless).
+inline void allow_full_lds(const void* f, std::atomic<uint64_t>& done) {
+    int dev = 0;
+    const bool known = hipGetDevice(&dev) == hipSuccess && dev >= 0 && dev < 64;
+    const uint64_t bit = known ? 1ull << dev : 0;
+    if (known && (done.load(std::memory_order_acquire) & bit)) return;
+    (void)hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+    if (known) done.fetch_or(bit, std::memory_order_acq_rel);
 }
 
 }  // namespace mar

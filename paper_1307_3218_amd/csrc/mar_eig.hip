@@ -16,7 +16,6 @@
 // (K^T S e_j = sqrt(S_jj) e_1 because u_1 = e_j / sqrt(S_jj) and K^T S K = I),
 //     E_j = sum_{i in P(j)} rho_ij H_ij,   N_j = sum_{i in P(j)} rho_ij S_ij.
 #include <algorithm>
-#include <atomic>
 #include <cfloat>
 #include <cstdint>
 
@@ -65,23 +64,6 @@ constexpr int EIG_WAVES = EIG_WG / 64;
 // Per-thread work lists of a Jacobi step when they are short (at most JB blocks
 // and JR entries of R per thread, fixed for the whole iteration).
 constexpr int JB = 3, JR = 4;
-
-// 1/x and 1/sqrt(x) (x > 0, normal) from the hardware estimates and two Newton steps each (full FP64
-// precision: the estimates carry about 23 bits and each step doubles them).
-__device__ __forceinline__ double recip(double x) {
-    double y = __builtin_amdgcn_rcp(x);
-    double e = fma(-x, y, 1.0);
-    y = fma(y, e, y);
-    e = fma(-x, y, 1.0);
-    return fma(y, e, y);
-}
-__device__ __forceinline__ double rsqrt(double x) {
-    double y = __builtin_amdgcn_rsq(x);
-    double e = fma(-x * y, y, 1.0);
-    y = fma(0.5 * y, e, y);
-    e = fma(-x * y, y, 1.0);
-    return fma(0.5 * y, e, y);
-}
 
 // Parallel cyclic Jacobi on the symmetric m x m matrix A (in LDS or global
 // memory, upper triangle only: a_ij, i <= j, at A[i * ld + j]; an odd ld spreads
@@ -171,9 +153,9 @@ __device__ __forceinline__ int jacobi_eig(double* A, int ld, int m, double* R, i
                             t = 0.5 * recip(tau);
                         } else {
                             const double r = 1.0 + tau * tau;
-                            t = copysign(recip(fabs(tau) + r * rsqrt(r)), tau);
+                            t = copysign(recip(fabs(tau) + r * rsqrt_nr(r)), tau);
                         }
-                        c = rsqrt(1.0 + t * t);
+                        c = rsqrt_nr(1.0 + t * t);
                         sv = t * c;
                         atomicAdd(cnt, 1);
                     }
@@ -493,17 +475,6 @@ __global__ __launch_bounds__(EIG_WG) void k_eig(EigExtra ex, int nseeds, const i
         n_seed[b] = N;
         nu_eff_out[b] = m;
     }
-}
-
-// Lets kernel f use up to 160 KB of dynamic LDS. The attribute belongs to the current device, so it is
-// set once per device (bit d of done for device d; concurrent first calls both set it, which is harmless).
-static void allow_full_lds(const void* f, std::atomic<uint64_t>& done) {
-    int dev = 0;
-    const bool known = hipGetDevice(&dev) == hipSuccess && dev >= 0 && dev < 64;
-    const uint64_t bit = known ? 1ull << dev : 0;
-    if (known && (done.load(std::memory_order_acquire) & bit)) return;
-    (void)hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-    if (known) done.fetch_or(bit, std::memory_order_acq_rel);
 }
 
 LaunchInfo launch_eig(int nseeds, const int32_t* seeds, int nu, double* h, const int32_t* nu_eff_blk,

@@ -290,6 +290,28 @@ constexpr int max_block() { return sizeof(T) == 4 ? 256 : 128; }
 size_t eig_lds_bytes(int nu, int max_row, bool a_in_lds);
 bool eig_a_fits_lds(int nu, int max_row);
 
+// ---- one workgroup per seed (small regions and cells) ----
+constexpr int SEED_MAX_BLOCKS = 2048;   // block rows of a seed's row set
+// Launch shape of k_seed for row sets of at most nbcap block rows: offsets (bytes) into the dynamic LDS, basis vectors
+// kept there, elements of scratch per workgroup.
+struct SeedGeom {
+    bool ok;
+    int64_t nbrow, sstride;
+    int nbcap, hs, threads, grid;
+    int oU, oD, oC, oList, oCol;
+    size_t kbytes, lds;
+};
+SeedGeom seed_geometry(int64_t nbrow, int64_t nnzb, int blocks_per_row, int hops, int64_t nbcap, int nu, size_t elem,
+                       int64_t ns, int n_cu);
+template <typename T>
+LaunchInfo launch_seed(const SeedGeom& g, const DevMat& H, const DevMat& SH, int64_t M, const double* diagS,
+                       const int32_t* seeds, int ns, int nu, int hops, double tau, T* scratch, const int32_t* Hrp,
+                       int max_row, double* h, double* Kp, int32_t* nu_out, const double* vref, double* pref, int64_t pB,
+                       bool acc64, hipStream_t s);
+// Largest number of block rows within hops of any block row (cap + 1: more than cap) into out[0].
+LaunchInfo launch_region_max(int64_t nbrow, const int32_t* brp, const int32_t* bcol, int hops, int cap, int32_t* out,
+                             hipStream_t s);
+
 // The device a context lives on (-1 for NULL).
 int ctx_device(const mar_ctx* c);
 // Record msg as the context's last error and return st.
