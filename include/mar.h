@@ -126,9 +126,11 @@ typedef struct {
                               eigen-state passes or inside mar_solve_many's graphs; the caller's stream
                               waits for the second one before the solve's last kernel. The results do
                               not depend on it. */
-    int32_t eig_max_sweeps; /* Jacobi sweeps allowed to the nu x nu subspace eigensolve (0 = 40; about
-                              ten are needed at nu = 100). A seed whose eigensolve has not converged
-                              after them gets nu_eff = -3 (see mar_solve). */
+    int32_t eig_max_sweeps; /* 0: the nu x nu subspace eigensolve by Householder reduction and implicit QL
+                              (up to 60 iterations per level; about two are needed); > 0: by the parallel
+                              cyclic Jacobi method with at most this many sweeps (about ten are needed at
+                              nu = 100). A seed whose eigensolve has not converged within its limit gets
+                              nu_eff = -3 (see mar_solve). */
 } mar_tuning;
 
 /* Create a context from host CSR arrays of H and S (M x M, 0-based, columns
@@ -150,9 +152,9 @@ void mar_destroy(mar_ctx* ctx);
 
 /* Host-side solve (blocking). seeds: n_seeds distinct indices in [0, M)
  * (MAR_ERR_ARG otherwise); 1 <= nu <= M; mu finite; kT >= 0 and finite.
- * The subspace eigensolve (Sec. 2: the nu x nu standard eigenproblem) is the
- * parallel cyclic Jacobi method; a seed whose eigensolve has not converged
- * after eig_max_sweeps sweeps (mar_tuning) gets nu_eff = -3, NaN in its rho
+ * A seed whose subspace eigensolve (Sec. 2: the nu x nu standard eigenproblem)
+ * has not converged within its limit (mar_tuning, eig_max_sweeps) gets
+ * nu_eff = -3, NaN in its rho
  * slots, E_j, N_j, eps and weight entries (so e_band is NaN), and the call
  * returns MAR_ERR_NOCONV naming the seed.
  * Outputs (host, caller-allocated):

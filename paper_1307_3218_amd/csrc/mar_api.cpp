@@ -508,10 +508,11 @@ mar_status ensure_ws(mar_ctx* c, size_t bytes) {
 // The eigensolve and assembly of one seed block, or one of the eigen-state passes.
 template <typename T>
 void eig_stage(mar_ctx* c, hipStream_t s, int B, int ns, const int32_t* seeds, int nu, double* h, const int32_t* nucp,
-               const double* Kp, const T* K, int64_t stride, int64_t Mp, double mu, double kT, double* rho,
+               double* Kp, const T* K, int64_t stride, int64_t Mp, double mu, double kT, double* rho,
                double* e_seed, double* n_seed, int32_t* nu_out, double* eps, double* w, int64_t blk0) {
     mar::EigExtra ex;
     ex.eig_max_sweeps = c->tune.eig_max_sweeps > 0 ? c->tune.eig_max_sweeps : 40;
+    ex.jacobi = c->tune.eig_max_sweeps > 0;
     if (c->es.mode == 2) {   // v_ref . v_alpha^(j) through K^T v_ref, then the signed Eq. 3 component
         launch(c, s, P_EIG, [&] {
             return mar::launch_es_pdot<T>(B, K, stride, c->M, Mp, nu, c->es.vref, c->es.pdot, c->es.groups, s);
@@ -1121,6 +1122,7 @@ mar_status run_seedwise(mar_ctx* c, const mar_request& r, hipStream_t s) {
         });
         mar::EigExtra ex;
         ex.eig_max_sweeps = c->tune.eig_max_sweeps > 0 ? c->tune.eig_max_sweeps : 40;
+        ex.jacobi = c->tune.eig_max_sweeps > 0;
         if (c->es.mode == 2) {
             ex.mode = 2;
             ex.pref = pref;
@@ -1165,8 +1167,10 @@ mar_status check_noconv(mar_ctx* c, const int32_t* seeds, const std::vector<int3
     for (size_t i = 0; i < nuv.size(); ++i)
         if (nuv[i] == mar::NU_NOCONV)
             return set_err(c, MAR_ERR_NOCONV,
-                           fmt("the subspace eigensolve of seed %d did not converge within %d Jacobi sweeps", seeds[i],
-                               c->tune.eig_max_sweeps > 0 ? c->tune.eig_max_sweeps : 40));
+                           c->tune.eig_max_sweeps > 0
+                               ? fmt("the subspace eigensolve of seed %d did not converge within %d Jacobi sweeps", seeds[i],
+                                     c->tune.eig_max_sweeps)
+                               : fmt("the subspace eigensolve of seed %d did not converge", seeds[i]));
     return MAR_OK;
 }
 

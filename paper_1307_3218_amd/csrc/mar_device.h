@@ -101,6 +101,13 @@ __device__ __forceinline__ double dpp_move(double v) {
     const unsigned hi = (unsigned)__builtin_amdgcn_update_dpp(0, (int)(unsigned)(x >> 32), CTRL, 0xf, 0xf, false);
     return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
 }
+// v of lane k (k the same in every lane).
+__device__ __forceinline__ double read_lane(double v, int k) {
+    const uint64_t x = __builtin_bit_cast(uint64_t, v);
+    const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)x, k);
+    const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)(x >> 32), k);
+    return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
 // Lanes 0..31: a + a of lane + 32; lanes 32..63: b + b of lane - 32.
 __device__ __forceinline__ double swap_add32(double a, double b) {
     const uint64_t x = __builtin_bit_cast(uint64_t, a), y = __builtin_bit_cast(uint64_t, b);

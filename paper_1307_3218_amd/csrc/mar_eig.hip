@@ -1,13 +1,10 @@
-// Subspace eigensolve and Fermi-weighted assembly, one workgroup per seed.
+// Subspace eigensolve and Fermi-weighted assembly.
 //
 // For seed j with m = nu_eff vectors, A = K^T H K (m x m, FP64) is
-// diagonalized by the parallel cyclic Jacobi method: each step rotates m / 2
-// disjoint index pairs at once (a round-robin tournament, so that every pair
-// meets once per sweep of m - 1 steps or m steps for odd m), A <- J^T A J,
-// and the same rotations are applied to the rows of the m x (1 + |P(j)|)
-// matrix R = [e_1 | K[P(j), :]^T]; sweeps repeat until one rotates nothing.
-// No m x m eigenvector matrix is formed. At the end A's diagonal holds the
-// levels eps_alpha and row alpha of R holds
+// diagonalized, and the same rotations are applied to the rows of the
+// m x (1 + |P(j)|) matrix R = [e_1 | K[P(j), :]^T]. No m x m eigenvector
+// matrix is formed. At the end the levels eps_alpha are known and row alpha of
+// R holds
 //     R[alpha][0]     = y_1alpha            (first component of y_alpha)
 //     R[alpha][1 + t] = e_i . v_alpha,  i = P(j)[t],  v_alpha = K y_alpha
 // which is all the Green's-function assembly needs (Sec. 2):
@@ -15,6 +12,14 @@
 //     w_alpha = (e_j^T S v_alpha)(v_alpha^T e_j) = sqrt(S_jj) y_1alpha (e_j.v_alpha)
 // (K^T S e_j = sqrt(S_jj) e_1 because u_1 = e_j / sqrt(S_jj) and K^T S K = I),
 //     E_j = sum_{i in P(j)} rho_ij H_ij,   N_j = sum_{i in P(j)} rho_ij S_ij.
+//
+// Two methods: Householder reduction to tridiagonal form and implicit QL
+// (k_tri, k_tri_big, k_ql; the ordinary passes), and the parallel cyclic
+// Jacobi method (k_eig; all eigenvectors of the reference seed of an eigen
+// state, solves with a cap on Jacobi sweeps, rows too long for a wavefront):
+// each step rotates m / 2 disjoint index pairs at once (a round-robin
+// tournament, so that every pair meets once per sweep of m - 1 steps or m
+// steps for odd m), A <- J^T A J; sweeps repeat until one rotates nothing.
 #include <algorithm>
 #include <cfloat>
 #include <cstdint>
@@ -275,6 +280,145 @@ __global__ __launch_bounds__(WG) void k_gather_rows(int nseeds, const int32_t* _
     }
 }
 
+// Orders LDS among the lanes of one wavefront, and among NT threads that share a seed (64: one wavefront).
+__device__ __forceinline__ void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+template <int NT>
+__device__ __forceinline__ void group_sync() {
+    if constexpr (NT == 64) wave_sync();
+    else __syncthreads();
+}
+
+// What a seed's eigenpairs give, run by NT threads (a workgroup of them, or NT = 64: one of its
+// wavefronts): R's rows hold y_1alpha, then e_i.v_alpha
+// (i in P(j)), then (mode 2) v_ref.v_alpha; d the levels. The Eq. 3 component (mode 2), or the kept rows for an
+// assembly at a Fermi level found later (zc; k_assemble takes the same sums in the same order), or the Fermi-weighted
+// assembly. fz: m doubles, rhoL: 64 doubles of LDS.
+template <int NT>
+__device__ __forceinline__ void eig_results(const EigExtra& ex, int b, int m, int nu, const double* R, int NR,
+                                            const double* d, double* fz, double* rhoL, int tj, int rlo, int nP, double sq,
+                                            int max_row, double mu, double kT, const double* __restrict__ Hval,
+                                            const double* __restrict__ SvalH, double* __restrict__ rho,
+                                            double* __restrict__ e_seed, double* __restrict__ n_seed,
+                                            int32_t* __restrict__ nu_eff_out, double* eps_b, double* w_b, double* zc) {
+    const int tid = threadIdx.x % NT;
+    if (ex.mode == 2) {   // Eq. 3 with the inner-product signs: sum_alpha s_alpha (e_j.v_alpha) window_alpha
+        const double lo = ex.win[1], hi = ex.win[2];
+        for (int a = tid; a < m; a += NT) {
+            const double c = R[a * NR + 1 + tj] * level_window(d[a], lo, hi, ex.sigma);
+            fz[a] = R[a * NR + NR - 1] >= 0.0 ? c : -c;
+        }
+        group_sync<NT>();
+        if (tid == 0) {
+            double phi = 0.0;
+            for (int a = 0; a < m; ++a) phi += fz[a];
+            ex.phi[b] = phi;
+            nu_eff_out[b] = m;
+        }
+        return;
+    }
+    if (zc != nullptr) {
+        double* zb = zc + (int64_t)b * nu * max_row;
+        for (int idx = tid; idx < m * nP; idx += NT) {
+            const int a = idx / nP, t = idx - a * nP;
+            zb[a * max_row + t] = R[a * NR + 1 + t];
+        }
+        for (int a = tid; a < m; a += NT) {
+            eps_b[a] = d[a];
+            w_b[a] = sq * R[a * NR] * R[a * NR + 1 + tj];
+        }
+        for (int a = m + tid; a < nu; a += NT) {
+            eps_b[a] = 0.0;
+            w_b[a] = 0.0;
+        }
+        if (tid == 0) nu_eff_out[b] = m;
+        return;
+    }
+    for (int a = tid; a < m; a += NT) {
+        const double ea = d[a];
+        const double zj = R[a * NR + 1 + tj];
+        fz[a] = fermi_occ(ea, mu, kT) * zj;
+        if (eps_b) eps_b[a] = ea;
+        if (w_b) w_b[a] = sq * R[a * NR] * zj;
+    }
+    for (int a = m + tid; a < nu; a += NT) {
+        if (eps_b) eps_b[a] = 0.0;
+        if (w_b) w_b[a] = 0.0;
+    }
+    group_sync<NT>();
+    for (int cb = 0; cb < nP; cb += NT / 8) {
+        const int t = cb + (tid >> 3), pi = tid & 7;
+        double s = 0.0;
+        if (t < nP)
+            for (int a = pi; a < m; a += 8) s += fz[a] * R[a * NR + 1 + t];
+        s += __shfl_xor(s, 1);
+        s += __shfl_xor(s, 2);
+        s += __shfl_xor(s, 4);
+        if (t < nP && pi == 0) {
+            const double r = 2.0 * s;
+            rho[rlo + t] = r;
+            rhoL[t] = r;
+        }
+    }
+    group_sync<NT>();
+    if (tid == 0) {
+        double E = 0.0, N = 0.0;
+        for (int t = 0; t < nP; ++t) {
+            E += rhoL[t] * Hval[rlo + t];
+            N += rhoL[t] * SvalH[rlo + t];
+        }
+        e_seed[b] = E;
+        n_seed[b] = N;
+        nu_eff_out[b] = m;
+    }
+}
+
+// The outputs of a seed whose eigensolve did not converge: NU_NOCONV, and NaN in every output.
+template <int NT>
+__device__ __forceinline__ void eig_failed(const EigExtra& ex, int b, int m, int nu, int rlo, int nP, double* __restrict__ rho,
+                                           double* __restrict__ e_seed, double* __restrict__ n_seed,
+                                           int32_t* __restrict__ nu_eff_out, double* eps_b, double* w_b, const double* zc) {
+    const int tid = threadIdx.x % NT;
+    const double nan = __builtin_nan("");
+    if (ex.mode == 1) {
+        for (int idx = tid; idx < m * m; idx += NT) {
+            const int a = idx / m, c = idx - a * m;
+            ex.Y[((int64_t)b * nu + a) * nu + c] = nan;
+        }
+    } else if (ex.mode == 2) {
+        if (tid == 0) ex.phi[b] = nan;
+    } else if (zc == nullptr) {
+        for (int t = tid; t < nP; t += NT) rho[rlo + t] = nan;
+        if (tid == 0) {
+            e_seed[b] = nan;
+            n_seed[b] = nan;
+        }
+    }
+    for (int a = tid; a < nu; a += NT) {
+        if (eps_b) eps_b[a] = nan;
+        if (w_b) w_b[a] = nan;
+    }
+    if (tid == 0) nu_eff_out[b] = NU_NOCONV;
+}
+
+// A seed without a subspace (outside the matrix, S not positive definite, padding).
+template <int NT>
+__device__ __forceinline__ void eig_empty(int b, int m, int nu, double* __restrict__ e_seed, double* __restrict__ n_seed,
+                                          int32_t* __restrict__ nu_eff_out, double* eps_b, double* w_b) {
+    if (threadIdx.x % NT == 0) {
+        nu_eff_out[b] = m;
+        e_seed[b] = 0.0;
+        n_seed[b] = 0.0;
+    }
+    for (int a = threadIdx.x % NT; a < nu; a += NT) {
+        if (eps_b) eps_b[a] = 0.0;
+        if (w_b) w_b[a] = 0.0;
+    }
+}
+
 template <bool LDS_A>
 __global__ __launch_bounds__(EIG_WG) void k_eig(EigExtra ex, int nseeds, const int32_t* __restrict__ seeds, int nu,
                                             double* __restrict__ h, const int32_t* __restrict__ nu_eff_blk,
@@ -293,15 +437,7 @@ __global__ __launch_bounds__(EIG_WG) void k_eig(EigExtra ex, int nseeds, const i
     double* eps_b = eps_out ? eps_out + (int64_t)b * nu : nullptr;
     double* w_b = w_out ? w_out + (int64_t)b * nu : nullptr;
     if (m <= 0) {
-        if (tid == 0) {
-            nu_eff_out[b] = m;
-            e_seed[b] = 0.0;
-            n_seed[b] = 0.0;
-        }
-        for (int a = tid; a < nu; a += EIG_WG) {
-            if (eps_b) eps_b[a] = 0.0;
-            if (w_b) w_b[a] = 0.0;
-        }
+        eig_empty<EIG_WG>(b, m, nu, e_seed, n_seed, nu_eff_out, eps_b, w_b);
         return;
     }
     const int j = seeds[b];
@@ -370,33 +506,10 @@ __global__ __launch_bounds__(EIG_WG) void k_eig(EigExtra ex, int nseeds, const i
     }
     __syncthreads();
     if (*failp != 0) {
-        // an eigenvalue is still unconverged: the seed reports NU_NOCONV and NaN in every output
-        const double nan = __builtin_nan("");
-        if (ex.mode == 1) {
-            for (int idx = tid; idx < m * m; idx += EIG_WG) {
-                const int a = idx / m, c = idx - a * m;
-                ex.Y[((int64_t)b * nu + a) * nu + c] = nan;
-            }
-        } else if (ex.mode == 2) {
-            if (tid == 0) ex.phi[b] = nan;
-        } else if (zc == nullptr) {
-            for (int t = tid; t < nP; t += EIG_WG) rho[rlo + t] = nan;
-            if (tid == 0) {
-                e_seed[b] = nan;
-                n_seed[b] = nan;
-            }
-        }
-        for (int a = tid; a < nu; a += EIG_WG) {
-            if (eps_b) eps_b[a] = nan;
-            if (w_b) w_b[a] = nan;
-        }
-        if (tid == 0) nu_eff_out[b] = NU_NOCONV;
+        eig_failed<EIG_WG>(ex, b, m, nu, rlo, nP, rho, e_seed, n_seed, nu_eff_out, eps_b, w_b, zc);
         return;
     }
 
-    // Fermi-weighted assembly, or (zc != nullptr) keep the rows e_i.v_alpha,
-    // i in P(j), for an assembly at a Fermi level found later (k_assemble).
-    const int tj = *tjp;
     const double sq = sqrt(diagS[j]);
     if (ex.mode == 1) {   // the full subspace eigenvectors y_alpha and levels
         for (int idx = tid; idx < m * m; idx += EIG_WG) {
@@ -407,82 +520,489 @@ __global__ __launch_bounds__(EIG_WG) void k_eig(EigExtra ex, int nseeds, const i
         if (tid == 0) nu_eff_out[b] = m;
         return;
     }
-    if (ex.mode == 2) {   // Eq. 3 with the inner-product signs: sum_alpha s_alpha (e_j.v_alpha) window_alpha
-        if (tid == 0) {
-            const double lo = ex.win[1], hi = ex.win[2];
-            double phi = 0.0;
-            for (int a = 0; a < m; ++a) {
-                const double c = R[a * NR + 1 + tj] * level_window(d[a], lo, hi, ex.sigma);
-                phi += R[a * NR + NR - 1] >= 0.0 ? c : -c;
+    eig_results<EIG_WG>(ex, b, m, nu, R, NR, d, q, rhoL, *tjp, rlo, nP, sq, max_row, mu, kT, Hval, SvalH, rho, e_seed, n_seed,
+                        nu_eff_out, eps_b, w_b, zc);
+}
+
+// ---------------------------------------------------------------------------
+// The eigensolve of the ordinary passes: Householder reduction of A to tridiagonal form (k_tri, k_tri_big), then the
+// implicit QL iteration (k_ql). Every reflector and rotation is applied to R's columns K[P(j), :]^T (and K^T v_ref) as
+// well; the reflectors leave the first basis vector alone, so R's column e_1 enters at the QL iteration. The Jacobi
+// iteration above takes about ten sweeps of m - 1 steps over all of A; this takes one reduction over A and about
+// 0.85 m^2 rotations of two rows of R.
+//
+// k_tri: A's rows and, below them, R's columns as further rows, in the registers of 512 threads (m <= 16 CJ, at most
+// 32 RI rows in all): thread (tr, tc) holds rows tr + 32 i and columns tc + 16 j. With v = 0 and w = tau p on the
+// further rows, p = A v and A -= v w^T + w v^T are one formula for all rows. The column of a step and the products p
+// go through LDS, twice buffered, two barriers a step. The reflector 1 - tau v v^T keeps v unscaled (v is the column
+// but for its first element, tau = 1 / (|beta| (|beta| + |alpha|))), so that the products need not wait for a
+// reciprocal. d and e leave in the first two rows of the seed's h, R's columns where they were. What bounds it: the
+// latency of a step (two sums over a wavefront, one over 16 lanes, a reciprocal square root, two barriers); 512
+// threads instead of 256 with twice the elements each halve it and leave room for two workgroups on a compute unit
+// (nu = 100, 1024 seeds: 1.30 -> 0.64 ms).
+constexpr int TRI_TH = 512;
+template <int CJ, int RI>
+__global__ __launch_bounds__(TRI_TH, RI <= 4 ? 4 : 2) void k_tri(EigExtra ex, const int32_t* __restrict__ seeds, int nu,
+                                                double* __restrict__ h, const int32_t* __restrict__ nu_eff_blk,
+                                                double* __restrict__ Kp, const int32_t* __restrict__ Hrp, int max_row,
+                                                double* __restrict__ pref) {
+    constexpr int NX = 16 * CJ;               // elements of a column (zero past m)
+    __shared__ double xs[2][NX], ps[2][32 * RI], dd[NX], ee[NX], amx[TRI_TH / 64];
+    const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, tr = tid >> 4, tc = tid & 15;
+    const int m = nu_eff_blk[b];
+    if (m <= 0) return;
+    const int j0 = seeds[b], nP = Hrp[j0 + 1] - Hrp[j0], nR = nP + (ex.mode == 2 ? 1 : 0);
+    double* hb = h + (int64_t)b * nu * nu;
+    double* kb = Kp + (int64_t)b * nu * max_row;
+    double A[RI][CJ];
+    double mx = 0.0;
+#pragma unroll
+    for (int ii = 0; ii < RI; ++ii)
+#pragma unroll
+        for (int jj = 0; jj < CJ; ++jj) {
+            const int i = tr + 32 * ii, c = tc + 16 * jj;
+            double v = 0.0;
+            if (c < m) {
+                if (i < m) v = hb[(int64_t)min(i, c) * nu + max(i, c)];
+                else if (i - m < nP) v = kb[(int64_t)c * max_row + (i - m)];
+                else if (i - m < nR) v = pref[(int64_t)c * ex.pB + b];
+                if (i < m) mx = fmax(mx, fabs(v));
             }
-            ex.phi[b] = phi;
-            nu_eff_out[b] = m;
+            A[ii][jj] = v;
         }
-        return;
-    }
-    if (zc != nullptr) {
-        double* zb = zc + (int64_t)b * nu * max_row;
-        for (int idx = tid; idx < m * nP; idx += EIG_WG) {
-            const int a = idx / nP, t = idx - a * nP;
-            zb[a * max_row + t] = R[a * NR + 1 + t];
+    // A scaled to a largest entry in [1/2, 1), so that the squares of a step stay in range
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) mx = fmax(mx, __shfl_xor(mx, o));
+    if (lane == 0) amx[wave] = mx;
+    __syncthreads();
+    mx = 0.0;
+#pragma unroll
+    for (int i = 0; i < TRI_TH / 64; ++i) mx = fmax(mx, amx[i]);
+    const int sc = mx > 0.0 && mx < INFINITY ? -ilogb(mx) - 1 : 0;
+#pragma unroll
+    for (int ii = 0; ii < RI; ++ii)
+#pragma unroll
+        for (int jj = 0; jj < CJ; ++jj)
+            if (tr + 32 * ii < m) A[ii][jj] = ldexp(A[ii][jj], sc);
+    for (int k = 0; k + 2 < m; ++k) {
+        double* x = xs[k & 1];
+        double* p = ps[k & 1];
+        // column k below the diagonal, zeros elsewhere
+#pragma unroll
+        for (int jj = 0; jj < CJ; ++jj)
+            if (jj == (k >> 4) && tc == (k & 15)) {
+#pragma unroll
+                for (int ii = 0; ii < RI; ++ii) {
+                    const int i = tr + 32 * ii;
+                    if (i == k) dd[k] = A[ii][jj];
+                    if (i < NX) x[i] = i > k && i < m ? A[ii][jj] : 0.0;
+                }
+            }
+        __syncthreads();
+        double n2 = 0.0;                       // every wavefront the same
+        for (int i = lane; i < NX; i += 64) n2 = fma(x[i], x[i], n2);
+        n2 = wave_sum(n2);
+        const double al = x[k + 1];
+        double beta = al, tau = 0.0, v1 = 0.0;
+        const bool refl = n2 > 1e-290 && n2 > al * al;   // else the column is in form (to 1e-145 of A's scale)
+        if (refl) {
+            const double r = n2 * rsqrt_nr(n2);
+            beta = -copysign(r, al);
+            v1 = al - beta;
+            tau = recip(fma(r, fabs(al), n2));
         }
-        for (int a = tid; a < m; a += EIG_WG) {
-            eps_b[a] = d[a];
-            w_b[a] = sq * R[a * NR] * R[a * NR + 1 + tj];
+        if (tid == 0) ee[k] = beta;
+        auto vat = [&](int i) { return refl ? (i == k + 1 ? v1 : x[i]) : 0.0; };
+        double vj[CJ], sr[RI];
+#pragma unroll
+        for (int jj = 0; jj < CJ; ++jj) vj[jj] = vat(tc + 16 * jj);
+        // p = A v: over the thread's columns, then over the 16 threads of a row
+#pragma unroll
+        for (int ii = 0; ii < RI; ++ii) {
+            sr[ii] = 0.0;
+            if (32 * ii + 31 <= k) continue;   // rows done with (uniform)
+#pragma unroll
+            for (int jj = 0; jj < CJ; ++jj) sr[ii] = fma(A[ii][jj], vj[jj], sr[ii]);
         }
-        for (int a = m + tid; a < nu; a += EIG_WG) {
-            eps_b[a] = 0.0;
-            w_b[a] = 0.0;
+#pragma unroll
+        for (int ii = 0; ii < RI; ++ii) {
+            if (32 * ii + 31 <= k) continue;
+            sr[ii] += dpp_move<0xb1>(sr[ii]);
+            sr[ii] += dpp_move<0x4e>(sr[ii]);
+            sr[ii] += dpp_move<0x141>(sr[ii]);
+            sr[ii] += dpp_move<0x140>(sr[ii]);
+            if (tc == 0) p[tr + 32 * ii] = sr[ii];
         }
-        if (tid == 0) nu_eff_out[b] = m;
-        return;
-    }
-    double* fz = q;
-    for (int a = tid; a < m; a += EIG_WG) {
-        const double ea = d[a];
-        const double zj = R[a * NR + 1 + tj];
-        fz[a] = fermi_occ(ea, mu, kT) * zj;
-        if (eps_b) eps_b[a] = ea;
-        if (w_b) w_b[a] = sq * R[a * NR] * zj;
-    }
-    for (int a = m + tid; a < nu; a += EIG_WG) {
-        if (eps_b) eps_b[a] = 0.0;
-        if (w_b) w_b[a] = 0.0;
+        __syncthreads();
+        double pv = 0.0, wj[CJ];
+        for (int i = lane; i < NX; i += 64) pv += i > k ? p[i] * vat(i) : 0.0;
+#pragma unroll
+        for (int jj = 0; jj < CJ; ++jj) wj[jj] = p[tc + 16 * jj];
+        pv = wave_sum(pv);
+        const double kk = 0.5 * tau * tau * pv;   // w = tau p - kk v
+#pragma unroll
+        for (int jj = 0; jj < CJ; ++jj) wj[jj] = fma(tau, wj[jj], -kk * vj[jj]);
+#pragma unroll
+        for (int ii = 0; ii < RI; ++ii) {
+            if (32 * ii + 31 <= k) continue;
+            const int i = tr + 32 * ii;
+            const double vi = i < m ? vat(i < NX ? i : 0) : 0.0, wi = fma(tau, sr[ii], -kk * vi);
+#pragma unroll
+            for (int jj = 0; jj < CJ; ++jj) A[ii][jj] = fma(-vi, wj[jj], fma(-wi, vj[jj], A[ii][jj]));
+        }
     }
     __syncthreads();
-    for (int cb = 0; cb < nP; cb += EIG_WG / 8) {
-        const int t = cb + (tid >> 3), pi = tid & 7;
-        double s = 0.0;
-        if (t < nP)
-            for (int a = pi; a < m; a += 8) s += fz[a] * R[a * NR + 1 + t];
-        s += __shfl_xor(s, 1);
-        s += __shfl_xor(s, 2);
-        s += __shfl_xor(s, 4);
-        if (t < nP && pi == 0) {
-            const double r = 2.0 * s;
-            rho[rlo + t] = r;
-            rhoL[t] = r;
+#pragma unroll
+    for (int ii = 0; ii < RI; ++ii)
+#pragma unroll
+        for (int jj = 0; jj < CJ; ++jj) {
+            const int i = tr + 32 * ii, c = tc + 16 * jj;
+            if (i < m && i == c && i + 2 >= m) dd[i] = A[ii][jj];
+            if (i < m && m >= 2 && i == m - 1 && c == m - 2) ee[c] = A[ii][jj];
+            if (c < m && i >= m) {
+                if (i - m < nP) kb[(int64_t)c * max_row + (i - m)] = A[ii][jj];
+                else if (i - m < nR) pref[(int64_t)c * ex.pB + b] = A[ii][jj];
+            }
         }
-    }
     __syncthreads();
+    for (int i = tid; i < m; i += TRI_TH) hb[i] = ldexp(dd[i], -sc);
+    for (int i = tid; i + 1 < m; i += TRI_TH) hb[nu + i] = ldexp(ee[i], -sc);
+}
+
+// The same reduction for larger m, with A (both triangles, scaled) in global memory in place of h and R's columns as
+// rows in LDS: a pass per step that applies the step before's update to the remaining rows and multiplies them by the
+// new reflector's vector, one wavefront per row. The next column is formed from the updated row before the pass, so
+// that each element of A crosses the L2 once each way per step. Three barriers a step.
+constexpr int TRI_WG = 1024;
+inline size_t tri_big_lds(int nu, int nr) { return ((size_t)nr * nu + 5 * (size_t)nu + nr + 16 + 2) * 8; }
+__global__ __launch_bounds__(TRI_WG) void k_tri_big(EigExtra ex, const int32_t* __restrict__ seeds, int nu, double* h,
+                                                    const int32_t* __restrict__ nu_eff_blk, double* Kp,
+                                                    const int32_t* __restrict__ Hrp, int max_row, double* pref) {
+    extern __shared__ double smem[];
+    constexpr int NW = TRI_WG / 64;
+    const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int m = nu_eff_blk[b];
+    if (m <= 0) return;
+    const int j0 = seeds[b], nP = Hrp[j0 + 1] - Hrp[j0], nR = nP + (ex.mode == 2 ? 1 : 0);
+    double* A = h + (int64_t)b * nu * nu;
+    double* kb = Kp + (int64_t)b * nu * max_row;
+    double* Rt = smem;                       // [nR][m]
+    double* v2 = Rt + (size_t)nR * nu;       // two reflector vectors
+    double* w = v2 + 2 * nu;
+    double* x = w + nu;
+    double* p = x + nu;                      // [m + nR]
+    double* amx = p + nu + nR;
+    double mx = 0.0;
+    for (int i = wave; i < m; i += NW)
+        for (int c = i + lane; c < m; c += 64) mx = fmax(mx, fabs(A[(int64_t)i * nu + c]));
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) mx = fmax(mx, __shfl_xor(mx, o));
+    if (lane == 0) amx[wave] = mx;
+    __syncthreads();
+    mx = 0.0;
+    for (int i = 0; i < NW; ++i) mx = fmax(mx, amx[i]);
+    const int sc = mx > 0.0 && mx < INFINITY ? -ilogb(mx) - 1 : 0;
+    for (int i = wave; i < m; i += NW)
+        for (int c = i + lane; c < m; c += 64) {
+            const double v = ldexp(A[(int64_t)i * nu + c], sc);
+            A[(int64_t)i * nu + c] = v;
+            A[(int64_t)c * nu + i] = v;
+            if (i == 0) x[c] = v;
+        }
+    for (int idx = tid; idx < nR * m; idx += TRI_WG) {
+        const int k = idx / nR, t = idx - k * nR;
+        Rt[(int64_t)t * m + k] = t < nP ? kb[(int64_t)k * max_row + t] : pref[(int64_t)k * ex.pB + b];
+    }
+    double dkeep = 0.0, ekeep = 0.0;   // thread k keeps d_k and e_k (m <= TRI_WG: the launcher)
+    __syncthreads();
+    double ptau = 0.0;
+    for (int k = 0; k + 2 < m; ++k) {
+        double* v = v2 + (k & 1) * nu;
+        const double* vp = v2 + ((k + 1) & 1) * nu;
+        double sg = 0.0;
+        for (int i = k + 2 + lane; i < m; i += 64) sg += x[i] * x[i];
+        sg = wave_sum(sg);
+        const double al = x[k + 1];
+        double beta = al, tau = 0.0, scal = 0.0;
+        if (sg > 0.0) {
+            const double n2 = fma(al, al, sg);
+            beta = -copysign(n2 * rsqrt_nr(n2), al);
+            tau = (beta - al) * recip(beta);
+            scal = recip(al - beta);
+        }
+        if (tid == k) {
+            dkeep = x[k];
+            ekeep = beta;
+        }
+        for (int i = k + 1 + tid; i < m; i += TRI_WG) v[i] = i == k + 1 ? 1.0 : x[i] * scal;
+        __syncthreads();
+        // rows k + 1 .. m - 1 of A, then R's columns: the step before's update, and the product with v
+        for (int r = k + 1 + wave; r < m + nR; r += NW) {
+            double* a = r < m ? A + (int64_t)r * nu : nullptr;
+            double* l = Rt + (int64_t)(r - m) * m;
+            const double vr = k > 0 && r < m ? vp[r] : 0.0, wr = k > 0 ? (r < m ? w[r] : ptau * p[r]) : 0.0;
+            double s = 0.0;
+            if (r < m) {
+#pragma unroll 4
+                for (int c = k + 1 + lane; c < m; c += 64) {
+                    double t = a[c];
+                    if (k > 0) {
+                        t = fma(-vr, w[c], fma(-wr, vp[c], t));
+                        a[c] = t;
+                    }
+                    s = fma(t, v[c], s);
+                }
+            } else {
+                // (column k of R, which the step before's update touches too, takes no further ones)
+                if (k > 0 && lane == 0) l[k] = fma(-wr, vp[k], l[k]);
+                for (int c = k + 1 + lane; c < m; c += 64) {
+                    double t = l[c];
+                    if (k > 0) {
+                        t = fma(-wr, vp[c], t);
+                        l[c] = t;
+                    }
+                    s = fma(t, v[c], s);
+                }
+            }
+            s = wave_sum(s);
+            if (lane == 0) p[r] = s;
+        }
+        __syncthreads();
+        double pv = 0.0;
+        for (int i = k + 1 + lane; i < m; i += 64) pv += p[i] * v[i];
+        pv = wave_sum(pv);
+        const double kk = 0.5 * tau * tau * pv, w1 = tau * p[k + 1] - kk;   // v_{k+1} = 1
+        for (int c = k + 1 + tid; c < m; c += TRI_WG) {
+            const double wc = tau * p[c] - kk * v[c];
+            w[c] = wc;
+            x[c] = A[(int64_t)(k + 1) * nu + c] - wc - w1 * v[c];
+        }
+        ptau = tau;
+        __syncthreads();
+    }
+    // the last two rows and R's columns with the last update
+    const double* vp = v2 + ((m + 1) & 1) * nu;   // of step m - 3
+    if (m >= 3)
+        for (int idx = tid; idx < nR * 2; idx += TRI_WG) {
+            const int t = idx / 2, c = m - 2 + idx % 2;
+            Rt[(int64_t)t * m + c] = fma(-ptau * p[m + t], vp[c], Rt[(int64_t)t * m + c]);
+        }
+    __syncthreads();
+    double dl = 0.0;
     if (tid == 0) {
-        double E = 0.0, N = 0.0;
-        for (int t = 0; t < nP; ++t) {
-            E += rhoL[t] * Hval[rlo + t];
-            N += rhoL[t] * SvalH[rlo + t];
+        dl = A[(int64_t)(m - 1) * nu + m - 1];
+        if (m >= 3) dl -= 2.0 * vp[m - 1] * w[m - 1];
+    }
+    const double dm2 = m >= 2 ? x[m - 2] : 0.0, em2 = m >= 2 ? x[m - 1] : 0.0;
+    __syncthreads();
+    if (tid + 2 < m) {
+        A[tid] = ldexp(dkeep, -sc);
+        A[nu + tid] = ldexp(ekeep, -sc);
+    }
+    if (tid == 0) {
+        A[m - 1] = ldexp(dl, -sc);
+        if (m >= 2) {
+            A[m - 2] = ldexp(dm2, -sc);
+            A[nu + m - 2] = ldexp(em2, -sc);
         }
-        e_seed[b] = E;
-        n_seed[b] = N;
-        nu_eff_out[b] = m;
+    }
+    for (int idx = tid; idx < nR * m; idx += TRI_WG) {
+        const int k = idx / nR, t = idx - k * nR;
+        if (t < nP) kb[(int64_t)k * max_row + t] = Rt[(int64_t)t * m + k];
+        else pref[(int64_t)k * ex.pB + b] = Rt[(int64_t)t * m + k];
     }
 }
 
+// Implicit QL iteration on the tridiagonal (d, e) of a seed with Wilkinson shifts, one wavefront per seed: every lane
+// carries the recurrence of the rotations, lane c applies them to column c of R (rows i + 1 and i of R; row i stays in
+// a register for the next rotation, which takes rows i and i - 1). The next d, e and row of R are requested one
+// rotation ahead. What bounds it: about 1.1 m^2 rotations in sequence, each some forty instructions that one wavefront
+// issues one after the other (an FP64 operation every seven cycles; the recurrence's dependent chain is no longer than
+// that), so the seeds of a launch share the chip: four to a workgroup, one on each SIMD.
+constexpr int QL_MAX_ITER = 60;   // iterations allowed per level (about two are needed)
+inline size_t ql_lds_bytes(int nu, int nr) { return (((size_t)nu * nr + 3 * (size_t)nu + 64) * 8 + 15) & ~(size_t)15; }
+__global__ __launch_bounds__(256) void k_ql(EigExtra ex, int nseeds, const int32_t* __restrict__ seeds, int nu,
+                                           const double* __restrict__ h, const int32_t* __restrict__ nu_eff_blk,
+                                           const double* __restrict__ Kp, const int32_t* __restrict__ Hrp,
+                                           const int32_t* __restrict__ Hcol, const double* __restrict__ Hval,
+                                           const double* __restrict__ SvalH, const double* __restrict__ diagS,
+                                           int max_row, double mu, double kT, double* __restrict__ rho,
+                                           double* __restrict__ e_seed, double* __restrict__ n_seed,
+                                           int32_t* __restrict__ nu_eff_out, double* __restrict__ eps_out,
+                                           double* __restrict__ w_out, double* __restrict__ zc,
+                                           int seed_doubles) {
+    extern __shared__ double smem[];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int b = blockIdx.x * (blockDim.x >> 6) + wave;
+    if (b >= nseeds) return;
+    const int m = nu_eff_blk[b];
+    double* eps_b = eps_out ? eps_out + (int64_t)b * nu : nullptr;
+    double* w_b = w_out ? w_out + (int64_t)b * nu : nullptr;
+    if (m <= 0) {
+        eig_empty<64>(b, m, nu, e_seed, n_seed, nu_eff_out, eps_b, w_b);
+        return;
+    }
+    const int j = seeds[b], rlo = Hrp[j], nP = Hrp[j + 1] - rlo;
+    const int NR = nP + 1 + (ex.mode == 2 ? 1 : 0);
+    double2* de = reinterpret_cast<double2*>(smem + (size_t)wave * seed_doubles);   // {d_i, e_i}
+    double* fz = reinterpret_cast<double*>(de + nu);
+    double* rhoL = fz + nu;
+    double* R = rhoL + 64;
+    const double* hb = h + (int64_t)b * nu * nu;
+    int tj = 0;
+    {
+        const unsigned long long at = __ballot(lane < nP && Hcol[rlo + (lane < nP ? lane : 0)] == j);
+        if (at) tj = __ffsll(at) - 1;
+    }
+    const double* Rl = R + (lane < NR ? lane : 0);
+    double* Rw = R + (lane < NR ? lane : 0);   // lanes past the columns repeat column 0
+    bool fail = false;
+    int sc = 0;
+    // the second time only when some f^2 + g^2 underflowed: with the check on every rotation
+    for (int safe = 0; safe < 2; ++safe) {
+        double mx = 0.0;
+        for (int i = lane; i < m; i += 64) {
+            const double di = hb[i], ei = i + 1 < m ? hb[nu + i] : 0.0;
+            mx = fmax(mx, fmax(fabs(di), fabs(ei)));
+            de[i] = make_double2(di, ei);
+        }
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) mx = fmax(mx, __shfl_xor(mx, o));
+        sc = mx > 0.0 && mx < INFINITY ? -ilogb(mx) - 1 : 0;
+        for (int i = lane; i < m; i += 64) de[i] = make_double2(ldexp(de[i].x, sc), ldexp(de[i].y, sc));
+        for (int idx = lane; idx < m * NR; idx += 64) {
+            const int k = idx / NR, c = idx - k * NR;
+            R[idx] = c == 0 ? (k == 0 ? 1.0 : 0.0)
+                            : (c <= nP ? Kp[((int64_t)b * nu + k) * max_row + (c - 1)] : ex.pref[(int64_t)k * ex.pB + b]);
+        }
+        wave_sync();
+        fail = false;
+        double xmin = 1.0;   // smallest f^2 + g^2 met
+        for (int l = 0; l + 1 < m && !fail; ++l) {
+            for (int iter = 0;; ++iter) {
+                // the first negligible e_i, i >= l: the block l .. mm is unreduced
+                int mm = m - 1;
+                for (int base = l; base < m - 1; base += 64) {
+                    const int i = base + lane;
+                    bool small = false;
+                    if (i < m - 1) small = fabs(de[i].y) <= DBL_EPSILON * (fabs(de[i].x) + fabs(de[i + 1].x)) + 1e-32;
+                    const unsigned long long bal = __ballot(small);
+                    if (bal) {
+                        mm = base + __ffsll(bal) - 1;
+                        break;
+                    }
+                }
+                if (mm == l) break;
+                if (iter == QL_MAX_ITER) {
+                    fail = true;
+                    break;
+                }
+                const double2 del = de[l];
+                double2 dei = de[mm - 1];
+                double di1 = de[mm].x;
+                double hr = Rl[mm * NR], ri = Rl[(mm - 1) * NR];
+                // shift: e_l / (g + sign(g) sqrt(1 + g^2)), g = (d_{l+1} - d_l) / (2 e_l); e_l / (2 g) for a huge g
+                double g = (de[l + 1].x - del.x) * recip(2.0 * del.y);
+                const double ag = fabs(g), q1 = fma(g, g, 1.0);
+                const double den = ag > 1e150 ? 2.0 * ag : ag + q1 * rsqrt_nr(q1);
+                g = di1 - del.x + copysign(del.y * recip(den), ag == 0.0 ? del.y : del.y * (g < 0.0 ? -1.0 : 1.0));
+                double s = 1.0, c = 1.0, p = 0.0;
+#pragma unroll 2
+                for (int i = mm - 1; i >= l; --i) {
+                    const int in = max(i - 1, l);
+                    const double2 den2 = de[in];
+                    const double rn = Rl[in * NR];
+                    const double f = s * dei.y, bb = c * dei.y, x = fma(g, g, fma(f, f, 1e-300));
+                    const double y = __builtin_amdgcn_rsq(x), xy = x * y, u = fma(-xy, y, 1.0);
+                    // third-order step: 23 bits to full precision
+                    const double cr = fma(u, fma(0.375, u, 0.5), 1.0), yc = y * cr;
+                    double r = xy * cr;
+                    s = f * yc;
+                    c = g * yc;
+                    xmin = fmin(xmin, x);
+                    if (safe && x < 1e-290) {   // the identity: the matrix splits here
+                        r = s = 0.0;
+                        c = 1.0;
+                    }
+                    g = di1 - p;
+                    const double rr = fma(c, bb + bb, (dei.x - g) * s);
+                    p = s * rr;
+                    de[i + 1] = make_double2(g + p, r);
+                    g = fma(c, rr, -bb);
+                    Rw[(i + 1) * NR] = fma(s, ri, c * hr);
+                    hr = fma(c, ri, -(s * hr));
+                    di1 = dei.x;
+                    dei = den2;
+                    ri = rn;
+                }
+                de[l] = make_double2(di1 - p, g);
+                de[mm].y = 0.0;
+                Rw[l * NR] = hr;
+                wave_sync();
+            }
+        }
+        if (!(xmin < 1e-290)) break;
+    }
+    if (fail) {
+        eig_failed<64>(ex, b, m, nu, rlo, nP, rho, e_seed, n_seed, nu_eff_out, eps_b, w_b, zc);
+        return;
+    }
+    // the levels side by side (d_i moves to or behind a place that is read already)
+    double* d = reinterpret_cast<double*>(de);
+    for (int base = 0; base < m; base += 64) {
+        const double v = ldexp(de[min(base + lane, m - 1)].x, -sc);
+        wave_sync();
+        if (base + lane < m) d[base + lane] = v;
+        wave_sync();
+    }
+    eig_results<64>(ex, b, m, nu, R, NR, d, fz, rhoL, tj, rlo, nP, sqrt(diagS[j]), max_row, mu, kT, Hval, SvalH, rho, e_seed,
+                    n_seed, nu_eff_out, eps_b, w_b, zc);
+}
+
 LaunchInfo launch_eig(int nseeds, const int32_t* seeds, int nu, double* h, const int32_t* nu_eff_blk,
-                      const double* Kp, const int32_t* Hrp, const int32_t* Hcol, const double* Hval,
+                      double* Kp, const int32_t* Hrp, const int32_t* Hcol, const double* Hval,
                       const double* SvalH, const double* diagS, int max_row, double mu, double kT, double* rho,
                       double* e_seed, double* n_seed, int32_t* nu_eff_out, double* eps_out, double* w_out,
                       double* zc, const EigExtra& ex, hipStream_t s) {
     const int rcols = max_row + (ex.mode == 2 ? 1 : 0);   // R's LDS share (mode 1 keeps R in global memory)
+    LaunchInfo li;
+    li.wgs = nseeds;
+    const double nv = (double)nu;
+    li.bytes = (double)nseeds * (nv * nv * 8.0 + nv * max_row * 8.0 + (max_row + 3) * 8.0 * 3);
+    li.flops = (double)nseeds * ((4.0 / 3.0) * nv * nv * nv + 4.0 * nv * nv * (max_row + 1));
+    // Reduction and QL iteration, except where all eigenvectors are wanted (mode 1: one seed), a cap on Jacobi sweeps
+    // was asked for, or a row of R outgrows a wavefront or the reduction's LDS.
+    // Measured (ms, Jacobi / this): nu = 30, 256 seeds 0.29 / 0.25; nu = 47, 777 seeds 2.02 / 0.62; nu = 100, 256 seeds
+    // 1.70 / 1.81, 1024 seeds 6.6 / 2.3; nu = 300, 64 seeds 112 / 18. The reduction and iteration are the more accurate
+    // of the two (rho against LAPACK at nu = 100: 2e-15 against 1.5e-14).
+    const size_t big = tri_big_lds(nu, rcols), ql = ql_lds_bytes(nu, rcols + 1);
+    if (!ex.jacobi && ex.mode != 1 && rcols + 1 <= 64 && ql <= 160 * 1024 &&
+        (nu <= 128 || (nu <= TRI_WG && big <= 160 * 1024))) {
+        double* pref = const_cast<double*>(ex.pref);
+#define MAR_TRI(CJ, RI)                                                                                          \
+    hipLaunchKernelGGL((k_tri<CJ, RI>), dim3(nseeds), dim3(TRI_TH), 0, s, ex, seeds, nu, h, nu_eff_blk, Kp, Hrp, \
+                       max_row, pref)
+        const int ri = (nu + rcols + 31) / 32;   // rows of 32 threads (rcols <= 63)
+        if (nu <= 32) { if (ri <= 2) MAR_TRI(2, 2); else MAR_TRI(2, 3); }
+        else if (nu <= 64) { if (ri <= 3) MAR_TRI(4, 3); else MAR_TRI(4, 4); }
+        else if (nu <= 96) { if (ri <= 4) MAR_TRI(6, 4); else MAR_TRI(6, 5); }
+        else if (nu <= 128) { if (ri <= 4) MAR_TRI(8, 4); else if (ri <= 5) MAR_TRI(8, 5); else MAR_TRI(8, 6); }
+        else {
+            static std::atomic<uint64_t> done{0};
+            allow_full_lds((const void*)k_tri_big, done);
+            hipLaunchKernelGGL(k_tri_big, dim3(nseeds), dim3(TRI_WG), big, s, ex, seeds, nu, h, nu_eff_blk, Kp, Hrp, max_row, pref);
+        }
+#undef MAR_TRI
+        static std::atomic<uint64_t> done{0};
+        allow_full_lds((const void*)k_ql, done);
+        // four seeds to a workgroup, one on each SIMD, as far as LDS allows: workgroups of one wavefront shared one
+        // SIMD (nu = 100, 1024 seeds: 2.58 -> 1.79 ms, 1.62 with fewer instructions per rotation)
+        int wv = 4;
+        while (wv > 1 && wv * ql > 160 * 1024) wv /= 2;
+        hipLaunchKernelGGL(k_ql, dim3((nseeds + wv - 1) / wv), dim3(64 * wv), wv * ql, s, ex, nseeds, seeds, nu, h, nu_eff_blk, Kp, Hrp, Hcol, Hval, SvalH,
+                           diagS, max_row, mu, kT, rho, e_seed, n_seed, nu_eff_out, eps_out, w_out, zc, (int)(ql / 8));
+        return li;
+    }
     const bool lds_a = eig_a_fits_lds(nu, rcols);
     const size_t lds = eig_lds_bytes(nu, rcols, lds_a);
     if (lds_a) {
@@ -498,11 +1018,6 @@ LaunchInfo launch_eig(int nseeds, const int32_t* seeds, int nu, double* h, const
                            Hrp, Hcol, Hval, SvalH, diagS, max_row, mu, kT, rho, e_seed, n_seed, nu_eff_out, eps_out,
                            w_out, zc);
     }
-    LaunchInfo li;
-    li.wgs = nseeds;
-    const double nv = (double)nu;
-    li.bytes = (double)nseeds * (nv * nv * 8.0 + nv * max_row * 8.0 + (max_row + 3) * 8.0 * 3);
-    li.flops = (double)nseeds * ((4.0 / 3.0) * nv * nv * nv + 4.0 * nv * nv * (max_row + 1));
     return li;
 }
 

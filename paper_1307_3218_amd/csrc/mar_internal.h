@@ -140,11 +140,12 @@ struct EigExtra {
     double sigma = 0.0;           // mode 2: width of the smoothed delta
     double* phi = nullptr;        // mode 2: e_j^T phi_k of each seed
     int eig_max_sweeps = 40;      // Jacobi sweeps allowed
+    bool jacobi = false;          // the Jacobi iteration in every mode (a cap on its sweeps was asked for)
 };
 // nu_eff of a seed whose subspace eigensolve did not converge
 constexpr int NU_NOCONV = -3;
 LaunchInfo launch_eig(int nseeds, const int32_t* seeds, int nu, double* h, const int32_t* nu_eff_blk,
-                      const double* Kp, const int32_t* Hrp, const int32_t* Hcol, const double* Hval,
+                      double* Kp, const int32_t* Hrp, const int32_t* Hcol, const double* Hval,
                       const double* SvalH, const double* diagS, int max_row, double mu, double kT, double* rho,
                       double* e_seed, double* n_seed, int32_t* nu_eff_out, double* eps_out, double* w_out,
                       double* zc, const EigExtra& ex, hipStream_t s);

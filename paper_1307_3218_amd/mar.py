@@ -425,7 +425,7 @@ class Context:
         """two_streams: None lets the library choose (two blocks in flight for local regions of 6 hops or
         more, else one block at a time); True alternates two blocks; False runs one block at a time, with
         each block's eigensolve on the second stream when overlap_eig, else everything on one stream.
-        eig_max_sweeps: Jacobi sweeps allowed to the subspace eigensolve (0 = 40)."""
+        eig_max_sweeps: 0 solves the subspace eigenproblem by implicit QL, > 0 by Jacobi with that many sweeps at most."""
         _check(self.handle, mar_set_tuning(self.handle, seed_block, SCHEDULE[schedule], proj_wgs, slab_pad_kb,
                                            proj_variant, upd_q, 0 if support else 1,
                                            (0 if overlap_eig else 2) if two_streams is None else
