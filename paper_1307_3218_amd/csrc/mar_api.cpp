@@ -1595,7 +1595,7 @@ mar_status mar_solve_fermi_async(mar_ctx* c, const int32_t* d_seeds, int64_t n_s
     };
     const size_t oZ = take(nl * c->max_row * 8), oEps = take(d_eps ? 0 : nl * 8), oW = take(d_weight ? 0 : nl * 8);
     const size_t oE = take(d_e_seed ? 0 : n * 8), oN = take(d_n_seed ? 0 : n * 8), oNu = take(d_nu_eff ? 0 : n * 4);
-    const size_t oPart = take(2 * 512 * 8), oSt = take(4 * 8);
+    const size_t oPart = take(mar::level_search_doubles(1) * 8), oSt = take(8);
     if (off > c->fws_bytes) {
         if (c->fws) {
             HIP_OR(c, hipDeviceSynchronize());
@@ -1625,11 +1625,11 @@ mar_status mar_solve_fermi_async(mar_ctx* c, const int32_t* d_seeds, int64_t n_s
     if (st != MAR_OK) return st;
     // 2. Fermi level by bisection on the device, 3. assembly at that level, 4. E_band
     launch(c, s, P_MU, [&] {
-        return mar::launch_fermi_search(n_seeds, nu, nu_eff, eps, wt, n_target, kT, 200, part, stt, d_mu, s);
+        return mar::launch_fermi_search(n_seeds, nu, nu_eff, eps, wt, n_target, kT, part, stt, d_mu, s);
     });
     launch(c, s, P_EIG, [&] {
         return mar::launch_assemble((int)n_seeds, d_seeds, nu, nu_eff, eps, zc, c->max_row, c->Hrp, c->Hcol, c->Hval,
-                                    c->SvalH, stt + 2, kT, d_rho, e_seed, n_seed, s);
+                                    c->SvalH, stt, kT, d_rho, e_seed, n_seed, s);
     });
     launch(c, s, P_SUM, [&] { return mar::launch_sum(e_seed, n_seeds, d_e_band, s); });
     if (c->refused) {
@@ -1664,7 +1664,7 @@ mar_status mar_eigen_state_async(mar_ctx* c, const int32_t* d_seeds, int64_t n_s
         return o;
     };
     const size_t oZ = take(nl * c->max_row * 8), oEps = take(nl * 8), oW = take(nl * 8), oE = take(n * 8),
-                 oN = take(n * 8), oNu = take(n * 4), oPart = take(3 * 512 * 8), oSt = take(8 * 8),
+                 oN = take(n * 8), oNu = take(n * 4), oPart = take(mar::level_search_doubles(3) * 8),
                  oCm = take(n * 8), oAm = take(n * 4), oRef = take(4 * 4), oRs = take(4), oRg = take((size_t)nu * (nu + 1) * 8),
                  oY = take((size_t)nu * nu * 8), oE1 = take((size_t)nu * 8), oYr = take((size_t)nu * 8),
                  oVr = take(Mp * 8), oPd = take((size_t)groups * nu * pl.B * 8), oPr = take((size_t)nu * pl.B * 8),
@@ -1698,8 +1698,7 @@ mar_status mar_eigen_state_async(mar_ctx* c, const int32_t* d_seeds, int64_t n_s
     if (st != MAR_OK) return st;
     // eta(k - 1), eps_k = eta(k - 1/2), eta(k) from the integrated density of states
     launch(c, s, P_MU, [&] {
-        return mar::launch_dos_search(n_seeds, nu, nu_eff, eps, wt, sigma, k, 200, (double*)(f + oPart),
-                                      (double*)(f + oSt), d_levels, s);
+        return mar::launch_dos_search(n_seeds, nu, nu_eff, eps, wt, sigma, k, (double*)(f + oPart), d_levels, s);
     });
     // the reference subspace eigenvector: the one contributing most to phi_k (Appendix)
     launch(c, s, P_EIG, [&] {

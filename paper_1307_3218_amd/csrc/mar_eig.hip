@@ -50,18 +50,6 @@ __device__ __forceinline__ double level_window(double eps, double a, double b, d
     return smooth_step(b - eps, sigma) - smooth_step(a - eps, sigma);
 }
 
-// Sum over the 256 threads; every thread gets the same value (butterfly
-// pairs add the same two operands, so all lanes agree bit for bit).
-__device__ __forceinline__ double block_sum(double v, double* red) {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    __syncthreads();
-    if (lane == 0) red[wave] = v;
-    __syncthreads();
-    return (red[0] + red[1]) + (red[2] + red[3]);
-}
-
 // Threads of the eigensolver's workgroup: four waves per SIMD, so that the
 // LDS latencies of the Jacobi steps of one seed hide behind each other.
 constexpr int EIG_WG = 1024;
@@ -1105,8 +1093,8 @@ LaunchInfo launch_assemble(int nseeds, const int32_t* seeds, int nu, const int32
 // Fermi level on the device: mu with N(mu) = sum_j 2 sum_alpha f((eps_alpha^(j)
 // - mu)/kT) w_alpha^(j) equal to n_target, by bisection on [min eps - 40 kT,
 // max eps + 40 kT] over the listed seeds' subspace levels (alpha < nu_eff).
-// st = {lo, hi, mu}. Every sum runs in a fixed order.
-constexpr int MU_WGS = 512;   // workgroups of the counting kernel
+// Every sum runs in a fixed order.
+constexpr int MU_WGS = 512;   // workgroups of the level bounds
 
 __device__ __forceinline__ void wg_minmax(double& lo, double& hi, double* red) {
 #pragma unroll
@@ -1145,198 +1133,316 @@ __global__ __launch_bounds__(WG) void k_mu_bounds(int64_t nseeds, int nu, const 
     }
 }
 
-__global__ __launch_bounds__(64) void k_mu_init(int nwg, const double* __restrict__ part, double kT,
-                                                double* __restrict__ st) {
-    if (threadIdx.x != 0) return;
-    double lo = INFINITY, hi = -INFINITY;
-    for (int g = 0; g < nwg; ++g) {
-        lo = fmin(lo, part[2 * g]);
-        hi = fmax(hi, part[2 * g + 1]);
+// Bisection of counts over the levels, LEVEL_D halvings per launch: the midpoints that the next LEVEL_D halvings can
+// meet form a binary tree of LEVEL_P points (heap order, left: the lower half). A launch first sums the partial counts
+// of the launch before, in a fixed order and in every workgroup alike, and walks that tree to the new interval; then
+// it counts at the points of the next tree over its share of the levels. So each halving takes the decision that one
+// at a time would, and a search is LEVEL_PASSES launches instead of two per halving (a counting launch of 3-5 us and a
+// one-thread sum of up to 512 partials, 10 us; 42 us for three counts). An interval that a launch leaves unchanged has
+// collapsed to neighbouring doubles and stays (about 60 halvings); the last kernel finishes the ones that have not.
+// Count t (blockIdx.y): the Fermi level's N(mu) or, DOS, n(eta) for k - 1, k - 1/2 and k.
+// st[t][pass & 1] = {lo, hi, collapsed}.
+constexpr int LEVEL_D = 4, LEVEL_P = (1 << LEVEL_D) - 1, LEVEL_PASSES = 22, LEVEL_WGS = 256, LEVEL_BITS = 200;
+
+struct LevelArgs {
+    int64_t nseeds;
+    int nu;
+    const int32_t* nu_eff;
+    const double *eps, *w;
+    double width;           // kT, or sigma
+    double target[3];
+    int nwg;                // workgroups that count (per target)
+    const double* bounds;   // [nb][2] partial level bounds
+    int nb;
+    double* part;           // [2][target][nwg][LEVEL_P]
+    double* st;             // [target][2][4]
+};
+
+// The LEVEL_P midpoints of [lo, hi] into mid, by the first threads.
+__device__ __forceinline__ void level_points(double lo, double hi, double* mid) {
+    const int q = threadIdx.x;
+    if (q < LEVEL_P) {
+        int d = 0;
+        while ((2 << d) - 1 <= q) ++d;   // depth of heap node q; its path from the root in the low d bits of q + 1
+        for (int i = d - 1; i >= 0; --i) {
+            const double m = 0.5 * (lo + hi);
+            if (((q + 1) >> i) & 1) lo = m;
+            else hi = m;
+        }
+        mid[q] = 0.5 * (lo + hi);
     }
-    if (!(lo <= hi)) lo = hi = 0.0;   // no levels at all
-    st[0] = lo - 40.0 * kT;
-    st[1] = hi + 40.0 * kT;
-    st[2] = 0.5 * (st[0] + st[1]);
 }
 
-__global__ __launch_bounds__(WG) void k_mu_count(int64_t nseeds, int nu, const int32_t* __restrict__ nu_eff,
-                                                 const double* __restrict__ eps, const double* __restrict__ w,
-                                                 double kT, const double* __restrict__ st, double* __restrict__ part) {
-    __shared__ double red[8];
-    const double mid = 0.5 * (st[0] + st[1]);
+// Counts at the points mid over the levels first, first + step, ... into cnt (a sum per point over the workgroup).
+template <bool DOS, int NT>
+__device__ __forceinline__ void level_count(const LevelArgs& a, const double* mid, int64_t first, int64_t step, double* red,
+                                            double* cnt) {
+    double s[LEVEL_P];
+#pragma unroll
+    for (int q = 0; q < LEVEL_P; ++q) s[q] = 0.0;
+    const int64_t npair = a.nseeds * a.nu;
+    for (int64_t p = first; p < npair; p += step) {
+        const int64_t b = p / a.nu;
+        if ((int)(p - b * a.nu) >= a.nu_eff[b]) continue;
+        const double e = a.eps[p], w = a.w[p];
+#pragma unroll
+        for (int q = 0; q < LEVEL_P; ++q)
+            s[q] += DOS ? w * smooth_step(mid[q] - e, a.width) : 2.0 * fermi_occ(e, mid[q], a.width) * w;
+    }
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+#pragma unroll
+    for (int q = 0; q < LEVEL_P; ++q) {
+        const double v = wave_sum(s[q]);
+        if (lane == 0) red[wave * LEVEL_P + q] = v;
+    }
+    __syncthreads();
+    if (threadIdx.x < LEVEL_P) {
+        double t = 0.0;
+        for (int i = 0; i < NT / 64; ++i) t += red[i * LEVEL_P + threadIdx.x];
+        cnt[threadIdx.x] = t;
+    }
+    __syncthreads();
+}
+
+// LEVEL_D halvings by the counts at mid's points; run by one thread.
+__device__ __forceinline__ void level_walk(const double* mid, const double* cnt, double target, double& lo, double& hi) {
+    int q = 0;
+    for (int d = 0; d < LEVEL_D; ++d) {
+        if (cnt[q] < target) {
+            lo = mid[q];
+            q = 2 * q + 2;
+        } else {
+            hi = mid[q];
+            q = 2 * q + 1;
+        }
+    }
+}
+
+// The interval at the start of launch `pass` into sh = {lo, hi, collapsed}: from the level bounds (pass 0) or from the
+// interval and the partial counts of the launch before.
+template <bool DOS, int NT>
+__device__ __forceinline__ void level_state(const LevelArgs& a, int pass, int t, double* sh, double* mid, double* red,
+                                            double* cnt) {
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    if (pass == 0) {
+        double lo = INFINITY, hi = -INFINITY;
+        for (int g = tid; g < a.nb; g += NT) {
+            lo = fmin(lo, a.bounds[2 * g]);
+            hi = fmax(hi, a.bounds[2 * g + 1]);
+        }
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) {
+            lo = fmin(lo, __shfl_xor(lo, o));
+            hi = fmax(hi, __shfl_xor(hi, o));
+        }
+        if (lane == 0) {
+            red[2 * wave] = lo;
+            red[2 * wave + 1] = hi;
+        }
+        __syncthreads();
+        if (tid == 0) {
+            for (int i = 1; i < NT / 64; ++i) {
+                lo = fmin(lo, red[2 * i]);
+                hi = fmax(hi, red[2 * i + 1]);
+            }
+            if (!(lo <= hi)) lo = hi = 0.0;   // no levels at all
+            sh[0] = DOS ? lo - 1.0 : lo - 40.0 * a.width;
+            sh[1] = DOS ? hi + 1.0 : hi + 40.0 * a.width;
+            sh[2] = 0.0;
+        }
+        __syncthreads();
+        return;
+    }
+    const double* prev = a.st + (t * 2 + ((pass - 1) & 1)) * 4;
+    if (tid < 3) sh[tid] = prev[tid];
+    __syncthreads();
+    if (sh[2] != 0.0) return;
+    level_points(sh[0], sh[1], mid);
+    const double* pt = a.part + ((int64_t)((pass - 1) & 1) * gridDim.y + t) * a.nwg * LEVEL_P;
+    // sixteen lanes of workgroups per point, each in order, then the lanes in order
+    const int q = tid % 16, r = tid / 16;
     double s = 0.0;
-    const int64_t npair = nseeds * nu;
-    for (int64_t p = (int64_t)blockIdx.x * WG + threadIdx.x; p < npair; p += (int64_t)gridDim.x * WG) {
-        const int64_t b = p / nu;
-        const int a = (int)(p - b * nu);
-        if (a < nu_eff[b]) s += 2.0 * fermi_occ(eps[p], mid, kT) * w[p];
+    if (tid < 256 && q < LEVEL_P)
+        for (int g = r; g < a.nwg; g += 16) s += pt[(int64_t)g * LEVEL_P + q];
+    if (tid < 256) red[tid] = s;
+    __syncthreads();
+    if (tid < LEVEL_P) {
+        double n = 0.0;
+        for (int i = 0; i < 16; ++i) n += red[i * 16 + tid];
+        cnt[tid] = n;
     }
-    s = block_sum(s, red);
-    if (threadIdx.x == 0) part[blockIdx.x] = s;
+    __syncthreads();
+    if (tid == 0) {
+        const double lo = sh[0], hi = sh[1];
+        level_walk(mid, cnt, a.target[t], sh[0], sh[1]);
+        sh[2] = sh[0] == lo && sh[1] == hi ? 1.0 : 0.0;
+    }
+    __syncthreads();
 }
 
-__global__ __launch_bounds__(64) void k_mu_step(int nwg, const double* __restrict__ part, double n_target,
-                                                double* __restrict__ st, int last, double* __restrict__ mu_out) {
-    if (threadIdx.x != 0) return;
-    double n = 0.0;
-    for (int g = 0; g < nwg; ++g) n += part[g];
-    const double mid = 0.5 * (st[0] + st[1]);
-    if (n < n_target) st[0] = mid;
-    else st[1] = mid;
-    if (last) {
-        st[2] = 0.5 * (st[0] + st[1]);
-        if (mu_out) *mu_out = st[2];
+template <bool DOS>
+__global__ __launch_bounds__(WG) void k_level_pass(LevelArgs a, int pass) {
+    __shared__ double sh[3], mid[LEVEL_P + 1], cnt[LEVEL_P + 1], red[WG];
+    const int t = blockIdx.y;
+    level_state<DOS, WG>(a, pass, t, sh, mid, red, cnt);
+    if (blockIdx.x == 0 && threadIdx.x < 3) a.st[(t * 2 + (pass & 1)) * 4 + threadIdx.x] = sh[threadIdx.x];
+    if (sh[2] != 0.0) return;
+    level_points(sh[0], sh[1], mid);
+    __syncthreads();
+    level_count<DOS, WG>(a, mid, (int64_t)blockIdx.x * WG + threadIdx.x, (int64_t)a.nwg * WG, red, cnt);
+    if (threadIdx.x < LEVEL_P)
+        a.part[(((int64_t)(pass & 1) * gridDim.y + t) * a.nwg + blockIdx.x) * LEVEL_P + threadIdx.x] = cnt[threadIdx.x];
+}
+
+// The rest of the LEVEL_BITS halvings for an interval that has not collapsed (one workgroup per count), and the
+// result, the interval's middle, into out[DOS: {eps_k, eta(k - 1), eta(k)}] and out2 (or null).
+constexpr int LEVEL_FIN = 1024;
+template <bool DOS>
+__global__ __launch_bounds__(LEVEL_FIN) void k_level_finish(LevelArgs a, double* out, double* out2) {
+    __shared__ double sh[3], mid[LEVEL_P + 1], cnt[LEVEL_P + 1], red[LEVEL_FIN];
+    const int t = blockIdx.y;
+    level_state<DOS, LEVEL_FIN>(a, LEVEL_PASSES, t, sh, mid, red, cnt);
+    for (int done = LEVEL_PASSES * LEVEL_D; done < LEVEL_BITS && sh[2] == 0.0; done += LEVEL_D) {
+        __syncthreads();
+        level_points(sh[0], sh[1], mid);
+        __syncthreads();
+        level_count<DOS, LEVEL_FIN>(a, mid, threadIdx.x, LEVEL_FIN, red, cnt);
+        if (threadIdx.x == 0) {
+            const double lo = sh[0], hi = sh[1];
+            level_walk(mid, cnt, a.target[t], sh[0], sh[1]);
+            sh[2] = sh[0] == lo && sh[1] == hi ? 1.0 : 0.0;
+        }
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) {
+        const double m = 0.5 * (sh[0] + sh[1]);
+        out[DOS ? (t == 1 ? 0 : (t == 0 ? 1 : 2)) : 0] = m;
+        if (out2) *out2 = m;
     }
 }
 
-LaunchInfo launch_fermi_search(int64_t nseeds, int nu, const int32_t* nu_eff, const double* eps, const double* w,
-                               double n_target, double kT, int iters, double* part, double* st, double* mu_out,
+template <bool DOS>
+static LaunchInfo level_search(int64_t nseeds, int nu, const int32_t* nu_eff, const double* eps, const double* w,
+                               double width, const double* target, int nt, double* work, double* out, double* out2,
                                hipStream_t s) {
+    static_assert(LEVEL_BITS % LEVEL_D == 0 && LEVEL_PASSES * LEVEL_D < LEVEL_BITS && LEVEL_P <= 16, "tree depth");
     const int64_t npair = nseeds * nu;
-    int nwg = (int)std::min<int64_t>(MU_WGS, std::max<int64_t>(1, (npair + WG - 1) / WG));
-    hipLaunchKernelGGL(k_mu_bounds, dim3(nwg), dim3(WG), 0, s, nseeds, nu, nu_eff, eps, part);
-    hipLaunchKernelGGL(k_mu_init, dim3(1), dim3(64), 0, s, nwg, part, kT, st);
-    for (int it = 0; it < iters; ++it) {
-        hipLaunchKernelGGL(k_mu_count, dim3(nwg), dim3(WG), 0, s, nseeds, nu, nu_eff, eps, w, kT, st, part);
-        hipLaunchKernelGGL(k_mu_step, dim3(1), dim3(64), 0, s, nwg, part, n_target, st, it + 1 == iters ? 1 : 0,
-                           mu_out);
-    }
+    const int nb = (int)std::min<int64_t>(MU_WGS, std::max<int64_t>(1, (npair + WG - 1) / WG));
+    LevelArgs a{};
+    a.nseeds = nseeds;
+    a.nu = nu;
+    a.nu_eff = nu_eff;
+    a.eps = eps;
+    a.w = w;
+    a.width = width;
+    for (int t = 0; t < nt; ++t) a.target[t] = target[t];
+    a.nwg = (int)std::min<int64_t>(LEVEL_WGS, nb);
+    a.bounds = work;
+    a.nb = nb;
+    a.st = work + 2 * MU_WGS;
+    a.part = a.st + 3 * 2 * 4;
+    hipLaunchKernelGGL(k_mu_bounds, dim3(nb), dim3(WG), 0, s, nseeds, nu, nu_eff, eps, work);
+    for (int pass = 0; pass < LEVEL_PASSES; ++pass)
+        hipLaunchKernelGGL((k_level_pass<DOS>), dim3(a.nwg, nt), dim3(WG), 0, s, a, pass);
+    hipLaunchKernelGGL((k_level_finish<DOS>), dim3(1, nt), dim3(LEVEL_FIN), 0, s, a, out, out2);
     LaunchInfo li;
-    li.wgs = nwg;
-    li.bytes = (double)(iters + 1) * npair * 20.0;
-    li.flops = (double)iters * npair * 30.0;
+    li.wgs = nb;
+    li.bytes = (double)(LEVEL_PASSES + 1) * npair * 20.0;
+    li.flops = (double)LEVEL_PASSES * LEVEL_P * nt * npair * 30.0;
     return li;
 }
 
-// ---------------------------------------------------------------------------
+size_t level_search_doubles(int nt) { return 2 * MU_WGS + 3 * 2 * 4 + (size_t)2 * nt * LEVEL_WGS * LEVEL_P; }
+
+LaunchInfo launch_fermi_search(int64_t nseeds, int nu, const int32_t* nu_eff, const double* eps, const double* w,
+                               double n_target, double kT, double* work, double* mu, double* mu_out, hipStream_t s) {
+    return level_search<false>(nseeds, nu, nu_eff, eps, w, kT, &n_target, 1, work, mu, mu_out, s);
+}
+
 // Eigen states (Sec. 3, Eq. 3; Appendix): integrated density of states
 //   n(eta) = sum_j sum_alpha w_alpha^(j) F((eta - eps_alpha^(j)) / sigma)
 // (F the logistic step; sigma = 0: the unit step, 1/2 at 0), bisected for the
-// three counts k - 1, k - 1/2 and k at once on [min eps - 1, max eps + 1].
-// st = {lo, hi} x 3; lv = {eta(k - 1/2), eta(k - 1), eta(k)}.
-__global__ __launch_bounds__(64) void k_dos_init(int nwg, const double* __restrict__ part, double* __restrict__ st) {
-    if (threadIdx.x != 0) return;
-    double lo = INFINITY, hi = -INFINITY;
-    for (int g = 0; g < nwg; ++g) {
-        lo = fmin(lo, part[2 * g]);
-        hi = fmax(hi, part[2 * g + 1]);
-    }
-    if (!(lo <= hi)) lo = hi = 0.0;
-    for (int t = 0; t < 3; ++t) {
-        st[2 * t] = lo - 1.0;
-        st[2 * t + 1] = hi + 1.0;
-    }
-}
-
-__global__ __launch_bounds__(WG) void k_dos_count(int64_t nseeds, int nu, const int32_t* __restrict__ nu_eff,
-                                                  const double* __restrict__ eps, const double* __restrict__ w,
-                                                  double sigma, const double* __restrict__ st,
-                                                  double* __restrict__ part) {
-    __shared__ double red[8];
-    double mid[3], c[3] = {0.0, 0.0, 0.0};
-#pragma unroll
-    for (int t = 0; t < 3; ++t) mid[t] = 0.5 * (st[2 * t] + st[2 * t + 1]);
-    const int64_t npair = nseeds * nu;
-    for (int64_t p = (int64_t)blockIdx.x * WG + threadIdx.x; p < npair; p += (int64_t)gridDim.x * WG) {
-        const int64_t b = p / nu;
-        const int a = (int)(p - b * nu);
-        if (a < nu_eff[b]) {
-#pragma unroll
-            for (int t = 0; t < 3; ++t) c[t] += w[p] * smooth_step(mid[t] - eps[p], sigma);
-        }
-    }
-#pragma unroll
-    for (int t = 0; t < 3; ++t) {
-        const double v = block_sum(c[t], red);
-        if (threadIdx.x == 0) part[3 * blockIdx.x + t] = v;
-    }
-}
-
-__global__ __launch_bounds__(64) void k_dos_step(int nwg, const double* __restrict__ part, int k,
-                                                 double* __restrict__ st, int last, double* __restrict__ lv) {
-    if (threadIdx.x != 0) return;
-    const double target[3] = {k - 1.0, k - 0.5, (double)k};
-    for (int t = 0; t < 3; ++t) {
-        double n = 0.0;
-        for (int g = 0; g < nwg; ++g) n += part[3 * g + t];
-        const double mid = 0.5 * (st[2 * t] + st[2 * t + 1]);
-        if (n < target[t]) st[2 * t] = mid;
-        else st[2 * t + 1] = mid;
-    }
-    if (last) {
-        lv[0] = 0.5 * (st[2] + st[3]);   // eps_k = eta(k - 1/2)
-        lv[1] = 0.5 * (st[0] + st[1]);   // eta(k - 1)
-        lv[2] = 0.5 * (st[4] + st[5]);   // eta(k)
-    }
-}
-
+// three counts k - 1, k - 1/2 and k on [min eps - 1, max eps + 1];
+// lv = {eta(k - 1/2), eta(k - 1), eta(k)}.
 LaunchInfo launch_dos_search(int64_t nseeds, int nu, const int32_t* nu_eff, const double* eps, const double* w,
-                             double sigma, int k, int iters, double* part, double* st, double* lv, hipStream_t s) {
-    const int64_t npair = nseeds * nu;
-    const int nwg = (int)std::min<int64_t>(MU_WGS, std::max<int64_t>(1, (npair + WG - 1) / WG));
-    hipLaunchKernelGGL(k_mu_bounds, dim3(nwg), dim3(WG), 0, s, nseeds, nu, nu_eff, eps, part);
-    hipLaunchKernelGGL(k_dos_init, dim3(1), dim3(64), 0, s, nwg, part, st);
-    for (int it = 0; it < iters; ++it) {
-        hipLaunchKernelGGL(k_dos_count, dim3(nwg), dim3(WG), 0, s, nseeds, nu, nu_eff, eps, w, sigma, st, part);
-        hipLaunchKernelGGL(k_dos_step, dim3(1), dim3(64), 0, s, nwg, part, k, st, it + 1 == iters ? 1 : 0, lv);
-    }
-    LaunchInfo li;
-    li.wgs = nwg;
-    li.bytes = (double)(iters + 1) * npair * 20.0;
-    li.flops = (double)iters * npair * 90.0;
-    return li;
+                             double sigma, int k, double* work, double* lv, hipStream_t s) {
+    const double target[3] = {k - 1.0, k - 0.5, (double)k};
+    return level_search<true>(nseeds, nu, nu_eff, eps, w, sigma, target, 3, work, lv, nullptr, s);
 }
 
 // Contributions c_alpha^(j) = (e_j . v_alpha^(j)) window_alpha of every seed
 // (kept rows zc, levels eps) and the reference: the largest |c| (first seed,
 // then first alpha, on ties). ref = {position b, alpha, seed j}; refseed[0] = j.
-__global__ __launch_bounds__(WG) void k_es_contrib(int nseeds, const int32_t* __restrict__ seeds, int nu,
+__device__ __forceinline__ void first_largest(double& v, int& at) {   // over a wavefront, the smaller index on ties
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+        const double ov = __shfl_xor(v, o);
+        const int oa = __shfl_xor(at, o);
+        if (ov > v || (ov == v && oa < at)) {
+            v = ov;
+            at = oa;
+        }
+    }
+}
+
+__global__ __launch_bounds__(64) void k_es_contrib(int nseeds, const int32_t* __restrict__ seeds, int nu,
                                                    const int32_t* __restrict__ nu_eff, const double* __restrict__ eps,
                                                    const double* __restrict__ zc, int max_row,
                                                    const int32_t* __restrict__ Hrp, const int32_t* __restrict__ Hcol,
                                                    const double* __restrict__ lv, double sigma,
                                                    double* __restrict__ cmax, int32_t* __restrict__ amax) {
-    __shared__ int tjs;
-    const int b = blockIdx.x;
-    if (b >= nseeds) return;
+    const int b = blockIdx.x, lane = threadIdx.x;
     const int m = nu_eff[b];
-    if (m <= 0) {
-        if (threadIdx.x == 0) {
-            cmax[b] = -1.0;
-            amax[b] = 0;
-        }
-        return;
-    }
-    const int j = seeds[b];
-    const int rlo = Hrp[j], nP = Hrp[j + 1] - rlo;
-    if ((int)threadIdx.x < nP && Hcol[rlo + threadIdx.x] == j) tjs = threadIdx.x;
-    __syncthreads();
-    if (threadIdx.x != 0) return;
-    const double* zb = zc + (int64_t)b * nu * max_row;
     double best = -1.0;
     int ba = 0;
-    for (int a = 0; a < m; ++a) {
-        const double c = fabs(zb[a * max_row + tjs] * level_window(eps[(int64_t)b * nu + a], lv[1], lv[2], sigma));
-        if (c > best) {
-            best = c;
-            ba = a;
+    if (m > 0) {
+        const int j = seeds[b];
+        const int rlo = Hrp[j], nP = Hrp[j + 1] - rlo;
+        const unsigned long long at = __ballot(lane < nP && Hcol[rlo + (lane < nP ? lane : 0)] == j);
+        const int tj = at ? __ffsll(at) - 1 : 0;
+        const double* zb = zc + (int64_t)b * nu * max_row;
+        for (int a = lane; a < m; a += 64) {
+            const double c = fabs(zb[a * max_row + tj] * level_window(eps[(int64_t)b * nu + a], lv[1], lv[2], sigma));
+            if (c > best) {
+                best = c;
+                ba = a;
+            }
         }
+        if (best < 0.0) ba = m;   // a lane without an alpha
+        first_largest(best, ba);
     }
-    cmax[b] = best;
-    amax[b] = ba;
+    if (lane == 0) {
+        cmax[b] = best;
+        amax[b] = best < 0.0 ? 0 : ba;
+    }
 }
 
-__global__ __launch_bounds__(64) void k_es_argmax(int nseeds, const int32_t* __restrict__ seeds,
-                                                  const double* __restrict__ cmax, const int32_t* __restrict__ amax,
-                                                  int32_t* __restrict__ ref, int32_t* __restrict__ refseed) {
-    if (threadIdx.x != 0) return;
+__global__ __launch_bounds__(1024) void k_es_argmax(int nseeds, const int32_t* __restrict__ seeds,
+                                                    const double* __restrict__ cmax, const int32_t* __restrict__ amax,
+                                                    int32_t* __restrict__ ref, int32_t* __restrict__ refseed) {
+    __shared__ double vs[16];
+    __shared__ int as[16];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     double best = -1.0;
-    int bb = 0;
-    for (int b = 0; b < nseeds; ++b)
+    int bb = nseeds;
+    for (int b = tid; b < nseeds; b += 1024)
         if (cmax[b] > best) {
             best = cmax[b];
             bb = b;
         }
+    first_largest(best, bb);
+    if (lane == 0) {
+        vs[wave] = best;
+        as[wave] = bb;
+    }
+    __syncthreads();
+    if (tid != 0) return;
+    for (int i = 1; i < 16; ++i)
+        if (vs[i] > best || (vs[i] == best && as[i] < bb)) {
+            best = vs[i];
+            bb = as[i];
+        }
+    if (!(best > -1.0)) bb = 0;   // no contribution at all
     ref[0] = bb;
     ref[1] = nseeds > 0 ? amax[bb] : 0;
     ref[2] = nseeds > 0 ? seeds[bb] : 0;
@@ -1348,9 +1454,9 @@ LaunchInfo launch_es_reference(int nseeds, const int32_t* seeds, int nu, const i
                                const double* lv, double sigma, double* cmax, int32_t* amax, int32_t* ref,
                                int32_t* refseed, hipStream_t s) {
     if (nseeds > 0)
-        hipLaunchKernelGGL(k_es_contrib, dim3(nseeds), dim3(WG), 0, s, nseeds, seeds, nu, nu_eff, eps, zc, max_row, Hrp,
+        hipLaunchKernelGGL(k_es_contrib, dim3(nseeds), dim3(64), 0, s, nseeds, seeds, nu, nu_eff, eps, zc, max_row, Hrp,
                            Hcol, lv, sigma, cmax, amax);
-    hipLaunchKernelGGL(k_es_argmax, dim3(1), dim3(64), 0, s, nseeds, seeds, cmax, amax, ref, refseed);
+    hipLaunchKernelGGL(k_es_argmax, dim3(1), dim3(1024), 0, s, nseeds, seeds, cmax, amax, ref, refseed);
     LaunchInfo li;
     li.wgs = nseeds;
     li.bytes = (double)nseeds * nu * 16.0;

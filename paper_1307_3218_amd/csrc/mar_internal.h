@@ -156,10 +156,12 @@ LaunchInfo launch_assemble(int nseeds, const int32_t* seeds, int nu, const int32
                            const double* zc, int max_row, const int32_t* Hrp, const int32_t* Hcol,
                            const double* Hval, const double* SvalH, const double* mu, double kT, double* rho,
                            double* e_seed, double* n_seed, hipStream_t s);
+// Doubles of work space of a search for nt counts (1: Fermi level, 3: eigen state).
+size_t level_search_doubles(int nt);
 // Eigen states: bisection of the smoothed integrated density of states for the counts k - 1, k - 1/2, k
-// (lv = {eta(k - 1/2), eta(k - 1), eta(k)}); part >= 3 * 512 doubles, st >= 6 doubles.
+// (lv = {eta(k - 1/2), eta(k - 1), eta(k)}).
 LaunchInfo launch_dos_search(int64_t nseeds, int nu, const int32_t* nu_eff, const double* eps, const double* w,
-                             double sigma, int k, int iters, double* part, double* st, double* lv, hipStream_t s);
+                             double sigma, int k, double* work, double* lv, hipStream_t s);
 // The seed and subspace eigenvector with the largest |(e_j.v_alpha) window| (ref = {position, alpha, seed}).
 LaunchInfo launch_es_reference(int nseeds, const int32_t* seeds, int nu, const int32_t* nu_eff, const double* eps,
                                const double* zc, int max_row, const int32_t* Hrp, const int32_t* Hcol,
@@ -174,11 +176,9 @@ LaunchInfo launch_es_refvec(const T* K, int64_t stride, int64_t M, const int32_t
 template <typename T>
 LaunchInfo launch_es_pdot(int B, const T* K, int64_t stride, int64_t M, int64_t Mp, int nu, const double* vref,
                           double* part, int groups, hipStream_t s);
-// Bisection for the Fermi level over the levels of nseeds seeds; part >= 2 * 512 doubles, st = {lo, hi, mu};
-// the final mu is also written to *mu_out when mu_out != nullptr.
+// Bisection for the Fermi level over the levels of nseeds seeds, into *mu and (not null) *mu_out.
 LaunchInfo launch_fermi_search(int64_t nseeds, int nu, const int32_t* nu_eff, const double* eps, const double* w,
-                               double n_target, double kT, int iters, double* part, double* st, double* mu_out,
-                               hipStream_t s);
+                               double n_target, double kT, double* work, double* mu, double* mu_out, hipStream_t s);
 
 // Y = H X and Z = S X in one pass (SH: S's values on H's BSR pattern); refused (wgs = -1) unless H is BSR
 // and B >= the vector width. ndot as in launch_spmm, against Z.
