@@ -338,9 +338,9 @@ mar_status mar_autotune(mar_ctx* ctx, int32_t nu, mar_precision prec, const int3
  *   d_R       [max_sweeps + 1] device or NULL: R before the first sweep and after
  *             each sweep run (later entries untouched).
  *   d_info    [2] device or NULL: sweeps run, flips made.
- * One workgroup on the caller's stream; asynchronous. The context keeps a
- * workspace of 25 M bytes for it (allocated at the first call). MAR_ERR_ARG for
- * a NULL phi, eps or c not finite, c < 0 or max_sweeps < 0. */
+ * On the caller's stream; asynchronous. The context keeps a workspace of
+ * about (32 + 12 w) M bytes for it, w = max(20, longest row of H) (allocated at the
+ * first call). MAR_ERR_ARG for a NULL phi, eps or c not finite, c < 0 or max_sweeps < 0. */
 mar_status mar_local_flip(mar_ctx* ctx, double* d_phi, double eps, const double* d_phi_ref, double c,
                           int32_t max_sweeps, double* d_R, int32_t* d_info, void* hip_stream);
 /* Number of colours of that colouring (built if needed; synchronous); -1 on error. */

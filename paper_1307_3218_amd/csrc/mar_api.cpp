@@ -94,10 +94,10 @@ struct mar_ctx {
     char* fws = nullptr;          // workspace of the device Fermi-level search
     size_t fws_bytes = 0;
     // local flipping: distance-2 colouring of H's rows (built at the first call) and workspace
-    int32_t* fl_coff = nullptr;   // [ncol + 1]
+    int32_t* fl_round = nullptr;  // [nround][2] entries of fl_crow that a round of k_flip takes
     int32_t* fl_crow = nullptr;   // [M] rows by colour, index order within a colour
-    int fl_ncol = 0;
-    char* flws = nullptr;         // r, s [M] doubles and flags [M]
+    int fl_ncol = 0, fl_nround = 0;
+    char* flws = nullptr;         // workspace of the flipping (flip_workspace)
 
     mar_tuning tune{};
     int32_t loc = -1;             // local-region hops of later solves (< 0: the full system)
@@ -1943,8 +1943,16 @@ mar_status build_colouring(mar_ctx* c) {
     for (int k = 0; k < ncol; ++k) off[k + 1] += off[k];
     std::vector<int32_t> fill(off.begin(), off.end() - 1);
     for (int64_t l = 0; l < M; ++l) rows[fill[colour[l]]++] = (int32_t)l;
+    std::vector<int32_t> round;   // the rounds of k_flip, filled up with empty ones
+    for (int k = 0; k < ncol; ++k)
+        for (int b = off[k]; b < off[k + 1]; b += mar::FLIP_WG) {
+            round.push_back(b);
+            round.push_back(std::min(off[k + 1], b + mar::FLIP_WG));
+        }
+    while (round.size() / 2 % (mar::FLIP_AHEAD + 1)) round.insert(round.end(), {0, 0});
     mar_status st;
-    if ((st = upload(c, &c->fl_coff, off.data(), off.size())) != MAR_OK) return st;
+    if ((st = upload(c, &c->fl_round, round.data(), round.size())) != MAR_OK) return st;
+    c->fl_nround = (int)(round.size() / 2);
     if ((st = upload(c, &c->fl_crow, rows.data(), rows.size())) != MAR_OK) return st;
     c->fl_ncol = ncol;
     return MAR_OK;
@@ -1964,15 +1972,11 @@ mar_status mar_local_flip(mar_ctx* c, double* d_phi, double eps, const double* d
     }
     if (!c->flws) {
         void* p = nullptr;
-        HIP_OR(c, hipMalloc(&p, (size_t)c->M * 25 + 16));
+        HIP_OR(c, hipMalloc(&p, mar::flip_workspace(c->M, c->max_row)));
         c->flws = (char*)p;
     }
-    double* r = (double*)c->flws;       // residual (H - eps S) phi
-    double* sv = r + c->M;              // S phi_ref
-    double* drr = sv + c->M;            // per colour entry: |r|^2 change of its single flip
-    int8_t* flag = (int8_t*)(drr + c->M);
-    mar::launch_flip(c->M, c->Hrp, c->Hcol, c->Hval, c->SvalH, eps, d_phi, d_phi_ref, cpen, c->fl_ncol, c->fl_coff,
-                     c->fl_crow, max_sweeps, r, sv, drr, flag, d_R, d_info, (hipStream_t)hip_stream);
+    mar::launch_flip(c->M, c->Hrp, c->Hcol, c->Hval, c->SvalH, c->max_row, eps, d_phi, d_phi_ref, cpen, c->fl_nround,
+                     c->fl_round, c->fl_crow, max_sweeps, c->flws, d_R, d_info, (hipStream_t)hip_stream);
     HIP_OR(c, hipGetLastError());
     return MAR_OK;
 }

@@ -144,6 +144,13 @@ __device__ __forceinline__ double wave_sum(double v) {
     return swap_add32(v, v);
 }
 
+// Barrier that orders LDS only: loads and stores of global memory stay in flight across it.
+__device__ __forceinline__ void lds_barrier() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
 // Workgroup reduction of per-seed partial sums (fixed order, deterministic).
 // Thread t holds vals[v][i] for seed (t % P) * SW + i. For every v and every
 // seed b in [0, P*SW) the sum over the workgroup's 256 threads is passed to
@@ -196,15 +203,18 @@ __device__ __forceinline__ void wg_seed_reduce(A (&vals)[NV][SW], A* lds, F&& em
     }
 }
 
-// Lets kernel f use up to 160 KB of dynamic LDS. The attribute belongs to the current device, so it is
-// set once per device (bit d of done for device d; concurrent first calls both set it, which is harmless).
-inline void allow_full_lds(const void* f, std::atomic<uint64_t>& done) {
+// Lets kernel f use up to `bytes` of dynamic LDS (160 KB less its static LDS at most). The attribute belongs to the
+// current device, so it is set once per device (bit d of done for device d; concurrent first calls both set it, which is
+// harmless).
+inline void allow_lds(const void* f, std::atomic<uint64_t>& done, int bytes) {
     int dev = 0;
     const bool known = hipGetDevice(&dev) == hipSuccess && dev >= 0 && dev < 64;
     const uint64_t bit = known ? 1ull << dev : 0;
     if (known && (done.load(std::memory_order_acquire) & bit)) return;
-    (void)hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+    (void)hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
     if (known) done.fetch_or(bit, std::memory_order_acq_rel);
 }
+
+inline void allow_full_lds(const void* f, std::atomic<uint64_t>& done) { allow_lds(f, done, 160 * 1024); }
 
 }  // namespace mar

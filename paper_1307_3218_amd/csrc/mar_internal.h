@@ -277,12 +277,15 @@ LaunchInfo launch_norm(int B, int nk, const double* beta2, const double* c1, con
 LaunchInfo launch_sum(const double* x, int64_t n, double* out, hipStream_t s);
 LaunchInfo launch_zero(void* p, int64_t bytes, hipStream_t s);  // bytes: multiple of 16
 
-// Local flipping refinement (Appendix), one workgroup: phi [M] in/out; colours: ncol lists, rows crow[coff[k]..
-// coff[k+1]) in index order; r, s [M] and flag [M] workspace; Rout [max_sweeps + 1] and info [2] optional.
-LaunchInfo launch_flip(int64_t M, const int32_t* rp, const int32_t* col, const double* hv, const double* sv,
-                       double eps, double* phi, const double* phi_ref, double cpen, int ncol, const int32_t* coff,
-                       const int32_t* crow, int max_sweeps, double* r, double* s, double* drr, int8_t* flag,
-                       double* Rout, int32_t* info, hipStream_t st);
+constexpr int FLIP_WG = 512;
+constexpr int FLIP_AHEAD = 1;
+// Local flipping refinement (Appendix): phi [M] in/out; the rows crow by colour, index order within a colour, in
+// nround (a multiple of FLIP_AHEAD + 1) rounds: round t takes the entries round[2 t] .. round[2 t + 1) of crow, at most
+// FLIP_WG of one colour, or none; work: flip_workspace bytes; Rout [max_sweeps + 1] and info [2] optional.
+size_t flip_workspace(int64_t M, int max_row);
+LaunchInfo launch_flip(int64_t M, const int32_t* rp, const int32_t* col, const double* hv, const double* sv, int max_row,
+                       double eps, double* phi, const double* phi_ref, double cpen, int nround, const int32_t* round,
+                       const int32_t* crow, int max_sweeps, void* work, double* Rout, int32_t* info, hipStream_t st);
 
 // Largest B accepted for an element type (P = B / vector width must fit one wavefront).
 template <typename T>

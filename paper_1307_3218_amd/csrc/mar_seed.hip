@@ -40,13 +40,6 @@ constexpr int SEED_NF = 4;      // 16-byte vectors of a lane kept in registers d
 constexpr int SEED_KP = 4;      // ranges of basis vectors in an update: 16 lanes of a wavefront each
 constexpr int SEED_UN = 16;     // basis vectors of one range in flight
 
-// Barrier that orders LDS only: loads and stores of global memory stay in flight across it.
-__device__ __forceinline__ void lds_barrier() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-    __builtin_amdgcn_s_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-}
-
 template <typename T>
 struct SeedArgs {
     SeedGeom g;
