@@ -393,10 +393,51 @@ int choose_block(const mar_ctx* c, int nu, mar_precision prec, int64_t n_seeds, 
             // the matrix values are reused B times
             B = block_cap(c, nu, prec, delayed);
         }
-        if (n_seeds > 0) B = std::min<int64_t>(B, pow2_floor(std::max<int64_t>(1, n_seeds)) * 2);
+        // the least power of two that holds the seeds (blocks of 2 and 4 for one to three: a local region needs 4)
+        if (n_seeds > 0) B = std::min<int64_t>(B, n_seeds < 4 ? 2 * pow2_floor(n_seeds) : 2 * pow2_floor(n_seeds - 1));
         B = std::min(B, bmax);
     }
     return std::max(1, pow2_floor(B));
+}
+
+// Seed blocks of one width: n seeds in blocks of B.
+struct SeedRun {
+    int64_t n;
+    int B;
+};
+
+// The blocks of a delayed solve: as many of B0 seeds as are full, then narrower ones for the seeds that are left, whose
+// sweeps would otherwise run over the padding of a whole block. row_bytes: one vector.
+std::vector<SeedRun> seed_runs(const mar_ctx* c, int64_t n_seeds, int B0, int nu, double row_bytes, bool local) {
+    std::vector<SeedRun> runs;
+    constexpr int kMin = 16;   // below, a step's time hardly falls with the width
+    // a pinned width stays; local regions and alternating blocks keep their number of blocks
+    if (c->tune.seed_block > 0 || local || c->tune.two_streams == 1 || B0 <= kMin) {
+        if (n_seeds > 0) runs.push_back({n_seeds, B0});
+        return runs;
+    }
+    int64_t left = n_seeds;
+    if (left >= B0) {
+        runs.push_back({left / B0 * B0, B0});
+        left %= B0;
+    }
+    while (left > 0) {
+        const int fit = std::max<int64_t>(kMin, left > 1 ? 2 * pow2_floor(left - 1) : 1);   // the least that holds them
+        const int half = fit / 2;
+        const int64_t rest = left - half;
+        const int fit2 = rest > 1 ? 2 * pow2_floor(rest - 1) : 1;
+        // in two blocks the padding of fit - half - fit2 seeds is not swept (two passes over nu / 2 slabs on average, at
+        // 5.5 TB/s), but the small kernels and launches of a step (about 80 us) run twice
+        const double saved = (double)(fit - half - std::max(kMin, fit2)) * nu * row_bytes / 5.5e12;
+        if (fit > kMin && saved > 80e-6) {
+            runs.push_back({half, half});
+            left = rest;
+        } else {
+            runs.push_back({left, fit});
+            left = 0;
+        }
+    }
+    return runs;
 }
 
 // What a solve will run: block size, schedule and projection variant.
@@ -697,74 +738,102 @@ mar_status run_solve(mar_ctx* c, const int32_t* d_seeds, int64_t n_seeds, int nu
 // residual. Two passes over the basis per step instead of five.
 template <typename T>
 mar_status run_solve_delayed(mar_ctx* c, const int32_t* d_seeds, int64_t n_seeds, int nu, double mu, double kT,
-                             int B, int variant, double* d_rho, double* d_e_band, double* d_e_seed,
+                             int B0, int variant, double* d_rho, double* d_e_band, double* d_e_seed,
                              double* d_n_seed, int32_t* d_nu_eff, double* d_eps, double* d_w, hipStream_t s) {
     constexpr int VEC = 16 / sizeof(T);
     const int64_t M = (c->M + 3) / 4 * 4;
-    const int64_t nvec = M * B / VEC;
-    const int P = B < VEC ? 1 : B / VEC;
-    const int64_t spmm_wgs = std::max((c->S.n * P + mar::WG - 1) / mar::WG, (c->H.n * P + mar::WG - 1) / mar::WG);
-    const size_t slab = (size_t)M * B * sizeof(T);
-    const int64_t stride = slab_stride(c, M, B, sizeof(T));
     // H u and S u of the same vector in one pass when H is BSR (S on H's pattern)
-    const bool dual = c->H.bsr && c->SH.nnz == c->H.nnz && B >= VEC;
+    const bool dual = c->H.bsr && c->SH.nnz == c->H.nnz && B0 >= VEC;
     // Support tracking: the kernels of a step skip the row tiles on which the block's vectors are exactly
     // zero (farther from every seed of the block than the step in hops of H's pattern).
     const bool sparse = dual && c->tune.support_off == 0;
-    const int64_t nbrow = c->H.n, bpt = mar::WG / std::max(P, 1);
+    const int64_t nbrow = c->H.n;
     // local regions (order-N form): per block row and seed, inside the seed's region or not. With the support
     // tracking on, the products and the update then run over the support list (a small grid of kListWgs
     // workgroups in a grid-stride loop) instead of a workgroup per row tile of the whole cell.
     const bool local = c->loc >= 0 && dual;
-    // Variant 0 streams the basis (variant 7: 8 slabs per workgroup, non-temporal loads) when the solve's
-    // widest sweep (nu + 3 slabs) exceeds the last-level cache: each slab is read once per sweep, and
-    // cached loads would only displace the lines that are reused (the right-hand sides, the vectors just
-    // written). Decided once per solve, so that every projection of a solve runs one kernel on one plan.
-    // Local regions sweep few tiles, which stay cached. Four slabs per workgroup (variant 2) instead:
-    //  * at nu <= 64, where the sweeps are short: at nu = 30 on the 16384-row cell 8 slabs took the
-    //    projection from 71 to 85 ms per step, where at nu = 100 on the 131072-row lattice they took it
-    //    from 316 to 297 ms;
-    //  * for the FP32 form at nu > kUpdAcc64Nu: there a single rho column's error depends on how the
-    //    projection's FP32 sums are partitioned, and the 4-slab partition is the one measured within 1e-5
-    //    (at nu = 300 on the 1048576-row lattice the worst of 8 sampled columns is 9.6e-6 with 4 slabs,
-    //    2.9e-5 with 8).
-    const bool four = nu <= 64 || (std::is_same<T, float>::value && nu > mar::kUpdAcc64Nu);
-    const int pvar = variant == 0 && !local && (double)(nu + 3) * (double)slab > mar::kNtSweepBytes
-                         ? (four ? 2 : 7)
-                         : variant;
-    const int kg = mar::projr_kg(pvar);
-    // default projection grid: the workgroups the device holds at once (one round, few partial sums)
-    const int64_t target = c->tune.proj_wgs > 0 ? (int64_t)c->tune.proj_wgs
-                                                 : (int64_t)projr_occupancy<T>(c, B, pvar) * c->n_cu;
     // grid of the list kernels (local regions): each workgroup also leaves a row of S-norm partials, so small
     // regions run best on few workgroups (512: +2-7 % against 2048 at 4-10 hops, equal at 16, -2 % at 24)
     const int64_t kListWgs = c->loc >= 0 && c->loc <= 16 ? 512 : 2048;
     constexpr double kTwoSetBytes = 160e9;   // two seed-block workspaces only when both fit in this
-    const int mW = (B + 31) / 32;
     const int hreach = local ? std::min(nu, (int)c->loc) : nu;   // farthest hop a vector can reach
     // Hops the support search covers. The whole-cell form does not clear the basis per block: the update
     // writes zeros into slab n + 1 on the tiles 1..kg hops past its support, the farthest a later sweep reads
     // it (a projection chunk of kg slabs, the fused product's neighbour rows), so the search runs kg + 1 hops
     // past the last vector. The eigen-state passes project whole slabs and clear the basis instead.
     const bool ring = sparse && !local && c->es.mode == 0;
-    const int hsup = ring ? nu + kg + 1 : hreach;
-    const int64_t ntiles = (nbrow + bpt - 1) / bpt;
-    const int64_t grid_max = mar::projr_sp_grid(target, nu, kg);
-    size_t part_doubles = 0;
-    // S-norm partials of the fused product, one slot per workgroup (reduced into redb before the projection,
-    // with part as the reduction's scratch)
-    const size_t np_doubles = (size_t)std::max<int64_t>(spmm_wgs, kListWgs) * 2 * B;
-    const int64_t np_cap = (int64_t)np_doubles;
-    for (int nk = 1; nk <= nu; ++nk) {
-        const mar::ProjrGeom gm = mar::projr_geometry(nvec, nk, pvar, target);
-        part_doubles = std::max<size_t>(part_doubles, (size_t)gm.groups * 3 * nk * B);
+    // What depends on the width of a block.
+    struct Geo {
+        int B, P, pvar, kg, mW, hsup;
+        int64_t nvec, spmm_wgs, stride, target, bpt, ntiles, grid_max, np_cap, part_cap, pstride;
+        size_t slab;
+    };
+    auto geometry = [&](int B) {
+        Geo g;
+        g.B = B;
+        g.nvec = M * B / VEC;
+        g.P = B < VEC ? 1 : B / VEC;
+        g.spmm_wgs = std::max((c->S.n * g.P + mar::WG - 1) / mar::WG, (c->H.n * g.P + mar::WG - 1) / mar::WG);
+        g.slab = (size_t)M * B * sizeof(T);
+        g.stride = slab_stride(c, M, B, sizeof(T));
+        g.bpt = mar::WG / std::max(g.P, 1);
+        // Variant 0 streams the basis (variant 7: 8 slabs per workgroup, non-temporal loads) when the solve's
+        // widest sweep (nu + 3 slabs) exceeds the last-level cache: each slab is read once per sweep, and
+        // cached loads would only displace the lines that are reused (the right-hand sides, the vectors just
+        // written). Decided once per block, so that every projection of a block runs one kernel on one plan.
+        // Local regions sweep few tiles, which stay cached. Four slabs per workgroup (variant 2) instead:
+        //  * at nu <= 64, where the sweeps are short: at nu = 30 on the 16384-row cell 8 slabs took the
+        //    projection from 71 to 85 ms per step, where at nu = 100 on the 131072-row lattice they took it
+        //    from 316 to 297 ms;
+        //  * for the FP32 form at nu > kUpdAcc64Nu: there a single rho column's error depends on how the
+        //    projection's FP32 sums are partitioned, and the 4-slab partition is the one measured within 1e-5
+        //    (at nu = 300 on the 1048576-row lattice the worst of 8 sampled columns is 9.6e-6 with 4 slabs,
+        //    2.9e-5 with 8).
+        const bool four = nu <= 64 || (std::is_same<T, float>::value && nu > mar::kUpdAcc64Nu);
+        g.pvar = variant == 0 && !local && (double)(nu + 3) * (double)g.slab > mar::kNtSweepBytes ? (four ? 2 : 7)
+                                                                                                 : variant;
+        g.kg = mar::projr_kg(g.pvar);
+        // default projection grid: the workgroups the device holds at once (one round, few partial sums)
+        g.target = c->tune.proj_wgs > 0 ? (int64_t)c->tune.proj_wgs
+                                        : (int64_t)projr_occupancy<T>(c, B, g.pvar) * c->n_cu;
+        g.mW = (B + 31) / 32;
+        g.hsup = ring ? nu + g.kg + 1 : hreach;
+        g.ntiles = (nbrow + g.bpt - 1) / g.bpt;
+        g.grid_max = mar::projr_sp_grid(g.target, nu, g.kg);
+        g.pstride = 8 + 4 * g.grid_max;   // ints per projection plan; the plans of all steps are kept
+        // S-norm partials of the fused product, one slot per workgroup (reduced into redb before the projection,
+        // with part as the reduction's scratch)
+        g.np_cap = std::max<int64_t>(g.spmm_wgs, kListWgs) * 2 * B;
+        g.part_cap = 0;
+        for (int nk = 1; nk <= nu; ++nk) {
+            const mar::ProjrGeom gm = mar::projr_geometry(g.nvec, nk, g.pvar, g.target);
+            g.part_cap = std::max<int64_t>(g.part_cap, gm.groups * 3 * nk * B);
+        }
+        if (sparse) g.part_cap = std::max<int64_t>(g.part_cap, g.grid_max * 3 * g.kg * B);
+        return g;
+    };
+    const std::vector<SeedRun> runs = seed_runs(c, n_seeds, B0, nu, (double)M * sizeof(T), local);
+    std::vector<Geo> geos;
+    for (const SeedRun& r : runs) geos.push_back(geometry(r.B));
+    if (geos.empty()) geos.push_back(geometry(B0));
+    // the arrays are sized for the first width, the widest, or for what a narrower one needs more of
+    const int B = geos[0].B;
+    const size_t slab = geos[0].slab;
+    const int64_t stride = geos[0].stride;
+    const int mW = geos[0].mW;
+    int64_t part_doubles = 0, np_doubles = 0, pstride_max = 0, ntiles_max = 0;
+    int hsup_max = 0;
+    for (const Geo& g : geos) {
+        part_doubles = std::max(part_doubles, g.part_cap);
+        np_doubles = std::max(np_doubles, g.np_cap);
+        pstride_max = std::max(pstride_max, g.pstride);
+        ntiles_max = std::max(ntiles_max, g.ntiles);
+        hsup_max = std::max(hsup_max, g.hsup);
     }
-    if (sparse) part_doubles = std::max<size_t>(part_doubles, (size_t)grid_max * 3 * kg * B);
     // update depth of the full sweep (support tracking runs one tile of 4 * WG vectors per workgroup)
     const int upd_q = c->tune.upd_q > 0 ? c->tune.upd_q : 4;
     // the FP32 form's update sums in FP64 at large subspace dimensions
     const bool upd_acc64 = std::is_same<T, float>::value && nu > mar::kUpdAcc64Nu;
-    const int64_t part_cap = (int64_t)part_doubles;
 
     size_t off = 0;
     auto take = [&](size_t bytes) {
@@ -776,7 +845,7 @@ mar_status run_solve_delayed(mar_ctx* c, const int32_t* d_seeds, int64_t n_seeds
     // them and between the caller's stream and the context's second stream, so that one block's short FP64
     // kernels (reductions, coefficients, norms, eigensolver) overlap the other block's streaming sweeps.
     const size_t oK = take((size_t)nu * stride * sizeof(T)), oY = take(slab), oSY = take(slab), oZT = take(slab);
-    const size_t oPart = take(part_doubles * 8), oNP = take(np_doubles * 8);
+    const size_t oPart = take((size_t)part_doubles * 8), oNP = take((size_t)np_doubles * 8);
     const size_t oRed = take((size_t)3 * nu * B * 8), oRedb = take((size_t)2 * B * 8);
     const size_t oH = take((size_t)B * nu * nu * 8), oG = take((size_t)B * nu * nu * 8);
     const size_t oKp = take((size_t)B * nu * std::max(1, c->max_row) * 8), oNc = take((size_t)B * 4);
@@ -786,14 +855,14 @@ mar_status run_solve_delayed(mar_ctx* c, const int32_t* d_seeds, int64_t n_seeds
     const size_t oCA = take((size_t)nu * B * 8), oCB = take((size_t)nu * B * 8);
     const size_t oCAf = take((size_t)nu * B * 4), oCBf = take((size_t)nu * B * 4);
     const size_t oAct = take((size_t)B * 4), oNu = take((size_t)B * 4);
-    const size_t oDist = take(sparse ? (size_t)nbrow * 4 : 0), oTD = take(sparse ? (size_t)ntiles * 4 : 0);
-    const size_t oCnt = take(sparse ? (size_t)(std::max(hsup, nu) + 1) * 4 : 0);
-    const size_t oList = take(sparse ? (size_t)ntiles * 4 : 0);
-    const int64_t pstride = 8 + 4 * grid_max;   // ints per projection plan; the plans of all steps are kept
-    const size_t oDl = take(sparse ? (size_t)ntiles * 4 : 0), oPlan = take(sparse ? (size_t)nu * pstride * 4 : 0);
+    const size_t oDist = take(sparse ? (size_t)nbrow * 4 : 0), oTD = take(sparse ? (size_t)ntiles_max * 4 : 0);
+    const size_t oCnt = take(sparse ? (size_t)(std::max(hsup_max, nu) + 1) * 4 : 0);
+    const size_t oList = take(sparse ? (size_t)ntiles_max * 4 : 0);
+    const size_t oDl = take(sparse ? (size_t)ntiles_max * 4 : 0), oPlan = take(sparse ? (size_t)nu * pstride_max * 4 : 0);
     const size_t oM0 = take(local ? (size_t)nbrow * mW * 4 : 0), oM1 = take(local ? (size_t)nbrow * mW * 4 : 0);
     const size_t set_bytes = off;
-    const int64_t n_blocks = (n_seeds + B - 1) / B;
+    int64_t n_blocks = 0;
+    for (const SeedRun& r : runs) n_blocks += (r.n + r.B - 1) / r.B;
     // a caller that captures its stream into a graph of its own gets every kernel on that stream
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
     const bool capturing = !c->dry && hipStreamIsCapturing(s, &cap) == hipSuccess && cap != hipStreamCaptureStatusNone;
@@ -858,17 +927,24 @@ mar_status run_solve_delayed(mar_ctx* c, const int32_t* d_seeds, int64_t n_seeds
     double* n_seed = own_n ? (double*)(w + oN) : d_n_seed;
     int32_t* nu_out = own_nu ? (int32_t*)(w + oNuOut) : d_nu_eff;
     const double tau = sizeof(T) == 4 ? 1e-5 : 1e-12;
-    const int64_t slab_el = stride;
 
     hipStream_t s_caller = s;
     if (nset == 2 && !c->dry) {   // the second stream starts after the caller's earlier work
         hipEventRecord(c->ev_fork, s_caller);
         hipStreamWaitEvent(c->stream2, c->ev_fork, 0);
     }
-    for (int64_t blk0 = 0; blk0 < n_seeds; blk0 += B) {
-        const int ns = (int)std::min<int64_t>(B, n_seeds - blk0);
+    int64_t blk0 = 0;
+    int ns = 0;
+    size_t run = 0;
+    for (int64_t bi = 0, left = runs.empty() ? 0 : runs[0].n; bi < n_blocks; ++bi, blk0 += ns, left -= ns) {
+        if (left == 0) left = runs[++run].n;
+        const Geo& g = geos[run];
+        const int B = g.B, mW = g.mW, kg = g.kg, hsup = g.hsup, pvar = g.pvar;
+        const int64_t stride = g.stride, slab_el = stride, nvec = g.nvec, bpt = g.bpt, ntiles = g.ntiles, target = g.target,
+                      np_cap = g.np_cap, part_cap = g.part_cap, pstride = g.pstride;
+        const size_t slab = g.slab;
+        ns = (int)std::min<int64_t>(B, left);
         const int32_t* seeds = d_seeds + blk0;
-        const int64_t bi = blk0 / B;
         const int set = (int)(bi % nset);
         hipStream_t s = set ? c->stream2 : s_caller;
         char* ws = w + (size_t)set * set_bytes;
@@ -916,8 +992,9 @@ mar_status run_solve_delayed(mar_ctx* c, const int32_t* d_seeds, int64_t n_seeds
         uint32_t* lm0 = (uint32_t*)(ws + oM0);
         uint32_t* lm1 = (uint32_t*)(ws + oM1);
         const uint32_t* lmask = nullptr;
-        if (M != c->M && bi < nset) {
-            // padded rows of Y, S y and S u~ must read as zero (spmm writes rows < M only)
+        if (M != c->M && (bi < nset || run > 0)) {
+            // padded rows of Y, S y and S u~ must read as zero (spmm writes rows < M only); a narrower block has them
+            // elsewhere
             launch(c, s, P_INIT, [&] { return mar::launch_zero(Y, (int64_t)slab, s); });
             launch(c, s, P_INIT, [&] { return mar::launch_zero(SY, (int64_t)slab, s); });
             launch(c, s, P_INIT, [&] { return mar::launch_zero(ZT, (int64_t)slab, s); });
