@@ -801,8 +801,7 @@ mar_status run_solve_delayed(mar_ctx* c, const int32_t* d_seeds, int64_t n_seeds
         g.ntiles = (nbrow + g.bpt - 1) / g.bpt;
         g.grid_max = mar::projr_sp_grid(g.target, nu, g.kg);
         g.pstride = 8 + 4 * g.grid_max;   // ints per projection plan; the plans of all steps are kept
-        // S-norm partials of the fused product, one slot per workgroup (reduced into redb before the projection,
-        // with part as the reduction's scratch)
+        // S-norm partials of the fused product, one slot per workgroup
         g.np_cap = std::max<int64_t>(g.spmm_wgs, kListWgs) * 2 * B;
         g.part_cap = 0;
         for (int nk = 1; nk <= nu; ++nk) {
@@ -846,7 +845,7 @@ mar_status run_solve_delayed(mar_ctx* c, const int32_t* d_seeds, int64_t n_seeds
     // kernels (reductions, coefficients, norms, eigensolver) overlap the other block's streaming sweeps.
     const size_t oK = take((size_t)nu * stride * sizeof(T)), oY = take(slab), oSY = take(slab), oZT = take(slab);
     const size_t oPart = take((size_t)part_doubles * 8), oNP = take((size_t)np_doubles * 8);
-    const size_t oRed = take((size_t)3 * nu * B * 8), oRedb = take((size_t)2 * B * 8);
+    const size_t oRed = take((size_t)3 * nu * B * 8), oRedb = take((size_t)mar::NORM_RANGES * 2 * B * 8);
     const size_t oH = take((size_t)B * nu * nu * 8), oG = take((size_t)B * nu * nu * 8);
     const size_t oKp = take((size_t)B * nu * std::max(1, c->max_row) * 8), oNc = take((size_t)B * 4);
     const size_t oR = take((size_t)B * nu * (nu + 1) * 8), oC1 = take((size_t)B * nu * 8);
@@ -1045,6 +1044,7 @@ mar_status run_solve_delayed(mar_ctx* c, const int32_t* d_seeds, int64_t n_seeds
             const int nk = n + 1;
             const bool last = n + 1 == nu;
             int64_t swgs = 0;
+            // (at n >= 1 with the S-norm partials of slab n, which k_reduce_step and k_coef sum)
             if (dual) {
                 const bool rec = launch(c, s, n == 0 ? P_SPMM : P_SPMM_DOT, [&] {
                     LaunchInfo li = local && sparse
@@ -1064,13 +1064,6 @@ mar_status run_solve_delayed(mar_ctx* c, const int32_t* d_seeds, int64_t n_seeds
                     return li;
                 });
             }
-            // the S-norm partials of slab n, summed across workgroups (a coalesced transposing reduction);
-            // the breakdown test itself runs at the start of this step's coefficient kernel
-            if (n >= 1)
-                // (the projection partials of this step are not written yet: their buffer is the scratch)
-                launch(c, s, P_REDUCE, [&] {
-                    return mar::launch_reduce(npart, swgs, 2 * B, redb, nullptr, B, nu, n, s, part, part_cap);
-                });
             if (!dual) launch(c, s, P_SPMM, [&] { return mar::launch_spmm<T>(B, c->H, Kn, Y, nullptr, 0, 0, s); });
             if (sparse) {
                 const bool rec = launch(c, s, P_SPMM, [&] {
@@ -1085,7 +1078,10 @@ mar_status run_solve_delayed(mar_ctx* c, const int32_t* d_seeds, int64_t n_seeds
                                                    part_cap, pvar, s);
                 });
                 tag(rp, SP_PROJR, n, bi, (double)ntiles);
-                launch(c, s, P_REDUCE, [&] { return mar::launch_reduce_sp(part, plan_n, grid, kg, nk, B, red, s); });
+                launch(c, s, P_REDUCE, [&] {
+                    return mar::launch_reduce_step(part, 0, plan_n, grid, kg, nk, B, red, n >= 1 ? npart : nullptr, swgs,
+                                                   redb, s);
+                });
             } else {
                 launch(c, s, P_SPMM, [&] {
                     return local ? mar::launch_spmm<T>(B, c->SH, Y, SY, nullptr, 0, 0, s, nullptr, 0, lmask, mW)
@@ -1096,12 +1092,14 @@ mar_status run_solve_delayed(mar_ctx* c, const int32_t* d_seeds, int64_t n_seeds
                     return mar::launch_projr<T>(B, K, M, stride, nk, ZT, SY, Y, part, part_cap, &ngroups, target,
                                                 pvar, s);
                 });
-                const int64_t L = (int64_t)3 * nk * B;
-                launch(c, s, P_REDUCE, [&] { return mar::launch_reduce(part, ngroups, L, red, nullptr, B, nu, n, s); });
+                launch(c, s, P_REDUCE, [&] {
+                    return mar::launch_reduce_step(part, ngroups, nullptr, 0, kg, nk, B, red, n >= 1 ? npart : nullptr,
+                                                   swgs, redb, s);
+                });
             }
             launch(c, s, P_COEF, [&] {
                 return mar::launch_coef(B, nu, n, red, h, G, R, C1, BT, UU, cA, cB, cAf, cBf, gam, Fn, active,
-                                        nu_blk, tau, n >= 1 ? redb : nullptr, s);
+                                        nu_blk, tau, redb, n >= 1 ? mar::norm_ranges(swgs) : 0, s);
             });
             const bool ru = launch(c, s, P_UPD2, [&] {
                 // w' goes straight into slab n + 1, unnormalized (its scale is handled by k_coef)

@@ -41,53 +41,10 @@ __global__ __launch_bounds__(WG) void k_reduce(const double* __restrict__ part, 
     }
 }
 
-// First stage of a two-stage reduction of many chunks onto few outputs:
-// tmp[y * L + o] = sum of part[c * L + o] over the chunks c of range y
-// (chunks [y * cps, (y + 1) * cps)), four chunk lanes of 64 outputs per
-// workgroup, each lane's chunks in order with four running sums, then the
-// lanes in order. Rows of 64 consecutive outputs are read whole.
-__global__ __launch_bounds__(WG) void k_reduce_split(const double* __restrict__ part, int64_t nchunks, int64_t L,
-                                                     int64_t cps, double* __restrict__ tmp) {
-    const int oi = threadIdx.x % 64, cl = threadIdx.x / 64;
-    const int64_t o = (int64_t)blockIdx.x * 64 + oi;
-    const int64_t c0 = (int64_t)blockIdx.y * cps;
-    const int64_t c1 = c0 + cps < nchunks ? c0 + cps : nchunks;
-    double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;
-    if (o < L) {
-        int64_t c = c0 + cl;
-        for (; c + 12 < c1; c += 16) {
-            s0 += part[c * L + o];
-            s1 += part[(c + 4) * L + o];
-            s2 += part[(c + 8) * L + o];
-            s3 += part[(c + 12) * L + o];
-        }
-        for (; c < c1; c += 4) s0 += part[c * L + o];
-    }
-    __shared__ double lds[WG];
-    lds[threadIdx.x] = (s0 + s1) + (s2 + s3);
-    __syncthreads();
-    if (cl == 0 && o < L)
-        tmp[(int64_t)blockIdx.y * L + o] = ((lds[oi] + lds[64 + oi]) + lds[128 + oi]) + lds[192 + oi];
-}
-
 LaunchInfo launch_reduce(const double* part, int64_t nchunks, int64_t L, double* out, double* h, int B, int nu,
-                         int n, hipStream_t s, double* tmp, int64_t tmp_cap) {
+                         int n, hipStream_t s) {
     const int64_t hL = h ? (int64_t)(n + 1) * B : 0;
     LaunchInfo li;
-    // Many chunks onto few outputs (the per-workgroup partials of a product kernel): split the chunks into
-    // ranges of RED_CPS, reduce each range over whole rows, then the range sums in order.
-    constexpr int64_t RED_CPS = 128;
-    const int64_t nsplit = (nchunks + RED_CPS - 1) / RED_CPS;
-    if (tmp != nullptr && nchunks >= 8 * RED_CPS && L <= 4096 && nsplit * L <= tmp_cap) {
-        const dim3 grid((unsigned)((L + 63) / 64), (unsigned)nsplit);
-        hipLaunchKernelGGL(k_reduce_split, grid, dim3(WG), 0, s, part, nchunks, L, RED_CPS, tmp);
-        const int64_t wgs = (L + 3) / 4;
-        hipLaunchKernelGGL((k_reduce<4>), dim3(wgs), dim3(WG), 0, s, tmp, nsplit, L, out, h, B, nu, n, hL);
-        li.wgs = (int64_t)grid.x * grid.y + wgs;
-        li.bytes = (double)(nchunks + 2 * nsplit + 1) * L * 8.0;
-        li.flops = (double)nchunks * L;
-        return li;
-    }
     if (L <= 2048) {
         const int64_t wgs = (L + 3) / 4;
         hipLaunchKernelGGL((k_reduce<4>), dim3(wgs), dim3(WG), 0, s, part, nchunks, L, out, h, B, nu, n, hL);
@@ -99,6 +56,142 @@ LaunchInfo launch_reduce(const double* part, int64_t nchunks, int64_t L, double*
     }
     li.bytes = (double)(nchunks + 1) * L * 8.0;
     li.flops = (double)nchunks * L;
+    return li;
+}
+
+// The reductions of one step of the delayed schedule in one launch.
+//
+// Workgroups below w1 sum the projection's partials, OPW outputs each: out[o] = sum over its partials in a fixed order
+// (lanes strided by CL = WG / OPW, each lane's in order, then the CL lane sums in order). Without a plan the partials
+// are part[c * L + o], c < nchunks. With the plan of a support-restricted sweep, o = (r * nk + k) * B + b sums over the
+// groups g that read slab k (ksmin[g] <= ks = k / kg; ksmin does not fall with g) the partial of workgroup
+// off[g] + ks - ksmin[g].
+// The workgroups behind them take the first stage of the S-norm sums, whose partials np.part[c][L2] one product kernel
+// left, a row per workgroup: np.tmp[y][L2] sums the rows of range y, four lanes of 64 outputs per workgroup; the
+// coefficient kernel adds the ranges.
+//
+// What bounds it is latency, not the partials (18 MB at nu = 30, 256 seeds on 16384 rows): the plan is copied to LDS
+// once per workgroup and eight partials are in flight per lane. Measured there: 6.3 us per step; 14.1 us with a plan
+// entry and a partial at a time, and 8.9 us more in two launches for the norms.
+constexpr int64_t PLAN_LDS = 4096;   // groups of a plan copied to LDS (more: a caller's own grid, read in place)
+struct NormPart {
+    const double* part;   // nullptr: none
+    double* tmp;
+    int64_t rows, rows_per;
+    int L, nx;            // outputs, workgroups per range
+};
+
+template <int OPW, bool SP>
+__global__ __launch_bounds__(WG) void k_reduce_step(const double* __restrict__ part, const int32_t* __restrict__ plan,
+                                                    int64_t grid, int64_t nchunks, int kg, int nk, int B, int64_t L,
+                                                    double* __restrict__ out, int64_t w1, NormPart np) {
+    constexpr int CL = WG / OPW, U = 8;
+    extern __shared__ int2 pl[];   // SP: off - ksmin and ksmin of every group
+    __shared__ double lds[WG];
+    if ((int64_t)blockIdx.x >= w1) {
+        const int j = (int)((int64_t)blockIdx.x - w1), x = j % np.nx;
+        const int oi = threadIdx.x % 64, cl = threadIdx.x / 64;
+        const int o = x * 64 + oi;
+        const int64_t y = j / np.nx, c0 = y * np.rows_per, c1 = c0 + np.rows_per < np.rows ? c0 + np.rows_per : np.rows;
+        double t[U] = {};
+        if (o < np.L) {
+            int64_t c = c0 + cl;
+            for (; c + 4 * (U - 1) < c1; c += 4 * U)
+#pragma unroll
+                for (int u = 0; u < U; ++u) t[u] += np.part[(c + 4 * u) * np.L + o];
+            for (; c < c1; c += 4) t[0] += np.part[c * np.L + o];
+        }
+        lds[threadIdx.x] = ((t[0] + t[1]) + (t[2] + t[3])) + ((t[4] + t[5]) + (t[6] + t[7]));
+        __syncthreads();
+        if (cl == 0 && o < np.L) np.tmp[y * np.L + o] = ((lds[oi] + lds[64 + oi]) + lds[128 + oi]) + lds[192 + oi];
+        return;
+    }
+    const int oi = threadIdx.x % OPW, cl = threadIdx.x / OPW;
+    const int64_t o = (int64_t)blockIdx.x * OPW + oi, oc = o < L ? o : L - 1;
+    double s0 = 0.0;
+    if constexpr (SP) {
+        const int ng = plan[0];
+        const int32_t* off = plan + 8;
+        const int32_t* ksm = off + grid;
+        const bool staged = grid <= PLAN_LDS;
+        auto entry = [&](int g) { return make_int2(off[g] - ksm[g], ksm[g]); };
+        if (staged)
+            for (int g = threadIdx.x; g < ng; g += WG) pl[g] = entry(g);
+        __syncthreads();
+        const int64_t b = oc % B, k = (oc / B) % nk, r = oc / ((int64_t)nk * B);
+        const int ks = (int)(k / kg);
+        const double* at = part + (r * kg + k % kg) * B + b;
+        const int64_t wstep = (int64_t)3 * kg * B;
+        for (int g = cl; g < ng; g += CL * U) {
+            if ((staged ? pl[g] : entry(g)).y > ks) break;
+            double v[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int gu = g + u * CL;
+                const int gc = gu < ng ? gu : g;
+                const int2 e = staged ? pl[gc] : entry(gc);
+                const bool in = gu < ng && e.y <= ks;
+                v[u] = at[(in ? e.x + ks : 0) * wstep];
+                if (!in) v[u] = 0.0;
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) s0 += v[u];
+        }
+    } else {
+        for (int64_t c = cl; c < nchunks; c += CL * U) {
+            double v[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int64_t cu = c + u * CL;
+                v[u] = part[(cu < nchunks ? cu : c) * L + oc];
+                if (cu >= nchunks) v[u] = 0.0;
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) s0 += v[u];
+        }
+    }
+    lds[threadIdx.x] = s0;
+    __syncthreads();
+    if (cl == 0 && o < L) {
+        double t = 0.0;
+        for (int c = 0; c < CL; ++c) t += lds[c * OPW + oi];
+        out[o] = t;
+    }
+}
+
+// Rows per range of the norm sums: at most NORM_RANGES ranges, which one wavefront of the coefficient kernel adds, and
+// at least 64 rows each (two rounds of loads).
+static int64_t norm_rows_per(int64_t rows) {
+    const int64_t r = (rows + NORM_RANGES - 1) / NORM_RANGES;
+    return r < 64 ? 64 : r;
+}
+int norm_ranges(int64_t rows) { return rows > 0 ? (int)((rows + norm_rows_per(rows) - 1) / norm_rows_per(rows)) : 0; }
+
+LaunchInfo launch_reduce_step(const double* part, int64_t nchunks, const int32_t* plan, int64_t grid, int kg, int nk,
+                              int B, double* out, const double* npart, int64_t nrows, double* ntmp, hipStream_t s) {
+    const int64_t L = (int64_t)3 * nk * B;
+    const int opw = L <= 2048 ? 4 : 16;
+    const int64_t w1 = (L + opw - 1) / opw;
+    NormPart np{npart, ntmp, nrows, norm_rows_per(nrows), 2 * B, (2 * B + 63) / 64};
+    const int64_t w2 = npart ? (int64_t)np.nx * norm_ranges(nrows) : 0;
+    const dim3 g((unsigned)(w1 + w2));
+    const size_t lds = plan && grid <= PLAN_LDS ? (size_t)grid * sizeof(int2) : 0;
+    if (plan && opw == 4)
+        hipLaunchKernelGGL((k_reduce_step<4, true>), g, dim3(WG), lds, s, part, plan, grid, nchunks, kg, nk, B, L, out, w1, np);
+    else if (plan)
+        hipLaunchKernelGGL((k_reduce_step<16, true>), g, dim3(WG), lds, s, part, plan, grid, nchunks, kg, nk, B, L, out, w1, np);
+    else if (opw == 4)
+        hipLaunchKernelGGL((k_reduce_step<4, false>), g, dim3(WG), 0, s, part, plan, grid, nchunks, kg, nk, B, L, out, w1, np);
+    else
+        hipLaunchKernelGGL((k_reduce_step<16, false>), g, dim3(WG), 0, s, part, plan, grid, nchunks, kg, nk, B, L, out, w1, np);
+    LaunchInfo li;
+    li.wgs = w1 + w2;
+    li.bytes = plan ? (double)L * 8.0 : (double)(nchunks + 1) * L * 8.0;
+    li.flops = plan ? 0.0 : (double)nchunks * L;
+    if (npart) {
+        li.bytes += (double)(nrows + norm_ranges(nrows)) * 2 * B * 8.0;
+        li.flops += (double)nrows * 2 * B;
+    }
     return li;
 }
 
@@ -234,7 +327,7 @@ __global__ __launch_bounds__(WG) void k_coef(int B, int nu, int n, const double*
                                              float* __restrict__ cAf, float* __restrict__ cBf,
                                              double* __restrict__ gam, double* __restrict__ Fn,
                                              int32_t* __restrict__ active, int32_t* __restrict__ nu_eff, double tau,
-                                             const double* __restrict__ redb) {
+                                             const double* __restrict__ redb, int nrange) {
     extern __shared__ double sm[];
     const int b = blockIdx.x, tid = threadIdx.x;
     const int nk = n + 1;
@@ -274,18 +367,22 @@ __global__ __launch_bounds__(WG) void k_coef(int B, int nu, int n, const double*
             }
         }
     };
-    // Step n >= 1 (redb != nullptr): first the breakdown test of slab n, the unnormalized residual of step
-    // n - 1, from redb = {u~.S u~ [B], u~.u~ [B]}: beta~ = sqrt(u~.S u~) <= tau sqrt(|c1_prev|^2 + beta~^2)
+    // Step n >= 1 (nrange > 0): first the breakdown test of slab n, the unnormalized residual of step
+    // n - 1, from the range sums redb[nrange][2 B] of {u~.S u~ [B], u~.u~ [B]}: beta~ = sqrt(u~.S u~) <= tau sqrt(|c1_prev|^2 + beta~^2)
     // stops the seed at nu_eff = n; a negative or non-finite u~.S u~ flags S as not positive definite
     // (nu_eff = -1). Otherwise beta~ and u~.u~ / beta~^2 become BT and UU.
     double btp = BT[b], uu = UU[b];
-    if (redb != nullptr) {
+    if (nrange > 0) {
+        const int lane = tid & 63;
+        const int64_t row = (int64_t)min(lane, nrange - 1) * 2 * B + b;
+        const double rb = redb[row], rw = redb[row + B];
+        const double bb = wave_sum(lane < nrange ? rb : 0.0), ww = wave_sum(lane < nrange ? rw : 0.0);
         double s2 = 0.0;
         for (int k = tid; k < n; k += WG) {
             const double a = C1[(int64_t)b * nu + k];
             s2 += a * a;
         }
-        const double bb = redb[b], ww = redb[B + b], cc = bsum(s2);
+        const double cc = bsum(s2);
         if (active[b]) {
             int nu_new = 0;
             const bool bad = !(bb >= 0.0) || !(bb < INFINITY);
@@ -456,10 +553,10 @@ __global__ __launch_bounds__(WG) void k_coef(int B, int nu, int n, const double*
 LaunchInfo launch_coef(int B, int nu, int n, const double* red, double* A, double* G, double* R, double* C1,
                        double* BT, double* UU, double* cA, double* cB, float* cAf, float* cBf,
                        double* gam, double* Fn, int32_t* active, int32_t* nu_eff, double tau, const double* redb,
-                       hipStream_t s) {
+                       int nrange, hipStream_t s) {
     const size_t lds = (size_t)(8 * (nu + 1) + 8 + 3 * WG) * sizeof(double);
     hipLaunchKernelGGL(k_coef, dim3(B), dim3(WG), lds, s, B, nu, n, red, A, G, R, C1, BT, UU, cA, cB, cAf, cBf, gam,
-                       Fn, active, nu_eff, tau, redb);
+                       Fn, active, nu_eff, tau, redb, nrange);
     LaunchInfo li;
     li.wgs = B;
     const double nn = (double)n + 1.0;

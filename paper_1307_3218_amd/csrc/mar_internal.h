@@ -232,17 +232,24 @@ LaunchInfo launch_upd2(int B, T* basis, int64_t M, int64_t stride, int n, const 
 // 131072-row lattice, where FP32 sums already meet the form's bar with room, they cost 0.7 % of the rate.
 constexpr int kUpdAcc64Nu = 128;
 // cAf/cBf (optional): the update coefficients rounded to FP32 for an FP32 basis.
-// redb (n >= 1): {u~.S u~ [B], u~.u~ [B]} of slab n; the kernel first takes the breakdown test of slab n and
-// sets BT, UU.
+// redb [nrange][2 B] (nrange = 0 at n = 0): range sums of {u~.S u~ [B], u~.u~ [B]} of slab n; the kernel first takes
+// the breakdown test of slab n and sets BT, UU.
 LaunchInfo launch_coef(int B, int nu, int n, const double* red, double* A, double* G, double* R, double* C1,
                        double* BT, double* UU, double* cA, double* cB, float* cAf, float* cBf,
                        double* gam, double* Fn, int32_t* active, int32_t* nu_eff, double tau, const double* redb,
-                       hipStream_t s);
+                       int nrange, hipStream_t s);
 
-// Fixed-order sums out[o] = sum_c part[c * L + o]. With tmp (tmp_cap doubles, not read by anything in flight)
-// and many chunks onto few outputs, the sum runs in two stages through tmp.
+// Fixed-order sums out[o] = sum_c part[c * L + o].
 LaunchInfo launch_reduce(const double* part, int64_t nchunks, int64_t L, double* out, double* h, int B, int nu,
-                         int n, hipStream_t s, double* tmp = nullptr, int64_t tmp_cap = 0);
+                         int n, hipStream_t s);
+
+// The reductions of a step of the delayed schedule: the projection's partials into out[3][nk][B] (by the plan of a
+// support-restricted sweep, or nchunks rows without one), and the nrows rows of S-norm partials npart [nrows][2 B]
+// (none when nullptr) into ntmp, norm_ranges(nrows) rows for launch_coef.
+constexpr int NORM_RANGES = 64;
+int norm_ranges(int64_t rows);
+LaunchInfo launch_reduce_step(const double* part, int64_t nchunks, const int32_t* plan, int64_t grid, int kg, int nk,
+                              int B, double* out, const double* npart, int64_t nrows, double* ntmp, hipStream_t s);
 
 // ---- support tracking of a seed block (exact zeros of the Krylov vectors) ----
 constexpr int32_t SUP_FAR = 0x3fffffff;   // tile distance: farther than the largest hop count kept
@@ -264,9 +271,6 @@ __host__ __device__ inline int64_t projr_sp_grid(int64_t G, int nk, int kg) { re
 // largest plan; refused otherwise).
 LaunchInfo launch_projr_plan(const int32_t* cnt, const int32_t* Dl, int n0, int nsteps, int kg, int64_t G,
                              int64_t pstride, int32_t* plans, hipStream_t s);
-// Fixed-order sum of the per-workgroup partials of that projection into red[3][nk][B].
-LaunchInfo launch_reduce_sp(const double* part, const int32_t* plan, int64_t grid, int kg, int nk, int B,
-                            double* out, hipStream_t s);
 // The projection sweep over the planned tiles (variants as in projr_geometry); partials part[wg][3][kg][B].
 template <typename T>
 LaunchInfo launch_projr_sp(int B, const T* basis, int64_t M, int64_t stride, int n, const T* r0, const T* r1,

@@ -327,56 +327,4 @@ LaunchInfo launch_projr_plan(const int32_t* cnt, const int32_t* Dl, int n0, int 
     return li;
 }
 
-// red[(r * nk + k) * B + b] = sum over the groups that read slab k of the
-// partial of workgroup off[g] + ks - ksmin[g] (ks = k / kg), in group order
-// (group lanes strided by CL, then the CL lane sums in order).
-template <int OPW>
-__global__ __launch_bounds__(WG) void k_reduce_sp(const double* __restrict__ part, const int32_t* __restrict__ plan,
-                                                  int64_t grid, int kg, int nk, int B, int64_t L,
-                                                  double* __restrict__ out) {
-    constexpr int CL = WG / OPW;
-    const int oi = threadIdx.x % OPW, cl = threadIdx.x / OPW;
-    const int64_t o = (int64_t)blockIdx.x * OPW + oi;
-    const int ng = plan[0];
-    const int32_t* off = plan + 8;
-    const int32_t* ksm = off + grid;
-    double s0 = 0.0;
-    if (o < L) {
-        const int64_t b = o % B, k = (o / B) % nk, r = o / ((int64_t)nk * B);
-        const int ks = (int)(k / kg), kk = (int)(k % kg);
-        for (int g = cl; g < ng; g += CL) {
-            const int km = ksm[g];
-            if (km <= ks) {
-                const int64_t w = off[g] + (ks - km);
-                s0 += part[((w * 3 + r) * kg + kk) * B + b];
-            }
-        }
-    }
-    __shared__ double lds[WG];
-    lds[threadIdx.x] = s0;
-    __syncthreads();
-    if (cl == 0 && o < L) {
-        double t = 0.0;
-        for (int c = 0; c < CL; ++c) t += lds[c * OPW + oi];
-        out[o] = t;
-    }
-}
-
-LaunchInfo launch_reduce_sp(const double* part, const int32_t* plan, int64_t grid, int kg, int nk, int B,
-                            double* out, hipStream_t s) {
-    const int64_t L = (int64_t)3 * nk * B;
-    LaunchInfo li;
-    if (L <= 2048) {
-        const int64_t wgs = (L + 3) / 4;
-        hipLaunchKernelGGL((k_reduce_sp<4>), dim3(wgs), dim3(WG), 0, s, part, plan, grid, kg, nk, B, L, out);
-        li.wgs = wgs;
-    } else {
-        const int64_t wgs = (L + 15) / 16;
-        hipLaunchKernelGGL((k_reduce_sp<16>), dim3(wgs), dim3(WG), 0, s, part, plan, grid, kg, nk, B, L, out);
-        li.wgs = wgs;
-    }
-    li.bytes = (double)L * 8.0;
-    return li;
-}
-
 }  // namespace mar
