@@ -293,6 +293,13 @@ LaunchInfo launch_zero(void* p, int64_t bytes, hipStream_t s) {
     return li;
 }
 
+// A wavefront's own LDS writes become visible to its other lanes.
+__device__ __forceinline__ void wave_lds_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
+}
+
 // ---------------------------------------------------------------------------
 // Delayed-reorthogonalization schedule: small FP64 per-seed algebra of step n.
 //
@@ -317,40 +324,60 @@ LaunchInfo launch_zero(void* p, int64_t bytes, hipStream_t s) {
 // do the sweep's right-hand sides; the products are rescaled here, and the
 // update coefficients go out multiplied by s (k_upd2 divides by s gamma).
 // A stopped seed gets gamma = inf, so that its slabs become zero.
-// One workgroup per seed; A is h[b][k][n]; G is [nu][nu]; R is column-major
-// [nu][nu+1] (R_{p,k} at k*(nu+1) + p).
-__global__ __launch_bounds__(WG) void k_coef(int B, int nu, int n, const double* __restrict__ red,
-                                             double* __restrict__ Ah, double* __restrict__ Gm,
-                                             double* __restrict__ Rm, double* __restrict__ C1,
-                                             double* __restrict__ BT, double* __restrict__ UU,
-                                             double* __restrict__ cA, double* __restrict__ cB,
-                                             float* __restrict__ cAf, float* __restrict__ cBf,
-                                             double* __restrict__ gam, double* __restrict__ Fn,
-                                             int32_t* __restrict__ active, int32_t* __restrict__ nu_eff, double tau,
-                                             const double* __restrict__ redb, int nrange) {
+// A is h[b][k][n]; G is [nu][nu]; R is column-major [nu][nu+1] (R_{p,k} at
+// k*(nu+1) + p).
+//
+// One workgroup of W wavefronts per seed. What bounds it is latency: a few KB to a few hundred KB per seed, passed
+// through a chain of sums. Lane = row p of R and G (64 rows at a time), wavefront w takes the columns k = w mod W, so that
+// rows are read whole; the W partial sums meet in LDS. The scalar sums are formed by every wavefront for itself, from the
+// vectors in LDS, without a barrier. KU > 0 (nu <= 64, nu <= KU W): the two matrices and the vectors are requested at the
+// start, before anything is known of the step, and kept in registers: one trip to memory and three barriers. KU = 0: the
+// columns are read eight at a time, 64 rows after another with one barrier each (the partial sums alternate between two
+// buffers). Measured (us per step, 256 seeds): 7.4 at nu = 30 and (FP64, 128 seeds) 8.1 at nu = 50, where a workgroup of
+// 256 threads with four columns in flight and a barrier for every scalar sum took 11.9 and 13.1; 26 at nu = 300 (64
+// seeds), 48 before.
+template <int W, int KU>
+__global__ __launch_bounds__(W * 64) void k_coef(int B, int nu, int n, const double* __restrict__ red,
+                                                 double* __restrict__ Ah, double* __restrict__ Gm,
+                                                 double* __restrict__ Rm, double* __restrict__ C1,
+                                                 double* __restrict__ BT, double* __restrict__ UU,
+                                                 double* __restrict__ cA, double* __restrict__ cB,
+                                                 float* __restrict__ cAf, float* __restrict__ cBf,
+                                                 double* __restrict__ gam, double* __restrict__ Fn,
+                                                 int32_t* __restrict__ active, int32_t* __restrict__ nu_eff, double tau,
+                                                 const double* __restrict__ redb, int nrange) {
+    constexpr int NT = W * 64;
+    constexpr bool PRE = KU > 0;
     extern __shared__ double sm[];
-    const int b = blockIdx.x, tid = threadIdx.x;
+    const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
+    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int nk = n + 1;
     double* c2 = sm;
     double* g = c2 + (nu + 1);
     double* e = g + (nu + 1);
     double* c1p = e + (nu + 1);
-    double* t = c1p + (nu + 1);
-    double* gc2 = t + (nu + 1);
-    double* q = gc2 + (nu + 1);
-    double* gq = q + (nu + 1);
-    double* red8 = gq + (nu + 1);
-    double* hsum = red8 + 8;   // [WG][3]: the two halves' sums of the Gram pass
-    auto bsum = [&](double v) {
+    double* q = c1p + (nu + 1);
+    double* v = q + (nu + 1);        // column n of G
+    double* gq = v + (nu + 1);
+    double* ps = gq + (nu + 1);      // partial sums: PRE [4][W][64], else [2][3][W][64]
+    double* A = Ah + (int64_t)b * nu * nu;
+    double* G = Gm + (int64_t)b * nu * nu;
+    double* Rc = Rm + (int64_t)b * nu * (nu + 1);
+
+    double rr[PRE ? KU : 1], gg[PRE ? KU : 1], ap = 0.0;
+    if constexpr (PRE) {
+        // columns and rows past the step's read column and row 0: finite, and taken with a zero or not used
+        const int pr = lane <= nu ? lane : 0, pg = lane < n ? lane : 0;
 #pragma unroll
-        for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
-        __syncthreads();
-        if ((tid & 63) == 0) red8[tid >> 6] = v;
-        __syncthreads();
-        return (red8[0] + red8[1]) + (red8[2] + red8[3]);
-    };
+        for (int i = 0; i < KU; ++i) {
+            const int k = wv + i * W;
+            rr[i] = Rc[(int64_t)(k < n - 1 ? k : 0) * (nu + 1) + pr];
+            gg[i] = G[(int64_t)(k < n ? k : 0) * nu + pg];
+        }
+        ap = A[lane < n ? (int64_t)lane * nu + (n - 1) : 0];
+    }
     auto stop = [&](int nu_new) {
-        for (int k = tid; k < n; k += WG) {
+        for (int k = tid; k < n; k += NT) {
             cA[(int64_t)k * B + b] = 0.0;
             cB[(int64_t)k * B + b] = 0.0;
             if (cAf) {
@@ -367,53 +394,24 @@ __global__ __launch_bounds__(WG) void k_coef(int B, int nu, int n, const double*
             }
         }
     };
-    // Step n >= 1 (nrange > 0): first the breakdown test of slab n, the unnormalized residual of step
-    // n - 1, from the range sums redb[nrange][2 B] of {u~.S u~ [B], u~.u~ [B]}: beta~ = sqrt(u~.S u~) <= tau sqrt(|c1_prev|^2 + beta~^2)
+    // Step n >= 1 (nrange > 0): the breakdown test of slab n, the unnormalized residual of step n - 1, from the range
+    // sums redb[nrange][2 B] of {u~.S u~ [B], u~.u~ [B]}: beta~ = sqrt(u~.S u~) <= tau sqrt(|c1_prev|^2 + beta~^2)
     // stops the seed at nu_eff = n; a negative or non-finite u~.S u~ flags S as not positive definite
     // (nu_eff = -1). Otherwise beta~ and u~.u~ / beta~^2 become BT and UU.
-    double btp = BT[b], uu = UU[b];
+    const bool was_active = active[b] != 0;
+    double btp = BT[b], uu = UU[b], bb = 0.0, ww = 0.0;
     if (nrange > 0) {
-        const int lane = tid & 63;
         const int64_t row = (int64_t)min(lane, nrange - 1) * 2 * B + b;
         const double rb = redb[row], rw = redb[row + B];
-        const double bb = wave_sum(lane < nrange ? rb : 0.0), ww = wave_sum(lane < nrange ? rw : 0.0);
-        double s2 = 0.0;
-        for (int k = tid; k < n; k += WG) {
-            const double a = C1[(int64_t)b * nu + k];
-            s2 += a * a;
-        }
-        const double cc = bsum(s2);
-        if (active[b]) {
-            int nu_new = 0;
-            const bool bad = !(bb >= 0.0) || !(bb < INFINITY);
-            if (bad) nu_new = -1;
-            else if (sqrt(bb) <= tau * sqrt(cc + bb)) nu_new = n;
-            if (bad || nu_new == n) {
-                if (tid == 0) {
-                    nu_eff[b] = nu_new;
-                    active[b] = 0;
-                    BT[b] = 0.0;
-                }
-                stop(-1);
-                return;
-            }
+        bb = wave_sum(lane < nrange ? rb : 0.0);
+        ww = wave_sum(lane < nrange ? rw : 0.0);
+        if (was_active) {
             btp = sqrt(bb);
             uu = ww / bb;
-            if (tid == 0) {
-                BT[b] = btp;
-                UU[b] = uu;
-            }
         }
     }
-    if (!active[b]) {
-        stop(-1);
-        return;
-    }
-    double* A = Ah + (int64_t)b * nu * nu;
-    double* G = Gm + (int64_t)b * nu * nu;
-    double* Rc = Rm + (int64_t)b * nu * (nu + 1);
     const double sc = n >= 1 ? btp : 1.0;   // scale of slab n
-    for (int k = tid; k < n; k += WG) {
+    for (int k = tid; k < n; k += NT) {
         c2[k] = red[((int64_t)0 * nk + k) * B + b] / sc;
         g[k] = red[((int64_t)1 * nk + k) * B + b] / sc;
         e[k] = red[((int64_t)2 * nk + k) * B + b] / sc;
@@ -423,13 +421,33 @@ __global__ __launch_bounds__(WG) void k_coef(int B, int nu, int n, const double*
     const double uty = red[((int64_t)2 * nk + n) * B + b] / sc / sc;
     __syncthreads();
     double p0 = 0.0, p1 = 0.0, p2 = 0.0, p3 = 0.0;
-    for (int k = tid; k < n; k += WG) {
+    for (int k = lane; k < n; k += 64) {
         p0 += c2[k] * c2[k];
         p1 += c1p[k] * c1p[k];
         p2 += c2[k] * e[k];
         p3 += c2[k] * g[k];
     }
-    const double s_cc = bsum(p0), s_c1p = bsum(p1), s_ce = bsum(p2), s_cg = bsum(p3);
+    const double s_cc = wave_sum(p0), s_c1p = wave_sum(p1), s_ce = wave_sum(p2), s_cg = wave_sum(p3);
+    if (nrange > 0 && was_active) {
+        const bool bad = !(bb >= 0.0) || !(bb < INFINITY);
+        if (bad || btp <= tau * sqrt(s_c1p + bb)) {
+            if (tid == 0) {
+                nu_eff[b] = bad ? -1 : n;
+                active[b] = 0;
+                BT[b] = 0.0;
+            }
+            stop(-1);
+            return;
+        }
+        if (tid == 0) {
+            BT[b] = btp;
+            UU[b] = uu;
+        }
+    }
+    if (!was_active) {
+        stop(-1);
+        return;
+    }
     const double gam2 = 1.0 - s_cc;
     if (!(gam2 > 0.0)) {  // u~ lies in span(K): the Krylov space is exhausted
         stop(n);
@@ -443,105 +461,133 @@ __global__ __launch_bounds__(WG) void k_coef(int B, int nu, int n, const double*
             stop(n);
             return;
         }
-        for (int p = tid; p < n; p += WG) Rc[(int64_t)(n - 1) * (nu + 1) + p] = c1p[p] + btp * c2[p];
-        if (tid == 0) Rc[(int64_t)(n - 1) * (nu + 1) + n] = btp * gm;
+        // column n - 1 of R, its zeros included
+        for (int p = tid; p <= nu; p += NT)
+            Rc[(int64_t)(n - 1) * (nu + 1) + p] = p < n ? c1p[p] + btp * c2[p] : p == n ? btp * gm : 0.0;
     }
-    __syncthreads();
-    // q = R[:n+1, :n] c2 (R_{p,k} vanishes for p > k + 1); each row's k range split over the two halves of
-    // the workgroup as in the Gram pass below
-    {
-        const int half = tid / (WG / 2), pl = tid % (WG / 2);
-        for (int p0 = 0; p0 <= n; p0 += WG / 2) {
-            const int p = p0 + pl;
-            double sq[4] = {0.0, 0.0, 0.0, 0.0};
-            if (p <= n) {
-                const int k0 = p > 0 ? p - 1 : 0;
-                const int kmid = k0 + (n - k0) / 2;
-                int k = half ? kmid : k0;
-                const int ke = half ? n : kmid;
-                for (; k + 3 < ke; k += 4) {
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) sq[i] += Rc[(int64_t)(k + i) * (nu + 1) + p] * c2[k + i];
-                }
-                for (; k < ke; ++k) sq[0] += Rc[(int64_t)k * (nu + 1) + p] * c2[k];
-            }
-            hsum[(int64_t)(half * (WG / 2) + pl) * 3] = (sq[0] + sq[1]) + (sq[2] + sq[3]);
-            __syncthreads();
-            if (half == 0 && p <= n) q[p] = hsum[(int64_t)pl * 3] + hsum[(int64_t)(WG / 2 + pl) * 3];
-            __syncthreads();
-        }
-    }
-    // one pass over the first n columns of G: G c1_prev, G c2 and G q. Thread (half, pl) takes column
-    // p = p0 + pl and half of its k range (four running sums each, so that four loads of G are in flight);
-    // the halves' sums meet in LDS and add in a fixed order.
-    {
-        const int half = tid / (WG / 2), pl = tid % (WG / 2);
-        const int kmid = n / 2;
-        const int kb = half ? kmid : 0, ke = half ? n : kmid;
-        for (int p0 = 0; p0 < n; p0 += WG / 2) {
-            const int p = p0 + pl;
-            double sg[4] = {0.0, 0.0, 0.0, 0.0}, sv[4] = {0.0, 0.0, 0.0, 0.0}, sw[4] = {0.0, 0.0, 0.0, 0.0};
-            if (p < n) {
-                int k = kb;
-                for (; k + 3 < ke; k += 4) {
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        const double gkp = G[(int64_t)(k + i) * nu + p];
-                        sg[i] += gkp * c1p[k + i];
-                        sv[i] += gkp * c2[k + i];
-                        sw[i] += gkp * q[k + i];
-                    }
-                }
-                for (; k < ke; ++k) {
-                    const double gkp = G[(int64_t)k * nu + p];
-                    sg[0] += gkp * c1p[k];
-                    sv[0] += gkp * c2[k];
-                    sw[0] += gkp * q[k];
-                }
-            }
-            double* hs = hsum + (int64_t)(half * (WG / 2) + pl) * 3;
-            hs[0] = (sg[0] + sg[1]) + (sg[2] + sg[3]);
-            hs[1] = (sv[0] + sv[1]) + (sv[2] + sv[3]);
-            hs[2] = (sw[0] + sw[1]) + (sw[2] + sw[3]);
-            __syncthreads();
-            if (half == 0 && p < n) {
-                const double* h1 = hsum + (int64_t)(WG / 2 + pl) * 3;
-                if (n >= 1) t[p] = (A[(int64_t)p * nu + (n - 1)] - (hs[0] + h1[0])) / btp;
-                gc2[p] = hs[1] + h1[1];
-                gq[p] = hs[2] + h1[2];
-            }
-            __syncthreads();
-        }
-    }
-    __syncthreads();
+    // From the sums over all k: q = R[:n+1, :n] c2 (its column n - 1 formed here), then with G c1_prev and G c2 the
+    // column n of G, its products with c2 and q on the way. Every wavefront does all rows.
     double p4 = 0.0, p5 = 0.0, p6 = 0.0;
-    for (int p = tid; p < n; p += WG) {
-        const double v = (t[p] - gc2[p]) / gm;
-        G[(int64_t)p * nu + n] = v;
-        G[(int64_t)n * nu + p] = v;
-        p4 += c2[p] * t[p];
-        p5 += c2[p] * gc2[p];
-        p6 += v * q[p];
+    auto row_q = [&](int p, double sum) {
+        if (n >= 1 && p <= n) sum += (p < n ? c1p[p] + btp * c2[p] : btp * gm) * c2[n - 1];
+        if (p <= n) q[p] = sum;
+    };
+    auto row_v = [&](int p, double gc1, double gc2, double a) {
+        if (p < n) {
+            const double t = (a - gc1) / btp, x = (t - gc2) / gm;
+            v[p] = x;
+            p4 += c2[p] * t;
+            p5 += c2[p] * gc2;
+            p6 += x * q[p];
+        }
+    };
+    auto total = [&](const double* s) {   // the W partial sums of the lane's row, in order
+        double t = 0.0;
+#pragma unroll
+        for (int u = 0; u < W; ++u) t += s[u * 64 + lane];
+        return t;
+    };
+    if constexpr (PRE) {
+        double sq = 0.0, s1 = 0.0, s2 = 0.0, sw = 0.0;
+#pragma unroll
+        for (int i = 0; i < KU; ++i) {
+            const int k = wv + i * W, kc = k < n ? k : 0;
+            const double x2 = k < n ? c2[kc] : 0.0, x1 = k < n ? c1p[kc] : 0.0;
+            if (n >= 2) sq += rr[i] * (k < n - 1 ? x2 : 0.0);
+            s1 += gg[i] * x1;
+            s2 += gg[i] * x2;
+        }
+        ps[tid] = sq;
+        ps[NT + tid] = s1;
+        ps[2 * NT + tid] = s2;
+        __syncthreads();
+        row_q(lane, total(ps));
+        row_v(lane, total(ps + NT), total(ps + 2 * NT), ap);
+        wave_lds_sync();
+#pragma unroll
+        for (int i = 0; i < KU; ++i) {
+            const int k = wv + i * W, kc = k < n ? k : 0;
+            sw += gg[i] * (k < n ? q[kc] : 0.0);
+        }
+        ps[3 * NT + tid] = sw;   // a place of its own: other wavefronts may still read the first sums
+        __syncthreads();
+        if (tid < n) gq[tid] = total(ps + 3 * NT);
+    } else {
+        constexpr int U = 8;
+        int buf = 0;
+        for (int c = 0; c * 64 <= n; ++c, buf ^= 1) {
+            const int p = c * 64 + lane;
+            double s[U] = {};
+            // the chunk's rows begin at column c * 64 - 1
+            int k0 = c * 64 - 1 - (W - 1);
+            k0 = k0 > 0 ? k0 / W * W : 0;
+            for (int k = k0 + wv; k < n - 1; k += W * U)
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const int ku = k + u * W;
+                    const bool in = ku < n - 1;
+                    const double r = Rc[(int64_t)(in ? ku : k) * (nu + 1) + (p <= nu ? p : 0)];
+                    s[u] += r * (in ? c2[in ? ku : k] : 0.0);
+                }
+            double* pb = ps + buf * 3 * NT;
+            pb[tid] = ((s[0] + s[1]) + (s[2] + s[3])) + ((s[4] + s[5]) + (s[6] + s[7]));
+            __syncthreads();
+            row_q(p, total(pb));
+        }
+        wave_lds_sync();
+        for (int c = 0; c * 64 < n; ++c, buf ^= 1) {
+            const int p = c * 64 + lane, pc = p < n ? p : 0;
+            const double a = A[(int64_t)pc * nu + (n - 1)];
+            double s1[4] = {}, s2[4] = {}, sw[4] = {};
+            for (int k = wv; k < n; k += W * U) {
+                double x[U];
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const int ku = k + u * W;
+                    x[u] = G[(int64_t)(ku < n ? ku : 0) * nu + pc];
+                }
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const int ku = k + u * W, kc = ku < n ? ku : 0;
+                    const double y = ku < n ? x[u] : 0.0;
+                    s1[u & 3] += y * c1p[kc];
+                    s2[u & 3] += y * c2[kc];
+                    sw[u & 3] += y * q[kc];
+                }
+            }
+            double* pb = ps + buf * 3 * NT;
+            pb[tid] = (s1[0] + s1[1]) + (s1[2] + s1[3]);
+            pb[NT + tid] = (s2[0] + s2[1]) + (s2[2] + s2[3]);
+            pb[2 * NT + tid] = (sw[0] + sw[1]) + (sw[2] + sw[3]);
+            __syncthreads();
+            row_v(p, total(pb), total(pb + NT), a);
+            if (p < n) gq[p] = total(pb + 2 * NT);
+        }
+        __syncthreads();
     }
-    const double s_ct = bsum(p4), s_cgc = bsum(p5), s_vq = bsum(p6);
+    wave_lds_sync();
+    const double s_ct = wave_sum(p4), s_cgc = wave_sum(p5), s_vq = wave_sum(p6);
     const double gnn = (uu - 2.0 * s_ct + s_cgc) / gam2;
-    if (tid == 0) G[(int64_t)n * nu + n] = gnn;
     const double En = (uty - s_ce) / gm;
     const double Fnn = (utsy - s_cg) / gm;
-    for (int p = tid; p <= n; p += WG) {
-        // (G q)_p over k <= n: the old columns, then column n (G[p][n] = G[n][p], just formed)
-        const double sgq = p < n ? gq[p] + G[(int64_t)p * nu + n] * q[n] : s_vq + gnn * q[n];
+    const double qn = q[n];
+    for (int p = tid; p <= n; p += NT) {
+        // (G q)_p over k <= n: the old columns, then column n
+        const double sgq = p < n ? gq[p] + v[p] * qn : s_vq + gnn * qn;
         const double Ep = p < n ? e[p] : En;
         A[(int64_t)p * nu + n] = (Ep - sgq) / gm;
         const double Fp = p < n ? g[p] : Fnn;
         C1[(int64_t)b * nu + p] = (Fp - q[p]) / gm;
-    }
-    for (int k = tid; k < n; k += WG) {
-        cA[(int64_t)k * B + b] = sc * c2[k];
-        cB[(int64_t)k * B + b] = sc * g[k];
-        if (cAf) {  // the same coefficients rounded once to the basis precision
-            cAf[(int64_t)k * B + b] = (float)(sc * c2[k]);
-            cBf[(int64_t)k * B + b] = (float)(sc * g[k]);
+        const double gp = p < n ? v[p] : gnn;
+        G[(int64_t)p * nu + n] = gp;
+        G[(int64_t)n * nu + p] = gp;
+        if (p < n) {
+            cA[(int64_t)p * B + b] = sc * c2[p];
+            cB[(int64_t)p * B + b] = sc * g[p];
+            if (cAf) {  // the same coefficients rounded once to the basis precision
+                cAf[(int64_t)p * B + b] = (float)(sc * c2[p]);
+                cBf[(int64_t)p * B + b] = (float)(sc * g[p]);
+            }
         }
     }
     if (tid == 0) {
@@ -550,13 +596,25 @@ __global__ __launch_bounds__(WG) void k_coef(int B, int nu, int n, const double*
     }
 }
 
+template <int W, int KU>
+static void coef(int B, int nu, int n, const double* red, double* A, double* G, double* R, double* C1, double* BT,
+                 double* UU, double* cA, double* cB, float* cAf, float* cBf, double* gam, double* Fn, int32_t* active,
+                 int32_t* nu_eff, double tau, const double* redb, int nrange, hipStream_t s) {
+    const size_t lds = (size_t)(7 * (nu + 1) + (KU > 0 ? 4 : 6) * W * 64) * sizeof(double);
+    static std::atomic<uint64_t> done{0};
+    if (lds > 64 * 1024) allow_full_lds((const void*)k_coef<W, KU>, done);
+    hipLaunchKernelGGL((k_coef<W, KU>), dim3(B), dim3(W * 64), lds, s, B, nu, n, red, A, G, R, C1, BT, UU, cA, cB, cAf,
+                       cBf, gam, Fn, active, nu_eff, tau, redb, nrange);
+}
+
 LaunchInfo launch_coef(int B, int nu, int n, const double* red, double* A, double* G, double* R, double* C1,
                        double* BT, double* UU, double* cA, double* cB, float* cAf, float* cBf,
                        double* gam, double* Fn, int32_t* active, int32_t* nu_eff, double tau, const double* redb,
                        int nrange, hipStream_t s) {
-    const size_t lds = (size_t)(8 * (nu + 1) + 8 + 3 * WG) * sizeof(double);
-    hipLaunchKernelGGL(k_coef, dim3(B), dim3(WG), lds, s, B, nu, n, red, A, G, R, C1, BT, UU, cA, cB, cAf, cBf, gam,
-                       Fn, active, nu_eff, tau, redb, nrange);
+    // 4 wavefronts hold the matrices up to nu = 32, 8 up to nu = 64 (7.4 us per step at nu = 30 against 7.5 for 8; 8.1 at
+    // nu = 50 against 9.1 for 4); at nu = 100 the columns read as they are used take 17.3 us, kept in registers 17.8
+    auto f = nu <= 32 ? coef<4, 8> : nu <= 64 ? coef<8, 8> : coef<16, 0>;
+    f(B, nu, n, red, A, G, R, C1, BT, UU, cA, cB, cAf, cBf, gam, Fn, active, nu_eff, tau, redb, nrange, s);
     LaunchInfo li;
     li.wgs = B;
     const double nn = (double)n + 1.0;
