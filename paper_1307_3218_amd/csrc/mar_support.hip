@@ -53,6 +53,60 @@ __global__ __launch_bounds__(WG) void k_sup_hop(int64_t nbrow, const int32_t* __
         }
 }
 
+// The whole search in one workgroup: distances, the rows reached in order (queue) and a bit per row reached, in LDS. Every
+// row's columns are read once, when the search reaches it (the pattern is symmetric), and the search ends with the last
+// row reached, however large hmax is. What bounds it is the latency of a level (a row's columns are read together): 40 us
+// for 256 seeds on 4096 block rows and 201 us on 32768, where a launch per level took about 4 us for each of nu + 5 levels
+// (165 us at nu = 30, 450 us at nu = 100).
+constexpr int SUP_WG = 1024;
+constexpr int64_t SUP_LDS_ROWS = 36 * 1024;   // 4 bytes and a bit per row within 160 KB
+
+__global__ __launch_bounds__(SUP_WG) void k_sup_search(const int32_t* __restrict__ seeds, int ns, int64_t M, int nbrow,
+                                                       const int32_t* __restrict__ brp, const int32_t* __restrict__ bcol,
+                                                       int hmax, int32_t* __restrict__ dist) {
+    extern __shared__ uint32_t vis[];
+    __shared__ int tail;
+    const int tid = threadIdx.x, words = (nbrow + 31) / 32;
+    uint16_t* d = (uint16_t*)(vis + words);
+    uint16_t* queue = d + nbrow;
+    constexpr uint16_t FAR = 0xffff;
+    for (int i = tid; i < words; i += SUP_WG) vis[i] = 0;
+    for (int i = tid; i < nbrow; i += SUP_WG) d[i] = FAR;
+    if (tid == 0) tail = 0;
+    __syncthreads();
+    auto reach = [&](int I, int h) {
+        const uint32_t bit = 1u << (I & 31);
+        if (atomicOr(&vis[I >> 5], bit) & bit) return;
+        d[I] = (uint16_t)h;
+        queue[atomicAdd(&tail, 1)] = (uint16_t)I;
+    };
+    for (int b = tid; b < ns; b += SUP_WG) {
+        const int j = seeds[b];
+        if (j >= 0 && j < M) reach(j / 4, 0);
+    }
+    __syncthreads();
+    int lo = 0, hi = tail;
+    for (int h = 1; h <= hmax && lo < hi; ++h) {
+        __syncthreads();   // everyone has read tail
+        for (int i = lo + tid; i < hi; i += SUP_WG) {
+            const int I = queue[i], q1 = brp[I + 1];
+            for (int q = brp[I]; q < q1; q += 8) {
+                int c[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) c[u] = bcol[q + u < q1 ? q + u : q];
+#pragma unroll
+                for (int u = 0; u < 8; ++u)
+                    if (q + u < q1) reach(c[u], h);
+            }
+        }
+        __syncthreads();
+        lo = hi;
+        hi = tail;
+    }
+    __syncthreads();
+    for (int i = tid; i < nbrow; i += SUP_WG) dist[i] = d[i] == FAR ? SUP_FAR : d[i];
+}
+
 __global__ __launch_bounds__(WG) void k_sup_tiles(int64_t nbrow, int bpt, int64_t ntiles,
                                                   const int32_t* __restrict__ dist, int hmax,
                                                   int32_t* __restrict__ D) {
@@ -117,9 +171,17 @@ LaunchInfo launch_support(int64_t M, int64_t nbrow, const int32_t* brp, const in
                           int32_t* cnt, int32_t* list, int32_t* Dl, hipStream_t s) {
     const int64_t ntiles = (nbrow + bpt - 1) / bpt;
     const unsigned rw = (unsigned)((nbrow + WG - 1) / WG), tw = (unsigned)((ntiles + WG - 1) / WG);
-    hipLaunchKernelGGL(k_sup_fill, dim3(rw), dim3(WG), 0, s, dist, nbrow);
-    if (ns > 0) hipLaunchKernelGGL(k_sup_seed, dim3((ns + WG - 1) / WG), dim3(WG), 0, s, seeds, ns, M, dist);
-    for (int h = 1; h <= hmax; ++h) hipLaunchKernelGGL(k_sup_hop, dim3(rw), dim3(WG), 0, s, nbrow, brp, bcol, dist, h);
+    if (nbrow <= SUP_LDS_ROWS && hmax < 0xffff) {
+        static std::atomic<uint64_t> done{0};
+        allow_lds((const void*)k_sup_search, done, 160 * 1024 - 256);
+        const size_t lds = (size_t)((nbrow + 31) / 32) * 4 + (size_t)nbrow * 4;
+        hipLaunchKernelGGL(k_sup_search, dim3(1), dim3(SUP_WG), lds, s, seeds, ns, M, (int)nbrow, brp, bcol, hmax, dist);
+    } else {
+        hipLaunchKernelGGL(k_sup_fill, dim3(rw), dim3(WG), 0, s, dist, nbrow);
+        if (ns > 0) hipLaunchKernelGGL(k_sup_seed, dim3((ns + WG - 1) / WG), dim3(WG), 0, s, seeds, ns, M, dist);
+        for (int h = 1; h <= hmax; ++h)
+            hipLaunchKernelGGL(k_sup_hop, dim3(rw), dim3(WG), 0, s, nbrow, brp, bcol, dist, h);
+    }
     hipLaunchKernelGGL(k_sup_tiles, dim3(tw), dim3(WG), 0, s, nbrow, bpt, ntiles, dist, hmax, D);
     hipLaunchKernelGGL(k_sup_count, dim3(hcnt + 1), dim3(WG), 0, s, ntiles, D, cnt);
     hipLaunchKernelGGL(k_sup_scatter, dim3(hmax + 1), dim3(WG), 0, s, ntiles, D, cnt, list, Dl);
