@@ -90,9 +90,15 @@ struct mar_ctx {
         double sigma = 0.0;
         double *pdot = nullptr, *pred = nullptr, *phi = nullptr;
         int groups = 64;
+        // one workgroup per seed: what the first pass leaves of every seed (nullptr: computed again)
+        void* K = nullptr;        // [seed][nu][rows] in the basis precision
+        double *h = nullptr, *Kp = nullptr;
+        int32_t* m = nullptr;     // [seed]
     } es;
     char* fws = nullptr;          // workspace of the device Fermi-level search
     size_t fws_bytes = 0;
+    char* kws = nullptr;          // what an eigen state's first pass leaves for its second
+    size_t kws_bytes = 0;
     // local flipping: distance-2 colouring of H's rows (built at the first call) and workspace
     int32_t* fl_round = nullptr;  // [nround][2] entries of fl_crow that a round of k_flip takes
     int32_t* fl_crow = nullptr;   // [M] rows by colour, index order within a colour
@@ -136,6 +142,7 @@ struct mar_ctx {
         if (ws) hipFree(ws);
         if (io) hipFree(io);
         if (fws) hipFree(fws);
+        if (kws) hipFree(kws);
         if (flws) hipFree(flws);
         if (stream) hipStreamDestroy(stream);
         if (stream2) hipStreamDestroy(stream2);
@@ -1189,12 +1196,29 @@ mar_status run_seedwise(mar_ctx* c, const mar_request& r, hipStream_t s) {
     for (int64_t at = 0; at < n_seeds; at += chunk) {
         const int ns = (int)std::min<int64_t>(chunk, n_seeds - at);
         const int32_t* seeds = r.d_seeds + at;
-        launch(c, s, P_UPD, [&] {
-            mar::SeedGeom gc = g;
-            gc.grid = std::min(g.grid, ns);
-            return mar::launch_seed<T>(gc, c->H, c->SH, c->M, c->diagS, seeds, ns, nu, c->loc, tau, (T*)(w + oK), c->Hrp,
-                                       c->max_row, h, Kp, nucp, pref ? c->es.vref : nullptr, pref, ns, acc64, s);
-        });
+        // an eigen state's first pass keeps what its second needs, and works on a copy (the eigensolve overwrites it)
+        T* keep = c->es.K ? (T*)c->es.K + (size_t)at * nu * 4 * g.nbcap : nullptr;
+        const size_t hs = (size_t)nu * nu, ks = (size_t)nu * c->max_row;
+        double* hk = keep ? c->es.h + (size_t)at * hs : h;
+        double* Kpk = keep ? c->es.Kp + (size_t)at * ks : Kp;
+        const int32_t* mk = nucp;
+        if (!keep || c->es.mode == 0)
+            launch(c, s, P_UPD, [&] {
+                mar::SeedGeom gc = g;
+                gc.grid = std::min(g.grid, ns);
+                return mar::launch_seed<T>(gc, c->H, c->SH, c->M, c->diagS, seeds, ns, nu, c->loc, tau, (T*)(w + oK),
+                                           c->Hrp, c->max_row, hk, Kpk, keep ? c->es.m + at : nucp,
+                                           pref ? c->es.vref : nullptr, pref, ns, keep, acc64, s);
+            });
+        else
+            launch(c, s, P_UPD, [&] {
+                return mar::launch_es_dots<T>(keep, 4 * (int64_t)g.nbcap, nu, ns, c->es.m + at, c->es.vref, pref, s);
+            });
+        if (keep && !c->dry) {
+            mk = c->es.m + at;
+            HIP_OR(c, hipMemcpyAsync(h, hk, (size_t)ns * hs * 8, hipMemcpyDeviceToDevice, s));
+            HIP_OR(c, hipMemcpyAsync(Kp, Kpk, (size_t)ns * ks * 8, hipMemcpyDeviceToDevice, s));
+        }
         mar::EigExtra ex;
         ex.eig_max_sweeps = c->tune.eig_max_sweeps > 0 ? c->tune.eig_max_sweeps : 40;
         ex.jacobi = c->tune.eig_max_sweeps > 0;
@@ -1207,7 +1231,7 @@ mar_status run_seedwise(mar_ctx* c, const mar_request& r, hipStream_t s) {
             ex.phi = c->es.phi + at;
         }
         launch(c, s, P_EIG, [&] {
-            return mar::launch_eig(ns, seeds, nu, h, nucp, Kp, c->Hrp, c->Hcol, c->Hval, c->SvalH, c->diagS, c->max_row,
+            return mar::launch_eig(ns, seeds, nu, h, mk, Kp, c->Hrp, c->Hcol, c->Hval, c->SvalH, c->diagS, c->max_row,
                                    r.mu, r.kT, r.d_rho, e_seed + at, n_seed + at, nu_out + at,
                                    r.d_eps ? r.d_eps + at * nu : nullptr, r.d_weight ? r.d_weight + at * nu : nullptr,
                                    c->zc_defer ? c->zc_defer + (size_t)at * nu * c->max_row : nullptr, ex, s);
@@ -1764,6 +1788,55 @@ mar_status mar_eigen_state_async(mar_ctx* c, const int32_t* d_seeds, int64_t n_s
     int32_t* ref = d_ref ? d_ref : (int32_t*)(f + oRef);
     int32_t* refseed = (int32_t*)(f + oRs);
     double* one = (double*)(f + o1);   // per-seed outputs of the one-seed reference solve
+    // With one workgroup per seed the first pass keeps every seed's basis, subspace matrix and gathered rows, so that the
+    // reference vector and the second pass need no Krylov phase of their own (512 atoms, nu = 30, FP64, all 2048 seeds,
+    // 1 GB: 11.2 ms against 21.9). Not where that takes more than kKeepBytes, in a caller's static scratch, while
+    // the stream is captured and nothing is allocated yet, or when the device has no room.
+    constexpr double kKeepBytes = 8e9;
+    const size_t el = prec == MAR_FP32 ? 4 : 8, nr = 4 * (size_t)c->H.n, hs = (size_t)nu * nu * 8,
+                 ks = (size_t)nu * c->max_row * 8, K1 = align_up((size_t)nu * nr * el);
+    size_t koff = 0;
+    auto ktake = [&](size_t bytes) {
+        const size_t o = koff;
+        koff += align_up(bytes);
+        return o;
+    };
+    const size_t oKK = ktake(n * nu * nr * el), oKh = ktake(n * hs), oKK1 = ktake(K1), oKh1 = ktake(hs),
+                 oKk = ktake(n * ks), oKk1 = ktake(ks), oKm = ktake(n * 4), oKm1 = ktake(4);
+    bool keep = pl.seedwise && (double)koff <= kKeepBytes && !c->ext_ws;
+    if (keep && koff > c->kws_bytes) {
+        hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+        size_t fr = 0, tot = 0;
+        keep = hipStreamIsCapturing(s, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone &&
+               hipMemGetInfo(&fr, &tot) == hipSuccess && koff + (koff >> 3) <= fr + c->kws_bytes;
+        if (keep) {
+            if (c->kws) {
+                HIP_OR(c, hipDeviceSynchronize());
+                HIP_OR(c, hipFree(c->kws));
+            }
+            c->kws = nullptr;
+            c->kws_bytes = 0;
+            void* p = nullptr;
+            if (hipMalloc(&p, koff) == hipSuccess) {
+                c->kws = (char*)p;
+                c->kws_bytes = koff;
+            } else {
+                (void)hipGetLastError();
+                keep = false;
+            }
+        }
+    }
+    struct EsReset {   // the hook ends with the call, however it ends
+        mar_ctx* c;
+        ~EsReset() { c->es = mar_ctx::EsHook{}; }
+    } es_reset{c};
+    c->es = mar_ctx::EsHook{};
+    if (keep) {
+        c->es.K = c->kws + oKK;
+        c->es.h = (double*)(c->kws + oKh);
+        c->es.Kp = (double*)(c->kws + oKk);
+        c->es.m = (int32_t*)(c->kws + oKm);
+    }
     // pass 1: levels, weights and rows e_i.v_alpha of every seed (Sec. 3: the Green's function of all seeds)
     mar_request r{d_seeds, n_seeds, nu, 0.0, 0.0, prec, form, nullptr, nullptr, (double*)(f + oE), (double*)(f + oN),
                   nu_eff, eps, wt};
@@ -1785,7 +1858,6 @@ mar_status mar_eigen_state_async(mar_ctx* c, const int32_t* d_seeds, int64_t n_s
         return set_err(c, MAR_ERR_STATE, "internal error: a launch was refused; eigen state not computed");
     }
     // pass 1': the reference seed alone (B = 1), its eigenvector formed over all rows as v_ref
-    c->es = mar_ctx::EsHook{};
     c->es.mode = 1;
     c->es.Rg = (double*)(f + oRg);
     c->es.Y = (double*)(f + oY);
@@ -1794,12 +1866,25 @@ mar_status mar_eigen_state_async(mar_ctx* c, const int32_t* d_seeds, int64_t n_s
     c->es.vref = (double*)(f + oVr);
     c->es.lv = d_levels;
     c->es.sigma = sigma;
-    mar_request r1{refseed, 1, nu, 0.0, 0.0, prec, MAR_FORM_PLAIN, nullptr, nullptr, one, one + 1, (int32_t*)(one + 2),
-                   nullptr, nullptr};
-    st = dispatch_solve(c, r1, plan_solve(c, nu, prec, MAR_FORM_PLAIN, 1), s);
-    if (st != MAR_OK) {
-        c->es = mar_ctx::EsHook{};
-        return st;
+    if (keep) {
+        auto reference = [&](auto* K1p) {
+            using T = std::remove_pointer_t<decltype(K1p)>;
+            double *h1 = (double*)(c->kws + oKh1), *Kp1 = (double*)(c->kws + oKk1);
+            int32_t* m1 = (int32_t*)(c->kws + oKm1);
+            launch(c, s, P_EIG, [&] {
+                return mar::launch_es_take<T>(ref, (const T*)c->es.K, nr, nu, c->max_row, c->es.h, c->es.Kp, c->es.m, K1p,
+                                              h1, Kp1, m1, s);
+            });
+            eig_stage<T>(c, s, 1, 1, refseed, nu, h1, m1, Kp1, K1p, nr, c->M, 0.0, 0.0, nullptr, one, one + 1,
+                         (int32_t*)(one + 2), nullptr, nullptr, 0);
+        };
+        if (prec == MAR_FP32) reference((float*)(c->kws + oKK1));
+        else reference((double*)(c->kws + oKK1));
+    } else {
+        mar_request r1{refseed, 1, nu, 0.0, 0.0, prec, MAR_FORM_PLAIN, nullptr, nullptr, one, one + 1,
+                       (int32_t*)(one + 2), nullptr, nullptr};
+        st = dispatch_solve(c, r1, plan_solve(c, nu, prec, MAR_FORM_PLAIN, 1), s);
+        if (st != MAR_OK) return st;
     }
     // pass 2: every seed again, with v_ref . v_alpha^(j) from K^T v_ref, then Eq. 3 with those signs
     c->es.mode = 2;
@@ -1808,7 +1893,6 @@ mar_status mar_eigen_state_async(mar_ctx* c, const int32_t* d_seeds, int64_t n_s
     c->es.groups = groups;
     c->es.phi = d_phi;
     st = dispatch_solve(c, r, pl, s);
-    c->es = mar_ctx::EsHook{};
     if (st != MAR_OK) return st;
     HIP_OR(c, hipGetLastError());
     return MAR_OK;

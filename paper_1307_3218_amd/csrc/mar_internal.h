@@ -315,7 +315,16 @@ template <typename T>
 LaunchInfo launch_seed(const SeedGeom& g, const DevMat& H, const DevMat& SH, int64_t M, const double* diagS,
                        const int32_t* seeds, int ns, int nu, int hops, double tau, T* scratch, const int32_t* Hrp,
                        int max_row, double* h, double* Kp, int32_t* nu_out, const double* vref, double* pref, int64_t pB,
-                       bool acc64, hipStream_t s);
+                       T* keep, bool acc64, hipStream_t s);
+// Eigen states on a kept basis keep [seed][nu][nr] (nr rows of the whole cell): u_k . v_ref into pref [nu][ns], and one
+// seed's share (the place in ref[0]) of the kept arrays.
+template <typename T>
+LaunchInfo launch_es_dots(const T* keep, int64_t nr, int nu, int ns, const int32_t* nu_eff, const double* vref,
+                          double* pref, hipStream_t s);
+template <typename T>
+LaunchInfo launch_es_take(const int32_t* ref, const T* keep, int64_t nr, int nu, int max_row, const double* h,
+                          const double* Kp, const int32_t* nu_eff, T* keep1, double* h1, double* Kp1, int32_t* nu1,
+                          hipStream_t s);
 // Largest number of block rows within hops of any block row (cap + 1: more than cap) into out[0].
 LaunchInfo launch_region_max(int64_t nbrow, const int32_t* brp, const int32_t* bcol, int hops, int cap, int32_t* out,
                              hipStream_t s);

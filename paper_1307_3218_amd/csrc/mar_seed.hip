@@ -59,6 +59,7 @@ struct SeedArgs {
     const double* vref;     // or null: also pref[k * pB + seed] = u_k . vref
     double* pref;
     int64_t pB;
+    T* keep;                // or null: every basis vector also to keep[seed][nu][rows] (whole cells)
 };
 
 // Sums of V (4 or 8) values per lane over a wavefront: afterwards lane holds in v[0] the sum of value lane / (64 / V).
@@ -219,7 +220,8 @@ __global__ __launch_bounds__(SEED_WG) void k_seed(SeedArgs<T> a) {
         const int nr = 4 * nb, nvec = nr / VEC;
         int nl = (int)(g.kbytes / ((size_t)nr * sizeof(T)));
         nl = nl >= nu ? nu : nl / SEED_G * SEED_G;
-        T* Kg = a.scratch + (int64_t)blockIdx.x * g.sstride - (int64_t)nl * nr;
+        T* kept = a.keep != nullptr ? a.keep + (int64_t)b * nu * nr : nullptr;
+        T* Kg = kept ? kept : a.scratch + (int64_t)blockIdx.x * g.sstride - (int64_t)nl * nr;
         if (tid == 0) {   // local block row of the seed: the list is ascending
             int lo = 0, hi = nb - 1;
             while (lo < hi) {
@@ -237,6 +239,7 @@ __global__ __launch_bounds__(SEED_WG) void k_seed(SeedArgs<T> a) {
             const T v = i == jl ? u1 : (T)0;
             u[i] = v;
             K0[i] = v;
+            if (kept && nl > 0) kept[i] = v;
         }
         if (tid < 4) u[nr + tid] = y[nr + tid] = z[nr + tid] = (T)0;
 
@@ -497,6 +500,8 @@ __global__ __launch_bounds__(SEED_WG) void k_seed(SeedArgs<T> a) {
                 row_values(a.hv, voff, rlen, 0);
                 lds_barrier();
             }
+            if (kept && nk < nl)
+                for (int i = tid; i < nr; i += nt) kept[(int64_t)nk * nr + i] = u[i];
             product(a.hv, u, y);
         }
         __syncthreads();
@@ -579,7 +584,7 @@ template <typename T>
 static LaunchInfo launch_seed_t(const SeedGeom& g, const DevMat& H, const DevMat& SH, int64_t M, const double* diagS,
                                 const int32_t* seeds, int ns, int nu, int hops, double tau, T* scratch,
                                 const int32_t* Hrp, int max_row, double* h, double* Kp, int32_t* nu_out,
-                                const double* vref, double* pref, int64_t pB, bool acc64, hipStream_t s) {
+                                const double* vref, double* pref, int64_t pB, T* keep, bool acc64, hipStream_t s) {
     LaunchInfo li;
     if (!g.ok || !H.bsr || SH.nnz != H.nnz || H.n != g.nbrow) {
         li.wgs = -1;
@@ -587,7 +592,7 @@ static LaunchInfo launch_seed_t(const SeedGeom& g, const DevMat& H, const DevMat
     }
     constexpr bool F32 = std::is_same<T, float>::value;
     SeedArgs<T> a{g, M, H.ptr, H.idx, F32 ? (const T*)H.v32 : (const T*)H.v64, F32 ? (const T*)SH.v32 : (const T*)SH.v64,
-                  diagS, seeds, ns, nu, hops, tau, scratch, Hrp, max_row, h, Kp, nu_out, vref, pref, pB};
+                  diagS, seeds, ns, nu, hops, tau, scratch, Hrp, max_row, h, Kp, nu_out, vref, pref, pB, keep};
     if (F32 && acc64) {
         static std::atomic<uint64_t> done{0};
         allow_full_lds((const void*)k_seed<T, F32>, done);
@@ -609,18 +614,89 @@ template <>
 LaunchInfo launch_seed<float>(const SeedGeom& g, const DevMat& H, const DevMat& SH, int64_t M, const double* diagS,
                               const int32_t* seeds, int ns, int nu, int hops, double tau, float* scratch,
                               const int32_t* Hrp, int max_row, double* h, double* Kp, int32_t* nu_out,
-                              const double* vref, double* pref, int64_t pB, bool acc64, hipStream_t s) {
+                              const double* vref, double* pref, int64_t pB, float* keep, bool acc64,
+                              hipStream_t s) {
     return launch_seed_t<float>(g, H, SH, M, diagS, seeds, ns, nu, hops, tau, scratch, Hrp, max_row, h, Kp, nu_out, vref,
-                                pref, pB, acc64, s);
+                                pref, pB, keep, acc64, s);
 }
 template <>
 LaunchInfo launch_seed<double>(const SeedGeom& g, const DevMat& H, const DevMat& SH, int64_t M, const double* diagS,
                                const int32_t* seeds, int ns, int nu, int hops, double tau, double* scratch,
                                const int32_t* Hrp, int max_row, double* h, double* Kp, int32_t* nu_out,
-                               const double* vref, double* pref, int64_t pB, bool acc64, hipStream_t s) {
+                               const double* vref, double* pref, int64_t pB, double* keep, bool acc64,
+                               hipStream_t s) {
     return launch_seed_t<double>(g, H, SH, M, diagS, seeds, ns, nu, hops, tau, scratch, Hrp, max_row, h, Kp, nu_out, vref,
-                                 pref, pB, acc64, s);
+                                 pref, pB, keep, acc64, s);
 }
+
+// ---------------------------------------------------------------------------
+// Eigen states on the basis kept by a first pass, [seed][nu][nr]. k_es_dots: pref[k * ns + seed] = u_k . v_ref, a
+// workgroup per seed, a wavefront per vector; bound by the reads of the basis (1 GB for 2048 seeds at nu = 30, FP64: 0.17 ms, 5.8 TB/s).
+template <typename T>
+__global__ __launch_bounds__(WG) void k_es_dots(const T* __restrict__ keep, int64_t nr, int nu,
+                                                const int32_t* __restrict__ nu_eff, const double* __restrict__ vref,
+                                                double* __restrict__ pref) {
+    typedef typename Vec16<T>::type VT;
+    constexpr int VEC = Vec16<T>::n;
+    const int b = blockIdx.x, lane = threadIdx.x & 63, ns = gridDim.x, m = nu_eff[b];
+    for (int k = threadIdx.x >> 6; k < nu; k += WG / 64) {
+        double s = 0.0;
+        if (k < m) {
+            const VT* u = reinterpret_cast<const VT*>(keep + ((int64_t)b * nu + k) * nr);
+            for (int v = lane; v < nr / VEC; v += 64) {
+                T e[VEC];
+                unpack(u[v], e);
+#pragma unroll
+                for (int i = 0; i < VEC; ++i) s += (double)e[i] * vref[v * VEC + i];
+            }
+            s = wave_sum(s);
+        }
+        if (lane == 0) pref[(int64_t)k * ns + b] = s;
+    }
+}
+
+// The kept basis, subspace matrix, gathered rows and dimension of the reference seed (ref[0]: its place) on their own.
+template <typename T>
+__global__ __launch_bounds__(WG) void k_es_take(const int32_t* __restrict__ ref, const T* __restrict__ keep, int64_t nK,
+                                                const double* __restrict__ h, int64_t nh, const double* __restrict__ Kp,
+                                                int64_t nKp, const int32_t* __restrict__ nu_eff, T* __restrict__ keep1,
+                                                double* __restrict__ h1, double* __restrict__ Kp1,
+                                                int32_t* __restrict__ nu1) {
+    const int64_t b = ref[0], i0 = (int64_t)blockIdx.x * WG + threadIdx.x, st = (int64_t)gridDim.x * WG;
+    for (int64_t i = i0; i < nK; i += st) keep1[i] = keep[b * nK + i];
+    for (int64_t i = i0; i < nh; i += st) h1[i] = h[b * nh + i];
+    for (int64_t i = i0; i < nKp; i += st) Kp1[i] = Kp[b * nKp + i];
+    if (i0 == 0) nu1[0] = nu_eff[b];
+}
+
+template <typename T>
+LaunchInfo launch_es_dots(const T* keep, int64_t nr, int nu, int ns, const int32_t* nu_eff, const double* vref,
+                          double* pref, hipStream_t s) {
+    hipLaunchKernelGGL((k_es_dots<T>), dim3(ns), dim3(WG), 0, s, keep, nr, nu, nu_eff, vref, pref);
+    LaunchInfo li;
+    li.wgs = ns;
+    li.bytes = (double)ns * nu * nr * sizeof(T);
+    li.flops = 2.0 * ns * nu * nr;
+    return li;
+}
+template <typename T>
+LaunchInfo launch_es_take(const int32_t* ref, const T* keep, int64_t nr, int nu, int max_row, const double* h,
+                          const double* Kp, const int32_t* nu_eff, T* keep1, double* h1, double* Kp1, int32_t* nu1,
+                          hipStream_t s) {
+    hipLaunchKernelGGL((k_es_take<T>), dim3(128), dim3(WG), 0, s, ref, keep, nr * nu, h, (int64_t)nu * nu, Kp,
+                       (int64_t)nu * max_row, nu_eff, keep1, h1, Kp1, nu1);
+    LaunchInfo li;
+    li.wgs = 128;
+    li.bytes = 2.0 * ((double)nr * nu * sizeof(T) + (double)nu * (nu + max_row) * 8.0);
+    return li;
+}
+#define MAR_ES(T)                                                                                                     \
+    template LaunchInfo launch_es_dots<T>(const T*, int64_t, int, int, const int32_t*, const double*, double*, hipStream_t); \
+    template LaunchInfo launch_es_take<T>(const int32_t*, const T*, int64_t, int, int, const double*, const double*,  \
+                                          const int32_t*, T*, double*, double*, int32_t*, hipStream_t);
+MAR_ES(float)
+MAR_ES(double)
+#undef MAR_ES
 
 // ---------------------------------------------------------------------------
 // Largest number of block rows within `hops` hops of any block row, or cap + 1 when some set is larger than cap:
