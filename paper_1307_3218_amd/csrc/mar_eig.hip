@@ -24,6 +24,8 @@
 #include <cfloat>
 #include <cstdint>
 
+#include <type_traits>
+
 #include "mar_device.h"
 #include "mar_internal.h"
 
@@ -352,15 +354,15 @@ __device__ __forceinline__ void eig_results(const EigExtra& ex, int b, int m, in
         }
     }
     group_sync<NT>();
-    if (tid == 0) {
-        double E = 0.0, N = 0.0;
-        for (int t = 0; t < nP; ++t) {
-            E += rhoL[t] * Hval[rlo + t];
-            N += rhoL[t] * SvalH[rlo + t];
+    if (tid < 64) {   // nP <= 63
+        const bool in = tid < nP;
+        const double r = in ? rhoL[tid] : 0.0;
+        const double E = wave_sum(r * (in ? Hval[rlo + tid] : 0.0)), N = wave_sum(r * (in ? SvalH[rlo + tid] : 0.0));
+        if (tid == 0) {
+            e_seed[b] = E;
+            n_seed[b] = N;
+            nu_eff_out[b] = m;
         }
-        e_seed[b] = E;
-        n_seed[b] = N;
-        nu_eff_out[b] = m;
     }
 }
 
@@ -804,11 +806,15 @@ __global__ __launch_bounds__(TRI_WG) void k_tri_big(EigExtra ex, const int32_t* 
 // Implicit QL iteration on the tridiagonal (d, e) of a seed with Wilkinson shifts, one wavefront per seed: every lane
 // carries the recurrence of the rotations, lane c applies them to column c of R (rows i + 1 and i of R; row i stays in
 // a register for the next rotation, which takes rows i and i - 1). The next d, e and row of R are requested one
-// rotation ahead. What bounds it: about 1.1 m^2 rotations in sequence, each some forty instructions that one wavefront
-// issues one after the other (an FP64 operation every seven cycles; the recurrence's dependent chain is no longer than
-// that), so the seeds of a launch share the chip: four to a workgroup, one on each SIMD.
+// rotation ahead. What bounds it: about 1.1 m^2 rotations in sequence, each 24 FP64 operations and a dozen others that one
+// wavefront issues one after the other (an FP64 operation every seven cycles: 269 cycles a rotation at nu = 100; the
+// recurrence's dependent chain is shorter), so the seeds of a launch share the chip: four to a workgroup, one on each
+// SIMD. All control is kept in scalar registers (the dimension, the block's ends and addresses are the same in every
+// lane) and the underflow check out of the loop: with masks, per-lane address products and selects a rotation took 350
+// cycles (nu = 30, 256 seeds: 193 us, now 152; nu = 100, 1024 seeds: 1.61 ms, now 1.23; nu = 300, 64 seeds: 12.5, now
+// 8.9).
 constexpr int QL_MAX_ITER = 60;   // iterations allowed per level (about two are needed)
-inline size_t ql_lds_bytes(int nu, int nr) { return (((size_t)nu * nr + 3 * (size_t)nu + 64) * 8 + 15) & ~(size_t)15; }
+inline size_t ql_lds_bytes(int nu, int nr) { return (((size_t)nu * nr + 3 * (size_t)nu + 66) * 8 + 15) & ~(size_t)15; }
 __global__ __launch_bounds__(256) void k_ql(EigExtra ex, int nseeds, const int32_t* __restrict__ seeds, int nu,
                                            const double* __restrict__ h, const int32_t* __restrict__ nu_eff_blk,
                                            const double* __restrict__ Kp, const int32_t* __restrict__ Hrp,
@@ -820,7 +826,7 @@ __global__ __launch_bounds__(256) void k_ql(EigExtra ex, int nseeds, const int32
                                            double* __restrict__ w_out, double* __restrict__ zc,
                                            int seed_doubles) {
     extern __shared__ double smem[];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int b = blockIdx.x * (blockDim.x >> 6) + wave;
     if (b >= nseeds) return;
     const int m = nu_eff_blk[b];
@@ -832,7 +838,8 @@ __global__ __launch_bounds__(256) void k_ql(EigExtra ex, int nseeds, const int32
     }
     const int j = seeds[b], rlo = Hrp[j], nP = Hrp[j + 1] - rlo;
     const int NR = nP + 1 + (ex.mode == 2 ? 1 : 0);
-    double2* de = reinterpret_cast<double2*>(smem + (size_t)wave * seed_doubles);   // {d_i, e_i}
+    // {d_i, e_i}; the entry in front of the first is read ahead of the last rotation and not used
+    double2* de = reinterpret_cast<double2*>(smem + (size_t)wave * seed_doubles) + 1;
     double* fz = reinterpret_cast<double*>(de + nu);
     double* rhoL = fz + nu;
     double* R = rhoL + 64;
@@ -846,8 +853,10 @@ __global__ __launch_bounds__(256) void k_ql(EigExtra ex, int nseeds, const int32
     double* Rw = R + (lane < NR ? lane : 0);   // lanes past the columns repeat column 0
     bool fail = false;
     int sc = 0;
-    // the second time only when some f^2 + g^2 underflowed: with the check on every rotation
-    for (int safe = 0; safe < 2; ++safe) {
+    unsigned xmin = ~0u;   // high word of the smallest f^2 + g^2 met
+    // SAFE, the second time, only when some f^2 + g^2 underflowed: with the check on every rotation
+    auto iterate = [&](auto safe_form) {
+        constexpr bool SAFE = decltype(safe_form)::value;
         double mx = 0.0;
         for (int i = lane; i < m; i += 64) {
             const double di = hb[i], ei = i + 1 < m ? hb[nu + i] : 0.0;
@@ -858,14 +867,24 @@ __global__ __launch_bounds__(256) void k_ql(EigExtra ex, int nseeds, const int32
         for (int o = 32; o > 0; o >>= 1) mx = fmax(mx, __shfl_xor(mx, o));
         sc = mx > 0.0 && mx < INFINITY ? -ilogb(mx) - 1 : 0;
         for (int i = lane; i < m; i += 64) de[i] = make_double2(ldexp(de[i].x, sc), ldexp(de[i].y, sc));
-        for (int idx = lane; idx < m * NR; idx += 64) {
-            const int k = idx / NR, c = idx - k * NR;
-            R[idx] = c == 0 ? (k == 0 ? 1.0 : 0.0)
-                            : (c <= nP ? Kp[((int64_t)b * nu + k) * max_row + (c - 1)] : ex.pref[(int64_t)k * ex.pB + b]);
+        // lane = column: e_1, the gathered rows, and v_ref's products; eight rows in flight
+        const double* col = lane >= 1 && lane <= nP ? Kp + (int64_t)b * nu * max_row + (lane - 1) : ex.pref + b;
+        const int64_t cst = lane <= nP ? max_row : ex.pB;
+        const bool mem = lane >= 1 && lane < NR;
+        for (int k0 = 0; k0 < m; k0 += 8) {
+            double v[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) v[u] = k0 + u == 0 ? 1.0 : 0.0;
+            if (mem) {
+#pragma unroll
+                for (int u = 0; u < 8; ++u) v[u] = col[min(k0 + u, m - 1) * cst];
+            }
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+                if (lane < NR && k0 + u < m) R[(k0 + u) * NR + lane] = v[u];
         }
         wave_sync();
         fail = false;
-        double xmin = 1.0;   // smallest f^2 + g^2 met
         for (int l = 0; l + 1 < m && !fail; ++l) {
             for (int iter = 0;; ++iter) {
                 // the first negligible e_i, i >= l: the block l .. mm is unreduced
@@ -895,11 +914,12 @@ __global__ __launch_bounds__(256) void k_ql(EigExtra ex, int nseeds, const int32
                 const double den = ag > 1e150 ? 2.0 * ag : ag + q1 * rsqrt_nr(q1);
                 g = di1 - del.x + copysign(del.y * recip(den), ag == 0.0 ? del.y : del.y * (g < 0.0 ? -1.0 : 1.0));
                 double s = 1.0, c = 1.0, p = 0.0;
-#pragma unroll 2
-                for (int i = mm - 1; i >= l; --i) {
-                    const int in = max(i - 1, l);
-                    const double2 den2 = de[in];
-                    const double rn = Rl[in * NR];
+                double2* dp = de + mm;
+                double* rp = Rw + mm * NR;
+#pragma unroll 4
+                for (int i = mm - l; i > 0; --i) {
+                    const double2 den2 = dp[-2];
+                    const double rn = rp[-2 * NR];
                     const double f = s * dei.y, bb = c * dei.y, x = fma(g, g, fma(f, f, 1e-300));
                     const double y = __builtin_amdgcn_rsq(x), xy = x * y, u = fma(-xy, y, 1.0);
                     // third-order step: 23 bits to full precision
@@ -907,21 +927,23 @@ __global__ __launch_bounds__(256) void k_ql(EigExtra ex, int nseeds, const int32
                     double r = xy * cr;
                     s = f * yc;
                     c = g * yc;
-                    xmin = fmin(xmin, x);
-                    if (safe && x < 1e-290) {   // the identity: the matrix splits here
+                    xmin = min(xmin, (unsigned)(__builtin_bit_cast(uint64_t, x) >> 32));
+                    if (SAFE && x < 1e-290) {   // the identity: the matrix splits here
                         r = s = 0.0;
                         c = 1.0;
                     }
                     g = di1 - p;
                     const double rr = fma(c, bb + bb, (dei.x - g) * s);
                     p = s * rr;
-                    de[i + 1] = make_double2(g + p, r);
+                    *dp = make_double2(g + p, r);
                     g = fma(c, rr, -bb);
-                    Rw[(i + 1) * NR] = fma(s, ri, c * hr);
+                    *rp = fma(s, ri, c * hr);
                     hr = fma(c, ri, -(s * hr));
                     di1 = dei.x;
                     dei = den2;
                     ri = rn;
+                    --dp;
+                    rp -= NR;
                 }
                 de[l] = make_double2(di1 - p, g);
                 de[mm].y = 0.0;
@@ -929,8 +951,9 @@ __global__ __launch_bounds__(256) void k_ql(EigExtra ex, int nseeds, const int32
                 wave_sync();
             }
         }
-        if (!(xmin < 1e-290)) break;
-    }
+    };
+    iterate(std::false_type{});
+    if (xmin <= 0x03b8f2b0u) iterate(std::true_type{});   // 1e-290
     if (fail) {
         eig_failed<64>(ex, b, m, nu, rlo, nP, rho, e_seed, n_seed, nu_eff_out, eps_b, w_b, zc);
         return;
@@ -960,8 +983,8 @@ LaunchInfo launch_eig(int nseeds, const int32_t* seeds, int nu, double* h, const
     li.flops = (double)nseeds * ((4.0 / 3.0) * nv * nv * nv + 4.0 * nv * nv * (max_row + 1));
     // Reduction and QL iteration, except where all eigenvectors are wanted (mode 1: one seed), a cap on Jacobi sweeps
     // was asked for, or a row of R outgrows a wavefront or the reduction's LDS.
-    // Measured (ms, Jacobi / this): nu = 30, 256 seeds 0.29 / 0.25; nu = 47, 777 seeds 2.02 / 0.62; nu = 100, 256 seeds
-    // 1.70 / 1.81, 1024 seeds 6.6 / 2.3; nu = 300, 64 seeds 112 / 18. The reduction and iteration are the more accurate
+    // Measured (ms, Jacobi / this): nu = 30, 256 seeds 0.29 / 0.19; nu = 47, 777 seeds 2.02 / 0.50; nu = 100, 256 seeds
+    // 1.71 / 1.39, 1024 seeds 6.6 / 1.9; nu = 300, 64 seeds 112 / 14. The reduction and iteration are the more accurate
     // of the two (rho against LAPACK at nu = 100: 2e-15 against 1.5e-14).
     const size_t big = tri_big_lds(nu, rcols), ql = ql_lds_bytes(nu, rcols + 1);
     if (!ex.jacobi && ex.mode != 1 && rcols + 1 <= 64 && ql <= 160 * 1024 &&
@@ -984,7 +1007,7 @@ LaunchInfo launch_eig(int nseeds, const int32_t* seeds, int nu, double* h, const
         static std::atomic<uint64_t> done{0};
         allow_full_lds((const void*)k_ql, done);
         // four seeds to a workgroup, one on each SIMD, as far as LDS allows: workgroups of one wavefront shared one
-        // SIMD (nu = 100, 1024 seeds: 2.58 -> 1.79 ms, 1.62 with fewer instructions per rotation)
+        // SIMD (nu = 100, 1024 seeds: 2.58 -> 1.79 ms)
         int wv = 4;
         while (wv > 1 && wv * ql > 160 * 1024) wv /= 2;
         hipLaunchKernelGGL(k_ql, dim3((nseeds + wv - 1) / wv), dim3(64 * wv), wv * ql, s, ex, nseeds, seeds, nu, h, nu_eff_blk, Kp, Hrp, Hcol, Hval, SvalH,
@@ -1060,14 +1083,14 @@ __global__ __launch_bounds__(WG) void k_assemble(int nseeds, const int32_t* __re
         }
     }
     __syncthreads();
-    if (tid == 0) {
-        double E = 0.0, N = 0.0;
-        for (int t = 0; t < nP; ++t) {
-            E += rhoL[t] * Hval[rlo + t];
-            N += rhoL[t] * SvalH[rlo + t];
+    if (tid < 64) {   // nP <= 63
+        const bool in = tid < nP;
+        const double r = in ? rhoL[tid] : 0.0;
+        const double E = wave_sum(r * (in ? Hval[rlo + tid] : 0.0)), N = wave_sum(r * (in ? SvalH[rlo + tid] : 0.0));
+        if (tid == 0) {
+            e_seed[b] = E;
+            n_seed[b] = N;
         }
-        e_seed[b] = E;
-        n_seed[b] = N;
     }
 }
 
