@@ -751,6 +751,8 @@ mar_status run_solve_delayed(mar_ctx* c, const int32_t* d_seeds, int64_t n_seeds
     const int64_t M = (c->M + 3) / 4 * 4;
     // H u and S u of the same vector in one pass when H is BSR (S on H's pattern)
     const bool dual = c->H.bsr && c->SH.nnz == c->H.nnz && B0 >= VEC;
+    // the same in general CSR storage
+    const bool pair = dual || (!c->H.bsr && !c->S.bsr && c->S.nnz == c->H.nnz && B0 >= VEC);
     // Support tracking: the kernels of a step skip the row tiles on which the block's vectors are exactly
     // zero (farther from every seed of the block than the step in hops of H's pattern).
     const bool sparse = dual && c->tune.support_off == 0;
@@ -1045,7 +1047,7 @@ mar_status run_solve_delayed(mar_ctx* c, const int32_t* d_seeds, int64_t n_seeds
             launch(c, s, P_SUPPORT, [&] { return mar::launch_projr_plan(scnt, sDl, 0, nu, kg, target, pstride, splan, s); });
         }
         // at steps n >= 1 the dual pass also gives the norms of slab n (the unnormalized residual of step n - 1)
-        if (!dual) launch(c, s, P_SPMM, [&] { return mar::launch_spmm<T>(B, c->S, K, ZT, nullptr, 0, 0, s); });
+        if (!pair) launch(c, s, P_SPMM, [&] { return mar::launch_spmm<T>(B, c->S, K, ZT, nullptr, 0, 0, s); });
         for (int n = 0; n < nu; ++n) {
             T* Kn = K + (size_t)n * slab_el;
             const int nk = n + 1;
@@ -1064,6 +1066,13 @@ mar_status run_solve_delayed(mar_ctx* c, const int32_t* d_seeds, int64_t n_seeds
                     return li;
                 });
                 tag(rec, SP_FRAC, n + 1, bi, (double)ntiles);
+            } else if (pair) {
+                launch(c, s, n == 0 ? P_SPMM : P_SPMM_DOT, [&] {
+                    LaunchInfo li = mar::launch_spmm2<T>(B, c->H, c->S, Kn, Y, ZT, n == 0 ? nullptr : npart,
+                                                         n == 0 ? 0 : 2, np_cap, s);
+                    swgs = li.wgs;
+                    return li;
+                });
             } else if (n >= 1) {
                 launch(c, s, P_SPMM_DOT, [&] {
                     LaunchInfo li = mar::launch_spmm<T>(B, c->S, Kn, ZT, npart, 2, np_cap, s);
@@ -1071,7 +1080,7 @@ mar_status run_solve_delayed(mar_ctx* c, const int32_t* d_seeds, int64_t n_seeds
                     return li;
                 });
             }
-            if (!dual) launch(c, s, P_SPMM, [&] { return mar::launch_spmm<T>(B, c->H, Kn, Y, nullptr, 0, 0, s); });
+            if (!pair) launch(c, s, P_SPMM, [&] { return mar::launch_spmm<T>(B, c->H, Kn, Y, nullptr, 0, 0, s); });
             if (sparse) {
                 const bool rec = launch(c, s, P_SPMM, [&] {
                     return local ? mar::launch_spmm_list<T>(B, c->SH, Y, SY, slist, scnt, n, lmask, mW, kListWgs, s)

@@ -180,8 +180,8 @@ LaunchInfo launch_es_pdot(int B, const T* K, int64_t stride, int64_t M, int64_t 
 LaunchInfo launch_fermi_search(int64_t nseeds, int nu, const int32_t* nu_eff, const double* eps, const double* w,
                                double n_target, double kT, double* work, double* mu, double* mu_out, hipStream_t s);
 
-// Y = H X and Z = S X in one pass (SH: S's values on H's BSR pattern); refused (wgs = -1) unless H is BSR
-// and B >= the vector width. ndot as in launch_spmm, against Z.
+// Y = H X and Z = S X in one pass (SH: S's values on H's pattern, in the same storage; general CSR takes neither the
+// support's arguments nor ndot = 1); refused (wgs = -1) unless B >= the vector width. ndot as in launch_spmm, against Z.
 template <typename T>
 LaunchInfo launch_spmm2(int B, const DevMat& H, const DevMat& SH, const T* X, T* Y, T* Z, double* part, int ndot,
                         int64_t part_cap, hipStream_t s, const int32_t* tdist = nullptr, int lim = 0,

@@ -457,7 +457,10 @@ __global__ __launch_bounds__(WG) void k_spmm_list(int64_t nbrow, const int32_t* 
     }
 }
 
-// Y = A X with A in CSR (patterns without 4x4 block structure). Thread = (row, seed group).
+// Y = A X with A in CSR (patterns without 4x4 block structure). Thread = (row, seed group). What bounds it: the gather of
+// the rows of X from L2 (18 rows of 1 KB for one written, 8189 rows, FP64, 128 seeds: 10.7 us, 14 TB/s); the entries are
+// scalars where a row is a wavefront, and eight rows are in flight (one at a time took 15.2 us). H and S of one pattern
+// share the gather (k_spmm2_csr): 18.5 us with the norms for both, 10.7 + 12.5 apart.
 template <typename T, int B, int NDOT>
 __global__ __launch_bounds__(WG) void k_spmm_csr(int64_t nrow, const int32_t* __restrict__ rp,
                                                  const int32_t* __restrict__ col, const T* __restrict__ val,
@@ -468,22 +471,36 @@ __global__ __launch_bounds__(WG) void k_spmm_csr(int64_t nrow, const int32_t* __
     using VT = typename Vec16<T>::type;
     const int64_t bid = xcd_remap(blockIdx.x, gridDim.x);
     const int64_t g = bid * WG + threadIdx.x;
-    const int64_t i0 = g / P;
+    constexpr int CH = 8;   // entries of a row in flight
     const int grp = threadIdx.x % P;
     const int s0 = (B < VEC) ? 0 : grp * VEC;
     T acc[SW];
 #pragma unroll
     for (int i = 0; i < SW; ++i) acc[i] = (T)0;
+    int64_t i0 = g / P;
+    if constexpr (P == 64) i0 = __builtin_amdgcn_readfirstlane((int)i0);   // one row per wavefront: its entries are scalars
     if (i0 < nrow) {
-        for (int t = rp[i0]; t < rp[i0 + 1]; ++t) {
-            const int64_t c = col[t];
-            const T a = val[t];
-            if constexpr (B >= VEC) {
-                T u[VEC];
-                unpack(reinterpret_cast<const VT*>(X)[(c * B + s0) / VEC], u);
+        const int hi = rp[i0 + 1];
+        if constexpr (B >= VEC) {
+            for (int t = rp[i0]; t < hi; t += CH) {
+                T a[CH], u[CH][VEC];
 #pragma unroll
-                for (int i = 0; i < SW; ++i) acc[i] = fma(a, u[i], acc[i]);
-            } else {
+                for (int q = 0; q < CH; ++q) {
+                    const int tt = t + q < hi ? t + q : hi - 1;
+                    a[q] = val[tt];
+                    unpack(reinterpret_cast<const VT*>(X)[((int64_t)col[tt] * B + s0) / VEC], u[q]);
+                }
+#pragma unroll
+                for (int q = 0; q < CH; ++q)
+                    if (t + q < hi) {
+#pragma unroll
+                        for (int i = 0; i < SW; ++i) acc[i] = fma(a[q], u[q][i], acc[i]);
+                    }
+            }
+        } else {
+            for (int t = rp[i0]; t < hi; ++t) {
+                const int64_t c = col[t];
+                const T a = val[t];
 #pragma unroll
                 for (int i = 0; i < SW; ++i) acc[i] = fma(a, X[c * B + i], acc[i]);
             }
@@ -505,6 +522,63 @@ __global__ __launch_bounds__(WG) void k_spmm_csr(int64_t nrow, const int32_t* __
         }
         __shared__ double lds[SeedReduce<P, SW, NDOT>::LDS];
         wg_seed_reduce<P, SW, NDOT>(d, lds, [&](int v, int b, double s) { part[(bid * NDOT + v) * B + b] = s; });
+    }
+}
+
+// Y = H X and Z = S X in one pass over the rows of X, for an S with H's pattern. NDOT = 2: also the partial sums of x.z
+// and x.x.
+template <typename T, int B, int NDOT>
+__global__ __launch_bounds__(WG) void k_spmm2_csr(int64_t nrow, const int32_t* __restrict__ rp,
+                                                  const int32_t* __restrict__ col, const T* __restrict__ hv,
+                                                  const T* __restrict__ sv, const T* __restrict__ X, T* __restrict__ Y,
+                                                  T* __restrict__ Z, double* __restrict__ part) {
+    using SM = SeedMap<T, B>;
+    constexpr int VEC = SM::VEC, P = SM::P, CH = 8;
+    using VT = typename Vec16<T>::type;
+    const int64_t bid = xcd_remap(blockIdx.x, gridDim.x);
+    int64_t i0 = (bid * WG + threadIdx.x) / P;
+    if constexpr (P == 64) i0 = __builtin_amdgcn_readfirstlane((int)i0);
+    const int s0 = threadIdx.x % P * VEC;
+    T ah[VEC], as[VEC];
+#pragma unroll
+    for (int i = 0; i < VEC; ++i) ah[i] = as[i] = (T)0;
+    if (i0 < nrow) {
+        const int hi = rp[i0 + 1];
+        for (int t = rp[i0]; t < hi; t += CH) {
+            T h[CH], o[CH], u[CH][VEC];
+#pragma unroll
+            for (int q = 0; q < CH; ++q) {
+                const int tt = t + q < hi ? t + q : hi - 1;
+                h[q] = hv[tt];
+                o[q] = sv[tt];
+                unpack(reinterpret_cast<const VT*>(X)[((int64_t)col[tt] * B + s0) / VEC], u[q]);
+            }
+#pragma unroll
+            for (int q = 0; q < CH; ++q)
+                if (t + q < hi) {
+#pragma unroll
+                    for (int i = 0; i < VEC; ++i) {
+                        ah[i] = fma(h[q], u[q][i], ah[i]);
+                        as[i] = fma(o[q], u[q][i], as[i]);
+                    }
+                }
+        }
+        reinterpret_cast<VT*>(Y)[(i0 * B + s0) / VEC] = pack(ah);
+        reinterpret_cast<VT*>(Z)[(i0 * B + s0) / VEC] = pack(as);
+    }
+    if constexpr (NDOT > 0) {
+        static_assert(NDOT == 2, "x.z and x.x");
+        T x[VEC];
+        unpack(reinterpret_cast<const VT*>(X)[((i0 < nrow ? i0 : 0) * B + s0) / VEC], x);
+        double d[2][VEC];
+#pragma unroll
+        for (int i = 0; i < VEC; ++i) {
+            const double xv = i0 < nrow ? (double)x[i] : 0.0;
+            d[0][i] = xv * (double)as[i];
+            d[1][i] = xv * xv;
+        }
+        __shared__ double lds[SeedReduce<P, VEC, 2>::LDS];
+        wg_seed_reduce<P, VEC, 2>(d, lds, [&](int v, int b, double s) { part[(bid * 2 + v) * B + b] = s; });
     }
 }
 
@@ -1193,7 +1267,8 @@ LaunchInfo launch_spmm2<MAR_T>(int B, const DevMat& H, const DevMat& SH, const M
                                int lim, const uint32_t* mask, int W, const int32_t* rdist) {
     constexpr int VEC = Vec16<MAR_T>::n;
     LaunchInfo li;
-    if (!H.bsr || B < VEC || SH.nnz != H.nnz) {
+    if (B < VEC || SH.nnz != H.nnz || SH.bsr != H.bsr ||
+        (!H.bsr && (ndot == 1 || tdist != nullptr || mask != nullptr || rdist != nullptr))) {
         li.wgs = -1;
         return li;
     }
@@ -1206,6 +1281,18 @@ LaunchInfo launch_spmm2<MAR_T>(int B, const DevMat& H, const DevMat& SH, const M
     const bool f32 = std::is_same<MAR_T, float>::value;
     const MAR_T* hv = f32 ? (const MAR_T*)H.v32 : (const MAR_T*)H.v64;
     const MAR_T* sv = f32 ? (const MAR_T*)SH.v32 : (const MAR_T*)SH.v64;
+    if (!H.bsr) {
+#define MAR_SPMM2C(ND) \
+    MAR_DISPATCH_B(B, if constexpr (BB >= VEC) hipLaunchKernelGGL((k_spmm2_csr<MAR_T, BB, ND>), dim3((unsigned)wgs), dim3(WG), 0, s, H.n, H.ptr, H.idx, hv, sv, X, Y, Z, part))
+        if (ndot == 2) { MAR_SPMM2C(2); }
+        else { MAR_SPMM2C(0); }
+#undef MAR_SPMM2C
+        li.wgs = wgs;
+        li.bytes = (double)H.nnz * (2.0 * sizeof(MAR_T) + 4.0) + (double)(H.n + 1) * 4.0 +
+                   3.0 * (double)H.n * B * sizeof(MAR_T);
+        li.flops = 4.0 * (double)H.nnz * B;
+        return li;
+    }
     const int64_t chunk = spmm_chunk(H.span, WG / P);
     const int64_t grid = chunk > 0 ? (wgs + 8 * chunk - 1) / (8 * chunk) * (8 * chunk) : wgs;
 #define MAR_SPMM2(ND) \
