@@ -306,7 +306,7 @@ struct SeedGeom {
     bool ok;
     int64_t nbrow, sstride;
     int nbcap, hs, threads, grid;
-    int oU, oD, oC, oList, oCol;
+    int oU, oP, oD, oC, oList, oCol;
     size_t kbytes, lds;
 };
 SeedGeom seed_geometry(int64_t nbrow, int64_t nnzb, int blocks_per_row, int hops, int64_t nbcap, int nu, size_t elem,

@@ -20,7 +20,10 @@
 // last-level-cache reads of that part. Measured, whole Krylov phase: 0.14 ms
 // for 256 seeds of the 256-row cell (FP32, nu = 30; the blocks' launches took
 // 1.3 ms), 5.7 ms for 1024 seeds in regions of 6 hops (about 730 rows, FP32,
-// nu = 100: 48 of 100 basis vectors in LDS; the blocks 78 ms).
+// nu = 100: 48 of 100 basis vectors in LDS; the blocks 78 ms), 8.3 ms for
+// 2048 seeds of a 2048-row cell (FP64, nu = 30: 6 of 30 vectors in LDS; 9.5 ms
+// with 4 in LDS and the wavefronts of a projection split over groups of
+// vectors only, half of them idle).
 // Two wavefronts per SIMD with 256 registers each: four with 128 spilled and
 // ran 2.5 times slower. Between most phases only LDS is ordered (lds_barrier):
 // a full barrier waits for the stores and the requested matrix values as well
@@ -198,13 +201,15 @@ __global__ __launch_bounds__(SEED_WG) void k_seed(SeedArgs<T> a) {
     T* z = y + 4 * g.nbcap + 4;
     double* d0 = reinterpret_cast<double*>(sm + g.oD);      // K^T w, then c2
     double* d1 = d0 + a.nu + 1;                             // c1
+    double* cp = reinterpret_cast<double*>(sm + g.oP);      // sums of the chunks of rows (more than one)
     T* cT = reinterpret_cast<T*>(sm + g.oC);                // update coefficients in the basis precision
     int* list = reinterpret_cast<int*>(sm + g.oList);
     int* gptr = list + g.nbcap;
     int* lptr = gptr + g.nbcap;
     int* misc = lptr + g.nbcap + 1;
     uint16_t* lcol = reinterpret_cast<uint16_t*>(sm + g.oCol);
-    const int tid = threadIdx.x, nt = blockDim.x, lane = tid & 63, wave = tid >> 6, nw = nt >> 6;
+    const int tid = threadIdx.x, nt = blockDim.x, lane = tid & 63, nw = nt >> 6;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int nu = a.nu;
     for (int b = blockIdx.x; b < a.ns; b += gridDim.x) {
         const int j = a.seeds[b];
@@ -219,7 +224,7 @@ __global__ __launch_bounds__(SEED_WG) void k_seed(SeedArgs<T> a) {
         // basis vectors of this seed's nr rows: the first nl in LDS, vector k >= nl at Kg + k nr
         const int nr = 4 * nb, nvec = nr / VEC;
         int nl = (int)(g.kbytes / ((size_t)nr * sizeof(T)));
-        nl = nl >= nu ? nu : nl / SEED_G * SEED_G;
+        nl = min(nl, nu);
         T* kept = a.keep != nullptr ? a.keep + (int64_t)b * nu * nr : nullptr;
         T* Kg = kept ? kept : a.scratch + (int64_t)blockIdx.x * g.sstride - (int64_t)nl * nr;
         if (tid == 0) {   // local block row of the seed: the list is ascending
@@ -309,16 +314,25 @@ __global__ __launch_bounds__(SEED_WG) void k_seed(SeedArgs<T> a) {
                 out[i] = s;
             }
         };
-        // o0[k] = u_k . x0 (and o1[k] = u_k . x1) for k < nk: wavefronts over groups of basis vectors, lanes over
-        // rows with their x in registers; sums of a lane in T, across lanes in FP64. The last of them, rounded, are
-        // the update coefficients cT.
+        // o0[k] = u_k . x0 (and o1[k] = u_k . x1) for k < nk: wavefronts over pairs of a group of basis vectors (in LDS,
+        // then in memory) and a chunk of the rows, lanes over the rows with their x in registers; sums of a lane in T,
+        // across lanes in FP64. Sums of several chunks meet in cp, one barrier later. (Wavefronts over the groups alone
+        // left half of them idle at 2048 rows and nu = 30, where the chunks are four.) The last sums, rounded, are the
+        // update coefficients cT.
+        const int nlv = (nvec + 63) / 64, nch = (nlv + SEED_NF - 1) / SEED_NF, cf = (nlv + nch - 1) / nch;   // equal chunks
+        auto groups = [&](int nk) {
+            return (min(nk, nl) + SEED_G - 1) / SEED_G + (nk > nl ? (nk - nl + SEED_G - 1) / SEED_G : 0);
+        };
         auto dots = [&](auto two, const T* x0, const T* x1, int nk, double* o0, double* o1) {
             constexpr int NR = decltype(two)::value ? 2 : 1;
             constexpr int V = SEED_G * NR;
-            for (int c0 = 0; c0 < nvec; c0 += 64 * SEED_NF) {
+            const int kl = min(nk, nl), gl = (kl + SEED_G - 1) / SEED_G, ng = groups(nk);
+            for (int ch = 0; ch < nch; ++ch) {
+                const int c0 = ch * 64 * cf, first = (wave - ch * ng) & (nw - 1);
+                if (first >= ng) continue;
                 T f0[SEED_NF][VEC], f1[SEED_NF][VEC];
                 int vs[SEED_NF];
-                const int nf = min(SEED_NF, (nvec - c0 + 63) / 64);
+                const int nf = min(cf, nlv - ch * cf);
 #pragma unroll
                 for (int f = 0; f < SEED_NF; ++f) {
                     const int v = c0 + f * 64 + lane;
@@ -332,7 +346,7 @@ __global__ __launch_bounds__(SEED_WG) void k_seed(SeedArgs<T> a) {
                         if constexpr (NR == 2) f1[f][i] = in ? f1[f][i] : (T)0;
                     }
                 }
-                auto group = [&](const T* base, int kb) {
+                auto group = [&](const T* base, int kb, int kz) {
                     T acc[V];
 #pragma unroll
                     for (int i = 0; i < V; ++i) acc[i] = (T)0;
@@ -342,7 +356,7 @@ __global__ __launch_bounds__(SEED_WG) void k_seed(SeedArgs<T> a) {
                         if (f >= nf) break;
 #pragma unroll
                         for (int q = 0; q < SEED_G; ++q) {
-                            const int k = kb + q < nk ? kb + q : nk - 1;
+                            const int k = kb + q < kz ? kb + q : kz - 1;
                             unpack(reinterpret_cast<const VT*>(base + (int64_t)k * nr)[vs[f]], k4[q]);
                         }
 #pragma unroll
@@ -359,16 +373,31 @@ __global__ __launch_bounds__(SEED_WG) void k_seed(SeedArgs<T> a) {
                     wave_sum_multi<V>(s, lane);
                     constexpr int LPV = 64 / V;
                     const int idx = lane / LPV, k = kb + idx / NR;
-                    if (lane % LPV == 0 && k < nk) {
-                        double* o = NR == 2 && idx % NR == 1 ? o1 : o0;
-                        const double t = c0 == 0 ? s[0] : o[k] + s[0];
-                        o[k] = t;
-                        if (idx % NR == NR - 1) cT[k] = (T)t;
+                    if (lane % LPV == 0 && k < kz) {
+                        const bool second = NR == 2 && idx % NR == 1;
+                        if (nch > 1) {
+                            cp[(2 * ch + (second ? 1 : 0)) * nu + k] = s[0];
+                        } else {
+                            (second ? o1 : o0)[k] = s[0];
+                            if (idx % NR == NR - 1) cT[k] = (T)s[0];
+                        }
                     }
                 };
-                for (int kb = wave * SEED_G; kb < nk; kb += nw * SEED_G) {
-                    if (kb < nl) group(Kl, kb);   // nl is a multiple of the group, or every vector is in LDS
-                    else group(Kg, kb);
+                int g = first;
+                for (; g < gl; g += nw) group(Kl, g * SEED_G, kl);
+                for (; g < ng; g += nw) group(Kg, nl + (g - gl) * SEED_G, nk);
+            }
+            if (nch > 1) {
+                lds_barrier();
+                for (int k = tid; k < nk; k += nt) {
+                    double t0 = 0.0, t1 = 0.0;
+                    for (int ch = 0; ch < nch; ++ch) {
+                        t0 += cp[2 * ch * nu + k];
+                        if constexpr (NR == 2) t1 += cp[(2 * ch + 1) * nu + k];
+                    }
+                    o0[k] = t0;
+                    if constexpr (NR == 2) o1[k] = t1;
+                    cT[k] = (T)(NR == 2 ? t1 : t0);
                 }
             }
         };
@@ -455,7 +484,7 @@ __global__ __launch_bounds__(SEED_WG) void k_seed(SeedArgs<T> a) {
             lds_barrier();
             product(a.sv, y, z);
             lds_barrier();
-            if (wave == (nk + SEED_G - 1) / SEED_G % nw) {   // the first wavefront without a group
+            if (wave == (groups(nk) * nch & (nw - 1))) {   // the next wavefront after the groups'
                 const double s = self_dot();
                 if (lane == 0) d1[nu] = s;
             }
@@ -552,6 +581,8 @@ SeedGeom seed_geometry(int64_t nbrow, int64_t nnzb, int blocks_per_row, int hops
         return (int)o;
     };
     const int oU = take((size_t)3 * (nr + 4) * elem);
+    const int64_t nch = (nr * (int64_t)elem / 16 + 64 * SEED_NF - 1) / (64 * SEED_NF);
+    const int oP = take(nch > 1 ? (size_t)nch * 2 * nu * 8 : 0);
     const int oD = take((size_t)2 * (nu + 1) * 8), oC = take((size_t)nu * elem);
     const int oL = take((size_t)(3 * nbcap + 1 + 8) * 4), oCol = take((size_t)ecap * 2);
     const size_t fixed = off, slab = (size_t)nr * elem;
@@ -564,6 +595,7 @@ SeedGeom seed_geometry(int64_t nbrow, int64_t nnzb, int blocks_per_row, int hops
         g.threads = SEED_WG / wgs;
         g.kbytes = std::min(kb, (total - fixed) & ~(size_t)15);
         g.oU = (int)g.kbytes + oU;
+        g.oP = (int)g.kbytes + oP;
         g.oD = (int)g.kbytes + oD;
         g.oC = (int)g.kbytes + oC;
         g.oList = (int)g.kbytes + oL;
@@ -571,8 +603,8 @@ SeedGeom seed_geometry(int64_t nbrow, int64_t nnzb, int blocks_per_row, int hops
         g.lds = g.kbytes + fixed;
         g.grid = (int)std::min<int64_t>(ns, (int64_t)n_cu * wgs);
         // the kernel keeps as many vectors of its seed's own row count in LDS; the largest set leaves the most out
-        // (a smaller one at most as many elements, rounding to groups included)
-        const int64_t nl = g.kbytes / slab >= (size_t)nu ? nu : (int64_t)(g.kbytes / slab) / SEED_G * SEED_G;
+        // (a smaller one at most as many elements)
+        const int64_t nl = std::min<int64_t>(nu, (int64_t)(g.kbytes / slab));
         g.sstride = ((int64_t)nu - nl) * nr;
         g.ok = true;
         return g;
