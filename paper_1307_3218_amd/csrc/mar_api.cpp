@@ -472,6 +472,11 @@ bool use_seedwise(const mar_ctx* c, int nu, mar_precision prec, int64_t ns) {
     if (ns < 1 || !c->H.bsr || c->SH.nnz != c->H.nnz) return false;
     const mar::SeedGeom g = seed_geom(c, nu, prec, ns);
     if (!g.ok) return false;
+    // FP32 regions of fewer than 4 nu rows (the largest) stay with the blocks: there the last vectors are what rounding
+    // leaves of a nearly exhausted Krylov space, and any other order of the sums moves single entries of rho (mixed lattice,
+    // 3 hops, nu = 54: by 3e-3 of their root mean square, with errors against 64 bits of 1e-5 and 2e-6; 9.3 ms in blocks,
+    // 0.9 with a workgroup per seed). At up to a quarter of the rows they move by 1e-4 at most.
+    if (c->loc >= 0 && prec == MAR_FP32 && nu > c->loc_blocks) return false;
     // Where the line lies (ms per solve, one workgroup per seed / blocks, diamond cells and mixed-lattice regions):
     //  * a few hundred to 2048 rows: FP32 nu = 30, 256 seeds: 0.42 / 1.60 at 256 rows, 0.84 / 2.03 at 2048; FP64
     //    nu = 100, 1024 seeds: 24.6 / 88.8 at 1024 rows, 56 / 96 at 2048. Always taken up to 3072 rows.
@@ -1168,6 +1173,7 @@ mar_status run_seedwise(mar_ctx* c, const mar_request& r, hipStream_t s) {
     const int nu = r.nu;
     const int64_t n_seeds = r.n_seeds;
     const double tau = sizeof(T) == 4 ? 1e-5 : 1e-12;
+    // the FP32 form sums in FP64 at large subspace dimensions
     const bool acc64 = sizeof(T) == 4 && nu > mar::kUpdAcc64Nu;
     const mar::SeedGeom g = seed_geom(c, nu, r.prec, n_seeds);
     const size_t per = (size_t)nu * (nu + std::max(1, c->max_row)) * 8;

@@ -30,6 +30,7 @@
 // and cost 1000 cycles a phase.
 #include <algorithm>
 #include <atomic>
+#include <cmath>
 #include <type_traits>
 
 #include "mar_device.h"
@@ -347,9 +348,9 @@ __global__ __launch_bounds__(SEED_WG) void k_seed(SeedArgs<T> a) {
                     }
                 }
                 auto group = [&](const T* base, int kb, int kz) {
-                    T acc[V];
+                    AT acc[V];
 #pragma unroll
-                    for (int i = 0; i < V; ++i) acc[i] = (T)0;
+                    for (int i = 0; i < V; ++i) acc[i] = (AT)0;
                     T k4[SEED_G][VEC];
 #pragma unroll
                     for (int f = 0; f < SEED_NF; ++f) {
@@ -363,8 +364,9 @@ __global__ __launch_bounds__(SEED_WG) void k_seed(SeedArgs<T> a) {
                         for (int q = 0; q < SEED_G; ++q)
 #pragma unroll
                             for (int i = 0; i < VEC; ++i) {
-                                acc[q * NR] = fma(k4[q][i], f0[f][i], acc[q * NR]);
-                                if constexpr (NR == 2) acc[q * NR + 1] = fma(k4[q][i], f1[f][i], acc[q * NR + 1]);
+                                acc[q * NR] = fma((AT)k4[q][i], (AT)f0[f][i], acc[q * NR]);
+                                if constexpr (NR == 2) acc[q * NR + 1] =
+                                    fma((AT)k4[q][i], (AT)f1[f][i], acc[q * NR + 1]);
                             }
                     }
                     double s[V];
@@ -635,9 +637,11 @@ static LaunchInfo launch_seed_t(const SeedGeom& g, const DevMat& H, const DevMat
         hipLaunchKernelGGL((k_seed<T, false>), dim3(g.grid), dim3(g.threads), g.lds, s, a);
     }
     li.wgs = g.grid;
-    // per seed: four sweeps over the basis vectors so far, on the rows of its region (at most the listed ones)
+    // per seed: four sweeps over the basis vectors so far outside LDS, on the rows of its region (at most the listed
+    // ones), and the values of three products
     const double rows = 4.0 * g.nbcap, el = sizeof(T);
-    li.bytes = (double)ns * rows * el * (2.0 * nu * (nu + 1.0) + 10.0 * nu);
+    const double out = std::max<double>(0.0, nu - std::floor((double)g.kbytes / (rows * el)));
+    li.bytes = (double)ns * rows * el * (2.0 * out * (out + 1.0) + out + 12.0 * nu * (double)H.nnz / (double)H.n);
     li.flops = (double)ns * rows * (5.0 * nu * (nu + 1.0) + 6.0 * nu * 4.0 * ((double)H.nnz / (double)H.n));
     return li;
 }

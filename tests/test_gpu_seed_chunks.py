@@ -28,3 +28,18 @@ def test_chunks(cells, nu, prec):
     tol = 1e-9 if prec == "fp64" else 2e-5
     for x, y in ((a.rho, b.rho), (a.n_seed, b.n_seed), (a.e_seed, b.e_seed)):
         assert np.abs(x - y).max() <= tol * np.abs(y).max()
+
+
+def test_nearly_exhausted_fp32_regions_run_in_blocks():
+    """Regions of fewer than 4 nu rows: the route of the blocks' kernels, bit for bit."""
+    s = lattice.generate(6, 5, 5, mixed=True, seed=8, check_spd=False)
+    seeds = lattice.sample_seeds(s.M, 50, seed=4)
+    ctx = mar.Context(s.H, s.S)
+    try:
+        ctx.set_local_region(3)
+        a = ctx.solve(seeds, 54, -0.4, 0.1, precision="fp32")
+        ctx.set_tuning(upd_q=4)   # the blocks' kernels
+        b = ctx.solve(seeds, 54, -0.4, 0.1, precision="fp32")
+    finally:
+        ctx.close()
+    assert np.array_equal(a.rho, b.rho) and np.array_equal(a.nu_eff, b.nu_eff)
