@@ -589,14 +589,19 @@ __global__ __launch_bounds__(TRI_TH, RI <= 4 ? 4 : 2) void k_tri(EigExtra ex, co
                 }
             }
         __syncthreads();
-        double n2 = 0.0;                       // every wavefront the same
-        for (int i = lane; i < NX; i += 64) n2 = fma(x[i], x[i], n2);
-        n2 = wave_sum(n2);
+        double sg = 0.0;                       // the entries below the subdiagonal; every wavefront the same
+        for (int i = lane; i < NX; i += 64) {
+            const double xi = i == k + 1 ? 0.0 : x[i];
+            sg = fma(xi, xi, sg);
+        }
+        sg = wave_sum(sg);
         const double al = x[k + 1];
         double beta = al, tau = 0.0, v1 = 0.0;
-        const bool refl = n2 > 1e-290 && n2 > al * al;   // else the column is in form (to 1e-145 of A's scale)
+        // else the column is in form (to 1e-145 of A's scale). Not by comparing n2 with al^2: entries up to 1e-8 |al|,
+        // which a small overlap leaves in every column, are below n2's last place and would be dropped
+        const bool refl = sg > 1e-290;
         if (refl) {
-            const double r = n2 * rsqrt_nr(n2);
+            const double n2 = fma(al, al, sg), r = n2 * rsqrt_nr(n2);
             beta = -copysign(r, al);
             v1 = al - beta;
             tau = recip(fma(r, fabs(al), n2));
