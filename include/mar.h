@@ -360,7 +360,12 @@ int32_t mar_flip_colours(mar_ctx* ctx);
  * the order of partial sums). hops < 0 (the default) restores the full system.
  * Needs H with 4x4 block structure (MAR_ERR_ARG here otherwise); solves then
  * need the batched delayed form with blocks of at least 4 (FP32) / 2 (FP64)
- * seeds, and the eigen-state entry points refuse a local region (MAR_ERR_ARG). */
+ * seeds, and the eigen-state entry points refuse a local region (MAR_ERR_ARG).
+ * The call sets host state only and may be made while a stream captures. The
+ * first batched solve in regions, with a tuning that asks for nothing of the
+ * blocks, measures the sizes of the regions (for up to 64 hops at once) to choose
+ * between blocks and one workgroup per seed: a kernel, and the call waits for
+ * it. Captured before that, a solve runs in blocks. */
 mar_status mar_set_local_region(mar_ctx* ctx, int32_t hops);
 /* Current local-region hops of ctx (-1: the full system, or ctx NULL). */
 int32_t mar_local_region(const mar_ctx* ctx);

@@ -107,8 +107,9 @@ struct mar_ctx {
 
     mar_tuning tune{};
     int32_t loc = -1;             // local-region hops of later solves (< 0: the full system)
-    int32_t loc_blocks = 0;       // block rows of the largest such region (0: not known, or too many for k_seed)
-    int32_t* d_loc = nullptr;     // device word for that count
+    std::vector<int32_t> reg;     // block rows of the largest region by hops, as far as measured (more than
+                                  // SEED_MAX_BLOCKS: too many for k_seed)
+    int32_t* d_reg = nullptr;     // [SEED_MAX_BLOCKS + 1] the same on the device
     char* ws = nullptr;
     size_t ws_bytes = 0;
     char* ext_ws = nullptr;       // a caller's workspace for the current solve (nothing is allocated then)
@@ -455,20 +456,48 @@ struct Plan {
     bool seedwise = false;   // one workgroup per seed (small regions and cells) instead of seed blocks
 };
 
+// Block rows of the largest local region of c's hops: 0 while they are not measured.
+int32_t region_blocks(const mar_ctx* c) {
+    if (c->reg.empty()) return 0;
+    const size_t h = std::min<size_t>(c->loc, mar::SEED_MAX_BLOCKS);
+    if (h < c->reg.size()) return c->reg[h];
+    return c->reg.back() > mar::SEED_MAX_BLOCKS ? c->reg.back() : 0;   // (the sizes do not fall with the hops)
+}
+
 // The launch shape of the one-workgroup-per-seed form.
 mar::SeedGeom seed_geom(const mar_ctx* c, int nu, mar_precision prec, int64_t ns) {
     const size_t elem = prec == MAR_FP32 ? 4 : 8;
-    return mar::seed_geometry(c->H.n, c->H.nnz, (c->max_row + 3) / 4, c->loc, c->loc >= 0 ? c->loc_blocks : c->H.n, nu,
+    return mar::seed_geometry(c->H.n, c->H.nnz, (c->max_row + 3) / 4, c->loc, c->loc >= 0 ? region_blocks(c) : c->H.n, nu,
                               elem, ns, c->n_cu);
+}
+
+// A tuning of the blocks' kernels asks for the blocks.
+bool tuned_for_blocks(const mar_tuning& t) {
+    return t.seed_block || t.schedule != MAR_SCHED_AUTO || t.proj_wgs || t.slab_pad_kb || t.proj_variant || t.upd_q ||
+           t.support_off || t.two_streams == 1;
+}
+
+// Measures the sizes of the local regions that a solve on stream s is about to run in, if they are not known and decide
+// its route: a kernel and a wait, once per context (1.9 ms for 131072 rows, 16 ms for 1048576). Under capture nothing may
+// wait: the solve then runs in seed blocks, which need no sizes.
+mar_status measure_regions(mar_ctx* c, mar_form form, hipStream_t s) {
+    if (c->loc < 0 || form != MAR_FORM_BATCHED || tuned_for_blocks(c->tune) || region_blocks(c) > 0) return MAR_OK;
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) return MAR_OK;
+    constexpr int kDepth = 64;   // deeper than asked for: other hops are known then, also under capture
+    const int depth = std::min(std::max<int>(c->loc, kDepth), mar::SEED_MAX_BLOCKS);
+    std::vector<int32_t> n(depth + 1);
+    mar::launch_region_sizes(c->H.n, c->H.ptr, c->H.idx, depth, mar::SEED_MAX_BLOCKS, c->d_reg, c->stream2);
+    HIP_OR(c, hipGetLastError());
+    HIP_OR(c, hipMemcpyAsync(n.data(), c->d_reg, n.size() * 4, hipMemcpyDeviceToHost, c->stream2));
+    HIP_OR(c, hipStreamSynchronize(c->stream2));
+    c->reg = std::move(n);
+    return MAR_OK;
 }
 
 // Whether a batched solve runs one workgroup per seed.
 bool use_seedwise(const mar_ctx* c, int nu, mar_precision prec, int64_t ns) {
-    const mar_tuning& t = c->tune;
-    // a tuning of the blocks' kernels asks for the blocks
-    if (t.seed_block || t.schedule != MAR_SCHED_AUTO || t.proj_wgs || t.slab_pad_kb || t.proj_variant || t.upd_q ||
-        t.support_off || t.two_streams == 1)
-        return false;
+    if (tuned_for_blocks(c->tune)) return false;
     if (ns < 1 || !c->H.bsr || c->SH.nnz != c->H.nnz) return false;
     const mar::SeedGeom g = seed_geom(c, nu, prec, ns);
     if (!g.ok) return false;
@@ -476,7 +505,7 @@ bool use_seedwise(const mar_ctx* c, int nu, mar_precision prec, int64_t ns) {
     // leaves of a nearly exhausted Krylov space, and any other order of the sums moves single entries of rho (mixed lattice,
     // 3 hops, nu = 54: by 3e-3 of their root mean square, with errors against 64 bits of 1e-5 and 2e-6; 9.3 ms in blocks,
     // 0.9 with a workgroup per seed). At up to a quarter of the rows they move by 1e-4 at most.
-    if (c->loc >= 0 && prec == MAR_FP32 && nu > c->loc_blocks) return false;
+    if (c->loc >= 0 && prec == MAR_FP32 && nu > region_blocks(c)) return false;
     // Where the line lies (ms per solve, one workgroup per seed / blocks, diamond cells and mixed-lattice regions):
     //  * a few hundred to 2048 rows: FP32 nu = 30, 256 seeds: 0.42 / 1.60 at 256 rows, 0.84 / 2.03 at 2048; FP64
     //    nu = 100, 1024 seeds: 24.6 / 88.8 at 1024 rows, 56 / 96 at 2048. Always taken up to 3072 rows.
@@ -1468,7 +1497,7 @@ mar_status mar_create(int64_t M, const int64_t* H_rowptr, const int32_t* H_col, 
     if ((st = upload(c, &c->Hval, H_val, (size_t)c->nnzH)) != MAR_OK) return fail(st);
     if ((st = upload(c, &c->SvalH, svalH.data(), svalH.size())) != MAR_OK) return fail(st);
     if ((st = upload(c, &c->diagS, diag.data(), diag.size())) != MAR_OK) return fail(st);
-    if ((st = upload(c, &c->d_loc, (const int32_t*)nullptr, 1)) != MAR_OK) return fail(st);
+    if ((st = upload(c, &c->d_reg, (const int32_t*)nullptr, mar::SEED_MAX_BLOCKS + 1)) != MAR_OK) return fail(st);
     he = hipStreamCreate(&c->stream);
     if (he == hipSuccess) he = hipStreamCreateWithFlags(&c->stream2, hipStreamNonBlocking);
     if (he == hipSuccess) he = hipEventCreateWithFlags(&c->ev_fork, hipEventDisableTiming);
@@ -1517,6 +1546,8 @@ mar_status mar_solve_many(int32_t n_sys, mar_ctx* const* ctx, const mar_request*
     std::vector<Plan> plans(n_sys);
     std::vector<char> key;
     for (int i = 0; i < n_sys; ++i) {
+        const mar_status st = measure_regions(ctx[i], req[i].form, (hipStream_t)hip_stream);
+        if (st != MAR_OK) return st;
         plans[i] = plan_solve(ctx[i], req[i].nu, req[i].prec, req[i].form, req[i].n_seeds);
         put_request(key, ctx[i], req[i], plans[i]);
     }
@@ -1683,6 +1714,7 @@ mar_status mar_solve_async(mar_ctx* c, const int32_t* d_seeds, int64_t n_seeds, 
     HIP_OR(c, hipSetDevice(c->device));
     mar_request r{d_seeds, n_seeds, nu, mu, kT, prec, form, d_rho, d_e_band, d_e_seed, d_n_seed, d_nu_eff, d_eps,
                   d_weight};
+    if ((st = measure_regions(c, form, (hipStream_t)hip_stream)) != MAR_OK) return st;
     return dispatch_solve(c, r, plan_solve(c, nu, prec, form, n_seeds), (hipStream_t)hip_stream);
 }
 
@@ -1699,6 +1731,7 @@ mar_status mar_solve_fermi_async(mar_ctx* c, const int32_t* d_seeds, int64_t n_s
     if ((size_t)nu > (size_t)mar::MAX_NU_ASSEMBLE) return set_err(c, MAR_ERR_ARG, "nu too large for the deferred assembly");
     HIP_OR(c, hipSetDevice(c->device));
     hipStream_t s = (hipStream_t)hip_stream;
+    if ((st = measure_regions(c, form, s)) != MAR_OK) return st;
     // levels, weights, kept eigenvector rows and per-seed results for all listed seeds
     const size_t n = (size_t)n_seeds, nl = n * nu;
     size_t off = 0;
@@ -2165,17 +2198,6 @@ mar_status mar_set_local_region(mar_ctx* c, int32_t hops) {
     if (!c) return MAR_ERR_STATE;
     if (hops >= 0 && (!c->H.bsr || c->SH.nnz != c->H.nnz))
         return set_err(c, MAR_ERR_ARG, "a local region needs H with 4x4 block structure");
-    if (hops >= 0 && hops != c->loc) {
-        // the largest region's block rows: whether one workgroup can hold a seed's region
-        int32_t n = 0;
-        c->loc_blocks = 0;
-        if (hipSetDevice(c->device) == hipSuccess &&
-            mar::launch_region_max(c->H.n, c->H.ptr, c->H.idx, hops, mar::SEED_MAX_BLOCKS, c->d_loc, c->stream).wgs > 0 &&
-            hipMemcpyAsync(&n, c->d_loc, 4, hipMemcpyDeviceToHost, c->stream) == hipSuccess &&
-            hipStreamSynchronize(c->stream) == hipSuccess && n <= mar::SEED_MAX_BLOCKS)
-            c->loc_blocks = n;
-        (void)hipGetLastError();
-    }
     c->loc = hops < 0 ? -1 : hops;
     return MAR_OK;
 }
@@ -2314,6 +2336,7 @@ mar_status solve_async_ext(mar_ctx* c, const int32_t* d_seeds, int64_t n_seeds, 
     const mar_request r{d_seeds, n_seeds, nu, mu, kT, prec, form, d_rho, d_e_band, d_e_seed, d_n_seed, d_nu_eff,
                         d_eps, d_weight};
     hipStream_t s = (hipStream_t)hip_stream;
+    if ((st = measure_regions(c, form, s)) != MAR_OK) return st;
     Plan pl = plan_solve(c, nu, prec, form, n_seeds);
     const int min_b = c->loc >= 0 ? (prec == MAR_FP32 ? 4 : 2) : 1;
     const bool shrink = form == MAR_FORM_BATCHED && c->tune.seed_block == 0;

@@ -325,9 +325,10 @@ template <typename T>
 LaunchInfo launch_es_take(const int32_t* ref, const T* keep, int64_t nr, int nu, int max_row, const double* h,
                           const double* Kp, const int32_t* nu_eff, T* keep1, double* h1, double* Kp1, int32_t* nu1,
                           hipStream_t s);
-// Largest number of block rows within hops of any block row (cap + 1: more than cap) into out[0].
-LaunchInfo launch_region_max(int64_t nbrow, const int32_t* brp, const int32_t* bcol, int hops, int cap, int32_t* out,
-                             hipStream_t s);
+// Largest number of block rows within h hops of any block row (cap + 1: more than cap) into out[h], h = 0 .. depth
+// (depth <= SEED_MAX_BLOCKS: a set that still grows then has more block rows than that).
+LaunchInfo launch_region_sizes(int64_t nbrow, const int32_t* brp, const int32_t* bcol, int depth, int cap, int32_t* out,
+                               hipStream_t s);
 
 // The device a context lives on (-1 for NULL).
 int ctx_device(const mar_ctx* c);

@@ -735,34 +735,39 @@ MAR_ES(double)
 #undef MAR_ES
 
 // ---------------------------------------------------------------------------
-// Largest number of block rows within `hops` hops of any block row, or cap + 1 when some set is larger than cap:
-// a wavefront per block row, its set in a hash table in LDS.
-__global__ __launch_bounds__(64) void k_region_max(int64_t nbrow, const int32_t* __restrict__ brp,
-                                                   const int32_t* __restrict__ bcol, int hops, int cap, int hs,
-                                                   int32_t* __restrict__ out) {
+// Largest number of block rows within h hops of any block row, h = 0 .. depth, or cap + 1 where some set is larger than
+// cap: a workgroup per block row, its set in a hash table in LDS, every level of one search.
+__global__ __launch_bounds__(WG) void k_region_sizes(int64_t nbrow, const int32_t* __restrict__ brp,
+                                                     const int32_t* __restrict__ bcol, int depth, int cap, int hs,
+                                                     int32_t* __restrict__ out) {
     extern __shared__ int shm[];
     int* key = shm;
-    int* raw = shm + hs;
+    int* raw = key + hs;
+    int* best = raw + cap;
     __shared__ int cnt;
-    int best = 0;
+    const int tid = threadIdx.x;
+    for (int k = tid; k <= depth; k += WG) best[k] = 0;
     for (int64_t I0 = blockIdx.x; I0 < nbrow; I0 += gridDim.x) {
-        for (int i = threadIdx.x; i < hs; i += 64) key[i] = -1;
+        for (int i = tid; i < hs; i += WG) key[i] = -1;
         __syncthreads();
         auto slot0 = [&](int I) { return (int)(((unsigned)I * 2654435761u) >> 7) & (hs - 1); };
-        if (threadIdx.x == 0) {
+        if (tid == 0) {
             key[slot0((int)I0)] = (int)I0;
             raw[0] = (int)I0;
             cnt = 1;
         }
         __syncthreads();
-        int f0 = 0, f1 = 1;
-        for (int h = 0; h < hops && f0 < f1 && f1 <= cap; ++h) {
-            for (int e = f0 + threadIdx.x; e < f1; e += 64) {
+        int f0 = 0, f1 = 1, h = 0;
+        for (;;) {
+            if (tid == 0) best[h] = max(best[h], f1);
+            // no further level: the set is complete or too large, or an earlier one was too large from there on
+            if (h == depth || f0 == f1 || f1 > cap || best[h + 1] > cap) break;
+            for (int e = f0 + tid; e < f1; e += WG) {
                 const int I = raw[e];
                 for (int p = brp[I]; p < brp[I + 1] && atomicAdd(&cnt, 0) <= cap; ++p) {
                     const int J = bcol[p];
                     int s = slot0(J);
-                    // 64 lanes stop adding once cap + 1 keys are in: at most cap + 65 of hs >= 2 cap + 128 slots fill
+                    // WG lanes stop adding once cap + 1 keys are in: at most cap + WG + 1 of hs >= 2 (cap + WG) slots fill
                     for (;;) {
                         const int old = atomicCAS(&key[s], -1, J);
                         if (old == -1) {
@@ -777,25 +782,28 @@ __global__ __launch_bounds__(64) void k_region_max(int64_t nbrow, const int32_t*
             }
             __syncthreads();
             f0 = f1;
-            f1 = cnt;
+            f1 = min(cnt, cap + 1);
+            ++h;
             __syncthreads();
         }
-        best = max(best, f1);
+        for (int k = h + 1 + tid; k <= depth; k += WG) best[k] = max(best[k], f1);
         __syncthreads();
     }
-    if (threadIdx.x == 0) atomicMax(out, best > cap ? cap + 1 : best);
+    for (int k = tid; k <= depth; k += WG) atomicMax(&out[k], best[k]);
 }
 
-__global__ void k_region_init(int32_t* out) { *out = 0; }
+__global__ void k_region_init(int32_t* out, int n) {
+    for (int i = threadIdx.x; i < n; i += WG) out[i] = 0;
+}
 
-LaunchInfo launch_region_max(int64_t nbrow, const int32_t* brp, const int32_t* bcol, int hops, int cap, int32_t* out,
-                             hipStream_t s) {
+LaunchInfo launch_region_sizes(int64_t nbrow, const int32_t* brp, const int32_t* bcol, int depth, int cap, int32_t* out,
+                               hipStream_t s) {
     int hs = 1;
-    while (hs < 2 * cap + 128) hs *= 2;
-    hipLaunchKernelGGL(k_region_init, dim3(1), dim3(1), 0, s, out);
-    const unsigned wgs = (unsigned)std::min<int64_t>(nbrow, 8192);
-    hipLaunchKernelGGL(k_region_max, dim3(wgs), dim3(64), (size_t)(hs + cap) * 4, s, nbrow, brp, bcol, hops, cap, hs,
-                       out);
+    while (hs < 2 * (cap + WG)) hs *= 2;
+    hipLaunchKernelGGL(k_region_init, dim3(1), dim3(WG), 0, s, out, depth + 1);
+    const unsigned wgs = (unsigned)std::min<int64_t>(nbrow, 2048);
+    hipLaunchKernelGGL(k_region_sizes, dim3(wgs), dim3(WG), (size_t)(hs + cap + depth + 1) * 4, s, nbrow, brp, bcol, depth,
+                       cap, hs, out);
     LaunchInfo li;
     li.wgs = wgs;
     return li;
