@@ -477,13 +477,18 @@ bool tuned_for_blocks(const mar_tuning& t) {
            t.support_off || t.two_streams == 1;
 }
 
+// Whether work on s may not allocate or wait: s captures into a graph (or its state cannot be told).
+bool captures(hipStream_t s) {
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    return hipStreamIsCapturing(s, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone;
+}
+
 // Measures the sizes of the local regions that a solve on stream s is about to run in, if they are not known and decide
 // its route: a kernel and a wait, once per context (1.9 ms for 131072 rows, 16 ms for 1048576). Under capture nothing may
 // wait: the solve then runs in seed blocks, which need no sizes.
 mar_status measure_regions(mar_ctx* c, mar_form form, hipStream_t s) {
     if (c->loc < 0 || form != MAR_FORM_BATCHED || tuned_for_blocks(c->tune) || region_blocks(c) > 0) return MAR_OK;
-    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(s, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) return MAR_OK;
+    if (captures(s)) return MAR_OK;
     constexpr int kDepth = 64;   // deeper than asked for: other hops are known then, also under capture
     const int depth = std::min(std::max<int>(c->loc, kDepth), mar::SEED_MAX_BLOCKS);
     std::vector<int32_t> n(depth + 1);
@@ -1196,6 +1201,31 @@ mar_status run_solve_delayed(mar_ctx* c, const int32_t* d_seeds, int64_t n_seeds
     return MAR_OK;
 }
 
+// Workspace of the one-workgroup-per-seed form for chunks of `chunk` seeds: offsets and bytes.
+struct SeedWs {
+    size_t K, h, Kp, nu, pr, e, n, nu_out, bytes;
+};
+SeedWs seed_workspace(const mar_ctx* c, const mar_request& r, const mar::SeedGeom& g, int64_t chunk) {
+    SeedWs o;
+    size_t off = 0;
+    auto take = [&](size_t bytes) {
+        const size_t at = off;
+        off += align_up(bytes);
+        return at;
+    };
+    const size_t n = (size_t)chunk, nu = r.nu;
+    o.K = take((size_t)g.grid * g.sstride * (r.prec == MAR_FP32 ? 4 : 8));
+    o.h = take(n * nu * nu * 8);
+    o.Kp = take(n * nu * std::max(1, c->max_row) * 8);
+    o.nu = take(n * 4);
+    o.pr = take(c->es.mode == 2 ? n * nu * 8 : 0);
+    o.e = take(r.d_e_seed ? 0 : (size_t)r.n_seeds * 8);
+    o.n = take(r.d_n_seed ? 0 : (size_t)r.n_seeds * 8);
+    o.nu_out = take(r.d_nu_eff ? 0 : (size_t)r.n_seeds * 4);
+    o.bytes = off;
+    return o;
+}
+
 // One workgroup per seed: the Krylov phase of a chunk of seeds in one launch, then its eigensolves.
 template <typename T>
 mar_status run_seedwise(mar_ctx* c, const mar_request& r, hipStream_t s) {
@@ -1207,36 +1237,23 @@ mar_status run_seedwise(mar_ctx* c, const mar_request& r, hipStream_t s) {
     const mar::SeedGeom g = seed_geom(c, nu, r.prec, n_seeds);
     const size_t per = (size_t)nu * (nu + std::max(1, c->max_row)) * 8;
     int64_t chunk = std::min<int64_t>(n_seeds, std::max<int64_t>(g.grid, (int64_t)(1e9 / (double)per)));
-    const bool own_e = r.d_e_seed == nullptr, own_n = r.d_n_seed == nullptr, own_nu = r.d_nu_eff == nullptr;
-    size_t oK = 0, oH = 0, oKp = 0, oNu = 0, oE = 0, oN = 0, oNuOut = 0, oPr = 0;
-    for (;;) {
-        size_t off = 0;
-        auto take = [&](size_t bytes) {
-            const size_t o = off;
-            off += align_up(bytes);
-            return o;
-        };
-        oK = take((size_t)g.grid * g.sstride * sizeof(T));
-        oH = take((size_t)chunk * nu * nu * 8);
-        oKp = take((size_t)chunk * nu * std::max(1, c->max_row) * 8);
-        oNu = take((size_t)chunk * 4);
-        oPr = take(c->es.mode == 2 ? (size_t)chunk * nu * 8 : 0);
-        oE = take(own_e ? (size_t)n_seeds * 8 : 0);
-        oN = take(own_n ? (size_t)n_seeds * 8 : 0);
-        oNuOut = take(own_nu ? (size_t)n_seeds * 4 : 0);
-        const mar_status st = ensure_ws(c, off);
-        if (st == MAR_OK) break;
-        if (!c->ext_ws || chunk <= 1) return st;   // a caller's workspace: shorter chunks
+    SeedWs o = seed_workspace(c, r, g, chunk);
+    // shorter chunks in a caller's workspace, and under capture, where the context's cannot grow
+    const size_t room = c->ext_ws ? c->ext_bytes : !c->dry && captures(s) ? c->ws_bytes : SIZE_MAX;
+    while (o.bytes > room && chunk > 1) {
         chunk = (chunk + 1) / 2;
+        o = seed_workspace(c, r, g, chunk);
     }
+    const mar_status st = ensure_ws(c, o.bytes);
+    if (st != MAR_OK) return st;
     char* w = c->ws_act;
-    double* h = (double*)(w + oH);
-    double* Kp = (double*)(w + oKp);
-    int32_t* nucp = (int32_t*)(w + oNu);
-    double* pref = c->es.mode == 2 ? (double*)(w + oPr) : nullptr;
-    double* e_seed = own_e ? (double*)(w + oE) : r.d_e_seed;
-    double* n_seed = own_n ? (double*)(w + oN) : r.d_n_seed;
-    int32_t* nu_out = own_nu ? (int32_t*)(w + oNuOut) : r.d_nu_eff;
+    double* h = (double*)(w + o.h);
+    double* Kp = (double*)(w + o.Kp);
+    int32_t* nucp = (int32_t*)(w + o.nu);
+    double* pref = c->es.mode == 2 ? (double*)(w + o.pr) : nullptr;
+    double* e_seed = r.d_e_seed ? r.d_e_seed : (double*)(w + o.e);
+    double* n_seed = r.d_n_seed ? r.d_n_seed : (double*)(w + o.n);
+    int32_t* nu_out = r.d_nu_eff ? r.d_nu_eff : (int32_t*)(w + o.nu_out);
     for (int64_t at = 0; at < n_seeds; at += chunk) {
         const int ns = (int)std::min<int64_t>(chunk, n_seeds - at);
         const int32_t* seeds = r.d_seeds + at;
@@ -1250,7 +1267,7 @@ mar_status run_seedwise(mar_ctx* c, const mar_request& r, hipStream_t s) {
             launch(c, s, P_UPD, [&] {
                 mar::SeedGeom gc = g;
                 gc.grid = std::min(g.grid, ns);
-                return mar::launch_seed<T>(gc, c->H, c->SH, c->M, c->diagS, seeds, ns, nu, c->loc, tau, (T*)(w + oK),
+                return mar::launch_seed<T>(gc, c->H, c->SH, c->M, c->diagS, seeds, ns, nu, c->loc, tau, (T*)(w + o.K),
                                            c->Hrp, c->max_row, hk, Kpk, keep ? c->es.m + at : nucp,
                                            pref ? c->es.vref : nullptr, pref, ns, keep, acc64, s);
             });
@@ -1337,7 +1354,9 @@ mar_status dispatch_solve(mar_ctx* c, const mar_request& r, const Plan& pl, hipS
                                "least %d seeds (block %d)", vec, pl.B));
     }
     mar_status st;
-    if (pl.seedwise) {
+    // (captured without room for one seed: the blocks may have it)
+    if (pl.seedwise && (c->ext_ws || c->dry || !captures(s) ||
+                        seed_workspace(c, r, seed_geom(c, r.nu, r.prec, r.n_seeds), 1).bytes <= c->ws_bytes)) {
         // the blocks' default would have run two of them in flight here: mar_solve_many goes on refusing the context
         hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
         if (!c->dry && !c->in_graph && !c->prof && c->es.mode == 0 && c->loc >= 6 && c->tune.two_streams == 0 &&

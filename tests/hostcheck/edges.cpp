@@ -26,8 +26,8 @@ namespace {
 struct Sys {
     int64_t M = 0, nnzH = 0;
     mar_ctx* c = nullptr;
-    int32_t* seeds = nullptr;
-    double *rho = nullptr, *eb = nullptr;
+    int32_t *seeds = nullptr, *nu = nullptr;
+    double *rho = nullptr, *eb = nullptr, *e = nullptr, *n = nullptr;
 };
 
 Sys load(const std::string& path) {
@@ -60,12 +60,15 @@ Sys load(const std::string& path) {
     (void)hipMemcpy(s.seeds, all.data(), 4 * s.M, hipMemcpyHostToDevice);
     (void)hipMalloc((void**)&s.rho, 8 * s.nnzH);
     (void)hipMalloc((void**)&s.eb, 8);
+    (void)hipMalloc((void**)&s.e, 8 * s.M);
+    (void)hipMalloc((void**)&s.n, 8 * s.M);
+    (void)hipMalloc((void**)&s.nu, 4 * s.M);
     return s;
 }
 
 mar_status solve(const Sys& s, int64_t n, int nu, mar_precision prec, hipStream_t st) {
-    return mar_solve_async(s.c, s.seeds, n, nu, -0.4, 0.1, prec, MAR_FORM_BATCHED, s.rho, s.eb, nullptr, nullptr, nullptr,
-                           nullptr, nullptr, st);
+    return mar_solve_async(s.c, s.seeds, n, nu, -0.4, 0.1, prec, MAR_FORM_BATCHED, s.rho, s.eb, s.e, s.n, s.nu, nullptr,
+                           nullptr, st);
 }
 
 void drop(Sys& s) {
@@ -73,6 +76,9 @@ void drop(Sys& s) {
     (void)hipFree(s.seeds);
     (void)hipFree(s.rho);
     (void)hipFree(s.eb);
+    (void)hipFree(s.e);
+    (void)hipFree(s.n);
+    (void)hipFree(s.nu);
 }
 
 }  // namespace
@@ -98,6 +104,18 @@ int main(int argc, char** argv) {
         const mar_status c = solve(s, 64, 12, MAR_FP32, st);
         printf("setter %d, solve %d (%s), again %d\n", (int)a, (int)b, b ? mar_last_error(s.c) : "", (int)c);
         if (b == MAR_OK) return 1;
+    } else if (what == "more_seeds_under_capture") {   // past the widest block the workspace need not grow with the seeds
+        for (int nu : {12, 60})
+            for (mar_precision p : {MAR_FP32, MAR_FP64}) {
+                const mar_status a = solve(s, 300, nu, p, st);
+                const long before = hip_stub_launches();
+                (void)hipStreamBeginCapture(st, hipStreamCaptureModeGlobal);
+                const mar_status b = solve(s, s.M, nu, p, st);
+                (void)hipStreamEndCapture(st, &g);
+                printf("warm %d, captured %d\n", (int)a, (int)b);
+                if (a || b || hip_stub_launches() == before) return 1;
+                (void)hipGraphDestroy(g);
+            }
     } else {
         return 2;
     }

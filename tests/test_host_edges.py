@@ -75,3 +75,7 @@ def test_local_region_set_while_a_stream_captures(program):
 def test_failing_measurement_of_the_regions_is_reported(program):
     out = _run(program, "region_sizes_fail")
     assert "setter 0, solve -5 (hipStreamSynchronize" in out and "again 0" in out
+
+
+def test_more_seeds_under_capture_than_in_the_warm_call(program):
+    assert _run(program, "more_seeds_under_capture").count("warm 0, captured 0") == 4
