@@ -1356,14 +1356,8 @@ mar_status dispatch_solve(mar_ctx* c, const mar_request& r, const Plan& pl, hipS
     mar_status st;
     // (captured without room for one seed: the blocks may have it)
     if (pl.seedwise && (c->ext_ws || c->dry || !captures(s) ||
-                        seed_workspace(c, r, seed_geom(c, r.nu, r.prec, r.n_seeds), 1).bytes <= c->ws_bytes)) {
-        // the blocks' default would have run two of them in flight here: mar_solve_many goes on refusing the context
-        hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-        if (!c->dry && !c->in_graph && !c->prof && c->es.mode == 0 && c->loc >= 6 && c->tune.two_streams == 0 &&
-            r.n_seeds > pl.B && hipStreamIsCapturing(s, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone)
-            c->ran_two_sets = true;
+                        seed_workspace(c, r, seed_geom(c, r.nu, r.prec, r.n_seeds), 1).bytes <= c->ws_bytes))
         return r.prec == MAR_FP32 ? run_seedwise<float>(c, r, s) : run_seedwise<double>(c, r, s);
-    }
     if (r.prec == MAR_FP32)
         st = pl.delayed ? run_solve_delayed<float>(c, r.d_seeds, r.n_seeds, r.nu, r.mu, r.kT, pl.B, pl.variant,
                                                    r.d_rho, r.d_e_band, r.d_e_seed, r.d_n_seed, r.d_nu_eff,
