@@ -596,11 +596,14 @@ __global__ __launch_bounds__(W * 64) void k_coef(int B, int nu, int n, const dou
     }
 }
 
+// Dynamic LDS of k_coef: seven vectors, and the partial sums of W wavefronts.
+constexpr size_t coef_lds(int nu, int W, bool pre) { return (size_t)(7 * (nu + 1) + (pre ? 4 : 6) * W * 64) * sizeof(double); }
+
 template <int W, int KU>
 static void coef(int B, int nu, int n, const double* red, double* A, double* G, double* R, double* C1, double* BT,
                  double* UU, double* cA, double* cB, float* cAf, float* cBf, double* gam, double* Fn, int32_t* active,
                  int32_t* nu_eff, double tau, const double* redb, int nrange, hipStream_t s) {
-    const size_t lds = (size_t)(7 * (nu + 1) + (KU > 0 ? 4 : 6) * W * 64) * sizeof(double);
+    const size_t lds = coef_lds(nu, W, KU > 0);
     static std::atomic<uint64_t> done{0};
     if (lds > 64 * 1024) allow_full_lds((const void*)k_coef<W, KU>, done);
     hipLaunchKernelGGL((k_coef<W, KU>), dim3(B), dim3(W * 64), lds, s, B, nu, n, red, A, G, R, C1, BT, UU, cA, cB, cAf,
@@ -613,9 +616,16 @@ LaunchInfo launch_coef(int B, int nu, int n, const double* red, double* A, doubl
                        int nrange, hipStream_t s) {
     // 4 wavefronts hold the matrices up to nu = 32, 8 up to nu = 64 (7.4 us per step at nu = 30 against 7.5 for 8; 8.1 at
     // nu = 50 against 9.1 for 4); at nu = 100 the columns read as they are used take 17.3 us, kept in registers 17.8
-    auto f = nu <= 32 ? coef<4, 8> : nu <= 64 ? coef<8, 8> : coef<16, 0>;
-    f(B, nu, n, red, A, G, R, C1, BT, UU, cA, cB, cAf, cBf, gam, Fn, active, nu_eff, tau, redb, nrange, s);
+    // past nu = 2047 the vectors leave LDS for eight wavefronts' sums (nu <= 2485), then for two
     LaunchInfo li;
+    constexpr size_t max_lds = 160 * 1024;
+    auto f = nu <= 32 ? coef<4, 8> : nu <= 64 ? coef<8, 8> : coef_lds(nu, 16, false) <= max_lds ? coef<16, 0>
+             : coef_lds(nu, 8, false) <= max_lds ? coef<8, 0> : coef<2, 0>;
+    if (coef_lds(nu, 2, false) > max_lds) {
+        li.wgs = -1;
+        return li;
+    }
+    f(B, nu, n, red, A, G, R, C1, BT, UU, cA, cB, cAf, cBf, gam, Fn, active, nu_eff, tau, redb, nrange, s);
     li.wgs = B;
     const double nn = (double)n + 1.0;
     li.bytes = (double)B * (3.0 * nn * nn + 8.0 * nn) * 8.0;
