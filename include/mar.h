@@ -71,8 +71,8 @@ typedef enum { MAR_FP64 = 0, MAR_FP32 = 1 } mar_precision;
  * row sets (cells of up to about 3072 rows, local regions of up to about ten
  * hops) with a 4x4-block H and a tuning that asks for nothing of the blocks
  * (every field of mar_tuning 0, eig_max_sweeps and two_streams 2 or 3 aside),
- * one workgroup runs each seed's whole textbook recurrence instead; an
- * autotuned block size does not apply there. */
+ * one workgroup runs each seed's whole textbook recurrence instead, unless
+ * mar_autotune found blocks faster there. */
 typedef enum { MAR_FORM_BATCHED = 0, MAR_FORM_PLAIN = 1 } mar_form;
 
 /* CGS2 schedules. Both run two classical Gram-Schmidt passes per new vector
@@ -309,9 +309,12 @@ mar_status mar_solve_many(int32_t n_sys, mar_ctx* const* ctx, const mar_request*
  * the 128 GB basis budget) and, for the delayed schedule, the projection tile
  * variants 0 and 3; keep the fastest (B, variant) for (nu, prec) in the context.
  * Later batched solves with seed_block = 0 and proj_variant = 0 in the tuning
- * use it. Outputs of the probe solves go to a context-owned scratch buffer;
+ * use it. Where solves of these seeds would run one workgroup per seed (see
+ * MAR_FORM_BATCHED) that is timed as well: later ones, in the same regions, run
+ * the blocks if those were faster, else one workgroup per seed. Outputs of the probe solves go to a context-owned scratch buffer;
  * the call synchronizes hip_stream. best_block (or NULL) receives B;
- * best_rate (or NULL) the probe throughput in seed-subspaces/s. */
+ * best_rate (or NULL) the probe throughput of what later solves run, in
+ * seed-subspaces/s. */
 mar_status mar_autotune(mar_ctx* ctx, int32_t nu, mar_precision prec, const int32_t* d_seeds, int64_t n_seeds,
                         double mu, double kT, void* hip_stream, int32_t* best_block, int32_t* best_variant,
                         double* best_rate);
@@ -378,7 +381,8 @@ int32_t mar_local_region(const mar_ctx* ctx);
 mar_status mar_set_tuning(mar_ctx* ctx, const mar_tuning* t);
 mar_status mar_get_tuning(const mar_ctx* ctx, mar_tuning* t);
 
-/* Seeds per block the batched form would use for (nu, prec) with the current tuning. */
+/* Seeds per block the batched form would use for (nu, prec) with the current tuning (where it runs in blocks: see
+ * MAR_FORM_BATCHED). */
 int32_t mar_seed_block(const mar_ctx* ctx, int32_t nu, mar_precision prec);
 
 /* Last error message of ctx, or of the calling thread's last mar_create when

@@ -79,8 +79,12 @@ struct mar_ctx {
     bool ran_two_sets = false;    // a solve ran two seed blocks in flight (mar_solve_many refuses the context)
     // projection workgroups per compute unit, by (element bytes, B, variant)
     std::map<std::tuple<int, int, int>, int> occ;
-    // autotuned (B, projection variant) by (nu, precision)
-    std::map<std::pair<int, int>, std::pair<int, int>> tuned;
+    struct Tuned {                // the fastest block width and projection variant,
+        int B, variant;
+        bool blocks;              // and whether it beat one workgroup per seed
+        int32_t loc;              // in these regions
+    };
+    std::map<std::pair<int, int>, Tuned> tuned;   // autotuned choices by (nu, precision)
     double* tune_buf = nullptr;   // probe outputs of the autotuner: rho [nnz(H)] + e_band
     double* zc_defer = nullptr;   // set during a solve whose assembly waits for a device Fermi level
     struct EsHook {               // eigen-state passes (mode 1: reference seed, 2: signed components)
@@ -395,7 +399,7 @@ int choose_block(const mar_ctx* c, int nu, mar_precision prec, int64_t n_seeds, 
     } else {
         auto t = c->tuned.find({nu, (int)prec});
         if (t != c->tuned.end() && delayed) {
-            B = t->second.first;
+            B = t->second.B;
         } else {
             // the widest block: one pass over a slab serves the most seeds and
             // the matrix values are reused B times
@@ -536,9 +540,13 @@ Plan plan_solve(const mar_ctx* c, int nu, mar_precision prec, mar_form form, int
     pl.variant = c->tune.proj_variant;
     if (pl.variant == 0 && c->tune.seed_block == 0 && form == MAR_FORM_BATCHED) {
         auto t = c->tuned.find({nu, (int)prec});
-        if (t != c->tuned.end()) pl.variant = t->second.second;
+        if (t != c->tuned.end()) pl.variant = t->second.variant;
     }
     pl.seedwise = form == MAR_FORM_BATCHED && use_seedwise(c, nu, prec, n_seeds);
+    if (pl.seedwise) {   // unless the autotuner found the blocks faster
+        auto t = c->tuned.find({nu, (int)prec});
+        pl.seedwise = t == c->tuned.end() || !t->second.blocks || t->second.loc != c->loc;
+    }
     return pl;
 }
 
@@ -1682,23 +1690,26 @@ mar_status mar_autotune(mar_ctx* c, int32_t nu, mar_precision prec, const int32_
         B0 = std::max(B0, prec == MAR_FP32 ? 4 : 2);
         cap_t = std::max(cap_t, B0);
     }
+    auto probe = [&](const Plan& pl) {   // seeds per second
+        st = dispatch_solve(c, r, pl, s);              // warm-up (sizes the workspace)
+        if (st != MAR_OK) return 0.0;
+        hipEventRecord(e0, s);
+        st = dispatch_solve(c, r, pl, s);
+        hipEventRecord(e1, s);
+        if (st != MAR_OK) return 0.0;
+        if (hipEventSynchronize(e1) != hipSuccess) {
+            st = set_err(c, MAR_ERR_HIP, "autotuner: hipEventSynchronize failed");
+            return 0.0;
+        }
+        float ms = 0.f;
+        hipEventElapsedTime(&ms, e0, e1);
+        return ms > 0.f ? n_probe / (ms * 1e-3) : 0.0;
+    };
     for (int B = B0; B <= cap_t && st == MAR_OK; B *= 2) {
         for (int v : {0, 3}) {
             if (!delayed && v != 0) continue;
-            Plan pl{B, delayed, v};
-            st = dispatch_solve(c, r, pl, s);          // warm-up (sizes the workspace)
+            const double rate = probe(Plan{B, delayed, v});
             if (st != MAR_OK) break;
-            hipEventRecord(e0, s);
-            st = dispatch_solve(c, r, pl, s);
-            hipEventRecord(e1, s);
-            if (st != MAR_OK) break;
-            if (hipEventSynchronize(e1) != hipSuccess) {
-                st = set_err(c, MAR_ERR_HIP, "autotuner: hipEventSynchronize failed");
-                break;
-            }
-            float ms = 0.f;
-            hipEventElapsedTime(&ms, e0, e1);
-            const double rate = ms > 0.f ? n_probe / (ms * 1e-3) : 0.0;
             if (rate > bestR) {
                 bestR = rate;
                 bestB = B;
@@ -1706,10 +1717,18 @@ mar_status mar_autotune(mar_ctx* c, int32_t nu, mar_precision prec, const int32_
             }
         }
     }
+    // one workgroup per seed, where solves would run that
+    bool blocks = false;
+    if (st == MAR_OK) st = measure_regions(c, MAR_FORM_BATCHED, s);
+    if (st == MAR_OK && use_seedwise(c, nu, prec, n_probe)) {
+        const double rate = probe(Plan{bestB, delayed, bestV, true});
+        blocks = rate < bestR;
+        bestR = std::max(rate, bestR);
+    }
     hipEventDestroy(e0);
     hipEventDestroy(e1);
     if (st != MAR_OK) return st;
-    c->tuned[{nu, (int)prec}] = {bestB, bestV};
+    c->tuned[{nu, (int)prec}] = {bestB, bestV, blocks, c->loc};
     if (best_block) *best_block = bestB;
     if (best_variant) *best_variant = bestV;
     if (best_rate) *best_rate = bestR;
