@@ -253,8 +253,9 @@ mar_status mar_solve_fermi(mar_ctx* ctx, const int32_t* seeds, int64_t n_seeds, 
  * |(e_j^T v_alpha^(j)) x window| over all listed seeds. Cost: every listed seed
  * is solved twice (levels and reference first, signs second) plus the
  * reference seed alone in the plain form; small cells that run one workgroup per
- * seed keep every seed's basis from the first time instead (up to 8 GB, held by
- * the context, where the device has room). With all M seeds listed and
+ * seed keep every seed's basis from the first time instead (up to 8 GB, where the
+ * device has room; the context holds it for the next call and gives it back when
+ * another of its allocations finds no memory). With all M seeds listed and
  * nu = M the result is the exact S-normalized generalized eigenvector up to one
  * global sign. Arguments: 1 <= k <= n_seeds, sigma finite and >= 0, the rest as
  * in mar_solve_async. Outputs: phi [n_seeds] (component of each listed seed, in

@@ -176,6 +176,27 @@ mar_status set_err(mar_ctx* c, mar_status st, const std::string& m) {
                            fmt("%s failed: %s", #call, hipGetErrorString(e_)));                      \
     } while (0)
 
+// Gives back what an eigen state left behind for its second pass, when the device has finished with it.
+hipError_t drop_kept(mar_ctx* c) {
+    if (!c->kws) return hipSuccess;
+    const hipError_t e = hipDeviceSynchronize();
+    if (e != hipSuccess) return e;
+    hipFree(c->kws);
+    c->kws = nullptr;
+    c->kws_bytes = 0;
+    return hipSuccess;
+}
+
+// Device memory of a context. Where there is none left the kept basis of an eigen state goes first, unless the call in
+// progress works on it.
+hipError_t dev_malloc(mar_ctx* c, void** p, size_t bytes) {
+    const hipError_t e = hipMalloc(p, bytes);
+    if (e != hipErrorOutOfMemory || !c->kws || c->es.K) return e;
+    (void)hipGetLastError();
+    const hipError_t d = drop_kept(c);
+    return d != hipSuccess ? d : hipMalloc(p, bytes);
+}
+
 // ---------------------------------------------------------------- validation
 mar_status check_csr(int64_t M, const int64_t* rp, const int32_t* col, const double* val, const char* nm,
                      std::string& msg) {
@@ -244,7 +265,7 @@ mar_status upload(mar_ctx* c, X** dst, const X* src, size_t n) {
     *dst = nullptr;
     if (n == 0) n = 1;
     void* p = nullptr;
-    HIP_OR(c, hipMalloc(&p, n * sizeof(X)));
+    HIP_OR(c, dev_malloc(c, &p, n * sizeof(X)));
     c->allocs.push_back(p);
     *dst = (X*)p;
     if (src) HIP_OR(c, hipMemcpy(p, src, n * sizeof(X), hipMemcpyHostToDevice));
@@ -592,7 +613,7 @@ mar_status ensure_ws(mar_ctx* c, size_t bytes) {
         c->ws_bytes = 0;
     }
     void* p = nullptr;
-    HIP_OR(c, hipMalloc(&p, bytes));
+    HIP_OR(c, dev_malloc(c, &p, bytes));
     c->ws = (char*)p;
     c->ws_bytes = bytes;
     c->ws_act = c->ws;
@@ -930,9 +951,9 @@ mar_status run_solve_delayed(mar_ctx* c, const int32_t* d_seeds, int64_t n_seeds
     bool two_fit = 2.0 * (double)set_bytes <= kTwoSetBytes;
     if (two_fit && tsm == 1 && c->tune.two_streams == 0 && !c->dry && !c->ext_ws && 2 * set_bytes > c->ws_bytes) {
         // the default takes a second workspace only when the device has room for it (the current
-        // workspace is given back first); else it runs one block at a time
+        // workspace and a kept basis are given back first); else it runs one block at a time
         size_t fr = 0, tot = 0;
-        two_fit = hipMemGetInfo(&fr, &tot) == hipSuccess && 2 * set_bytes + (set_bytes >> 4) <= fr + c->ws_bytes;
+        two_fit = hipMemGetInfo(&fr, &tot) == hipSuccess && 2 * set_bytes + (set_bytes >> 4) <= fr + c->ws_bytes + c->kws_bytes;
     }
     const int nset = n_blocks >= 2 && !c->prof && !c->in_graph && !capturing && c->es.mode == 0 &&
                              tsm == 1 &&
@@ -1226,7 +1247,7 @@ SeedWs seed_workspace(const mar_ctx* c, const mar_request& r, const mar::SeedGeo
     o.h = take(n * nu * nu * 8);
     o.Kp = take(n * nu * std::max(1, c->max_row) * 8);
     o.nu = take(n * 4);
-    o.pr = take(c->es.mode == 2 ? n * nu * 8 : 0);
+    o.pr = take(c->es.mode == 2 || c->es.K ? n * nu * 8 : 0);   // (a kept basis: no growth between the passes)
     o.e = take(r.d_e_seed ? 0 : (size_t)r.n_seeds * 8);
     o.n = take(r.d_n_seed ? 0 : (size_t)r.n_seeds * 8);
     o.nu_out = take(r.d_nu_eff ? 0 : (size_t)r.n_seeds * 4);
@@ -1667,7 +1688,7 @@ mar_status mar_autotune(mar_ctx* c, int32_t nu, mar_precision prec, const int32_
     hipStream_t s = (hipStream_t)hip_stream;
     if (!c->tune_buf) {
         void* p = nullptr;
-        HIP_OR(c, hipMalloc(&p, (size_t)(c->nnzH + 1) * 8));
+        HIP_OR(c, dev_malloc(c, &p, (size_t)(c->nnzH + 1) * 8));
         c->tune_buf = (double*)p;
         c->allocs.push_back(p);
     }
@@ -1783,7 +1804,7 @@ mar_status mar_solve_fermi_async(mar_ctx* c, const int32_t* d_seeds, int64_t n_s
         c->fws = nullptr;
         c->fws_bytes = 0;
         void* p = nullptr;
-        HIP_OR(c, hipMalloc(&p, off));
+        HIP_OR(c, dev_malloc(c, &p, off));
         c->fws = (char*)p;
         c->fws_bytes = off;
     }
@@ -1856,7 +1877,7 @@ mar_status mar_eigen_state_async(mar_ctx* c, const int32_t* d_seeds, int64_t n_s
         c->fws = nullptr;
         c->fws_bytes = 0;
         void* p = nullptr;
-        HIP_OR(c, hipMalloc(&p, off));
+        HIP_OR(c, dev_malloc(c, &p, off));
         c->fws = (char*)p;
         c->fws_bytes = off;
     }
@@ -1890,12 +1911,7 @@ mar_status mar_eigen_state_async(mar_ctx* c, const int32_t* d_seeds, int64_t n_s
         keep = hipStreamIsCapturing(s, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone &&
                hipMemGetInfo(&fr, &tot) == hipSuccess && koff + (koff >> 3) <= fr + c->kws_bytes;
         if (keep) {
-            if (c->kws) {
-                HIP_OR(c, hipDeviceSynchronize());
-                HIP_OR(c, hipFree(c->kws));
-            }
-            c->kws = nullptr;
-            c->kws_bytes = 0;
+            HIP_OR(c, drop_kept(c));
             void* p = nullptr;
             if (hipMalloc(&p, koff) == hipSuccess) {
                 c->kws = (char*)p;
@@ -1922,6 +1938,12 @@ mar_status mar_eigen_state_async(mar_ctx* c, const int32_t* d_seeds, int64_t n_s
                   nu_eff, eps, wt};
     c->zc_defer = zc;
     st = dispatch_solve(c, r, pl, s);
+    if (st == MAR_ERR_NOMEM && keep) {   // no room for the pass beside the kept basis: it is formed again instead
+        (void)hipGetLastError();
+        keep = false;
+        c->es = mar_ctx::EsHook{};
+        st = drop_kept(c) == hipSuccess ? dispatch_solve(c, r, pl, s) : MAR_ERR_NOMEM;
+    }
     c->zc_defer = nullptr;
     if (st != MAR_OK) return st;
     // eta(k - 1), eps_k = eta(k - 1/2), eta(k) from the integrated density of states
@@ -2005,7 +2027,7 @@ mar_status mar_eigen_state(mar_ctx* c, const int32_t* seeds, int64_t n_seeds, in
         c->io = nullptr;
         c->io_bytes = 0;
         void* p = nullptr;
-        HIP_OR(c, hipMalloc(&p, off));
+        HIP_OR(c, dev_malloc(c, &p, off));
         c->io = (char*)p;
         c->io_bytes = off;
     }
@@ -2055,7 +2077,7 @@ mar_status mar_solve_fermi(mar_ctx* c, const int32_t* seeds, int64_t n_seeds, in
         c->io = nullptr;
         c->io_bytes = 0;
         void* p = nullptr;
-        HIP_OR(c, hipMalloc(&p, off));
+        HIP_OR(c, dev_malloc(c, &p, off));
         c->io = (char*)p;
         c->io_bytes = off;
     }
@@ -2121,7 +2143,7 @@ mar_status mar_solve(mar_ctx* c, const int32_t* seeds, int64_t n_seeds, int32_t 
         c->io = nullptr;
         c->io_bytes = 0;
         void* p = nullptr;
-        HIP_OR(c, hipMalloc(&p, off));
+        HIP_OR(c, dev_malloc(c, &p, off));
         c->io = (char*)p;
         c->io_bytes = off;
     }
@@ -2211,7 +2233,7 @@ mar_status mar_local_flip(mar_ctx* c, double* d_phi, double eps, const double* d
     }
     if (!c->flws) {
         void* p = nullptr;
-        HIP_OR(c, hipMalloc(&p, mar::flip_workspace(c->M, c->max_row)));
+        HIP_OR(c, dev_malloc(c, &p, mar::flip_workspace(c->M, c->max_row)));
         c->flws = (char*)p;
     }
     mar::launch_flip(c->M, c->Hrp, c->Hcol, c->Hval, c->SvalH, c->max_row, eps, d_phi, d_phi_ref, cpen, c->fl_nround,

@@ -6,6 +6,7 @@
 #include <cstdint>
 #include <cstdio>
 #include <cstring>
+#include <map>
 #include <string>
 #include <vector>
 
@@ -15,7 +16,30 @@ extern "C" {
 long hip_stub_errors();
 long hip_stub_launches();
 hipError_t __real_hipStreamSynchronize(hipStream_t s);
+hipError_t __real_hipMalloc(void** p, size_t n);
+hipError_t __real_hipFree(void* p);
 static bool fail_sync = false;
+static std::map<void*, size_t> live;          // what the device holds
+static size_t held = 0, budget = SIZE_MAX;    // bytes, and the device's size
+hipError_t __wrap_hipMalloc(void** p, size_t n) {
+    if (held + n > budget) return hipErrorOutOfMemory;
+    const hipError_t e = __real_hipMalloc(p, n);
+    if (e == hipSuccess && *p) held += live[*p] = n;
+    return e;
+}
+hipError_t __wrap_hipFree(void* p) {
+    auto it = live.find(p);
+    if (it != live.end()) {
+        held -= it->second;
+        live.erase(it);
+    }
+    return __real_hipFree(p);
+}
+hipError_t __wrap_hipMemGetInfo(size_t* f, size_t* t) {
+    *t = budget == SIZE_MAX ? 288ull << 30 : budget;
+    *f = *t - held;
+    return hipSuccess;
+}
 hipError_t __wrap_hipStreamSynchronize(hipStream_t s) {
     return fail_sync ? hipErrorUnknown : __real_hipStreamSynchronize(s);
 }
@@ -71,6 +95,11 @@ mar_status solve(const Sys& s, int64_t n, int nu, mar_precision prec, hipStream_
                            nullptr, st);
 }
 
+mar_status eigen_state(const Sys& s, int64_t n, int nu, hipStream_t st) {   // (1024 seeds, nu = 24: 201 MB of basis)
+    return mar_eigen_state_async(s.c, s.seeds, n, nu, (int)(n / 2), 0.02, MAR_FP64, MAR_FORM_BATCHED, s.e, s.n, nullptr,
+                                 st);
+}
+
 void drop(Sys& s) {
     mar_destroy(s.c);
     (void)hipFree(s.seeds);
@@ -116,6 +145,22 @@ int main(int argc, char** argv) {
                 if (a || b || hip_stub_launches() == before) return 1;
                 (void)hipGraphDestroy(g);
             }
+    } else if (what == "kept_basis_gives_way") {   // a later solve gets the memory that an eigen state's basis holds
+        const mar_status a = eigen_state(s, s.M, 24, st);
+        budget = 500ull << 20;
+        mar_tuning t;
+        memset(&t, 0, sizeof t);
+        t.upd_q = 4;   // seed blocks: 210 MB of basis, 126 MB of subspace matrices
+        const mar_status b = mar_set_tuning(s.c, &t), c = solve(s, 128, 200, MAR_FP64, st);
+        printf("eigen state %d, tuning %d, solve %d\n", (int)a, (int)b, (int)c);
+    } else if (what == "kept_basis_without_room_for_the_pass") {   // the basis alone fits: the state is found without it
+        const mar_status a = eigen_state(s, 256, 24, st);
+        printf("with the basis %zu KB\n", held >> 10);
+        drop(s);
+        s = load(argv[2]);
+        budget = 70ull << 20;
+        const mar_status b = eigen_state(s, 256, 24, st);
+        printf("eigen state %d, on less memory %d (%s)\n", (int)a, (int)b, b ? mar_last_error(s.c) : "");
     } else {
         return 2;
     }

@@ -19,7 +19,7 @@ CSRC = os.path.join(ROOT, "paper_1307_3218_amd", "csrc")
 ROCM = os.environ.get("ROCM_PATH", "/opt/rocm")
 HIPCC = os.path.join(ROCM, "bin", "hipcc")
 CLANG = os.path.join(ROCM, "llvm", "bin", "clang++")
-WRAPPED = ["hipStreamSynchronize"]
+WRAPPED = ["hipStreamSynchronize", "hipMalloc", "hipFree", "hipMemGetInfo"]
 
 
 def _compile(cmd):
@@ -79,3 +79,11 @@ def test_failing_measurement_of_the_regions_is_reported(program):
 
 def test_more_seeds_under_capture_than_in_the_warm_call(program):
     assert _run(program, "more_seeds_under_capture").count("warm 0, captured 0") == 4
+
+
+def test_basis_of_an_eigen_state_gives_way_to_a_later_solve(program):
+    assert "eigen state 0, tuning 0, solve 0" in _run(program, "kept_basis_gives_way")
+
+
+def test_eigen_state_without_room_for_the_pass_beside_the_kept_basis(program):
+    assert "eigen state 0, on less memory 0" in _run(program, "kept_basis_without_room_for_the_pass")
