@@ -536,19 +536,25 @@ bool use_seedwise(const mar_ctx* c, int nu, mar_precision prec, int64_t ns) {
     // 3 hops, nu = 54: by 3e-3 of their root mean square, with errors against 64 bits of 1e-5 and 2e-6; 9.3 ms in blocks,
     // 0.9 with a workgroup per seed). At up to a quarter of the rows they move by 1e-4 at most.
     if (c->loc >= 0 && prec == MAR_FP32 && nu > region_blocks(c)) return false;
-    // Where the line lies (ms per solve, one workgroup per seed / blocks, diamond cells and mixed-lattice regions):
-    //  * a few hundred to 2048 rows: FP32 nu = 30, 256 seeds: 0.42 / 1.60 at 256 rows, 0.84 / 2.03 at 2048; FP64
-    //    nu = 100, 1024 seeds: 24.6 / 88.8 at 1024 rows, 56 / 96 at 2048. Always taken up to 3072 rows.
-    //  * 4096 rows: one compute unit streams its seed's basis four times per step from the last-level cache, the
-    //    blocks stream all seeds' twice: FP32 nu = 30 (0.5 MB of basis) 6.3 / 9.6 for 1024 seeds, nu = 100 (1.6 MB)
-    //    55.9 / 58.2, 15.2 / 14.3 for 256; FP64 nu = 100 (3.3 MB) 116 / 134, nu = 200 (6.6 MB) 76 / 70 for 8 seeds.
-    //  * 8192 rows: FP32 nu = 30 13.0 / 11.9, nu = 100 116 / 98.
-    //  * local regions: a block of seeds streams the union of its regions, so the line lies further out: regions of
-    //    6 hops (226 blocks) FP32 nu = 100, 1024 seeds 12.0 / 84.5, 10 hops (about 900) 46 / 165, 12 hops (about
-    //    1500) 91 / 187, but nu = 12 4.3 / 3.8; FP64 10 hops with 8 seeds 9.9 / 9.2, with 64 14.5 / 24.8.
-    const double rows = 4.0 * g.nbcap, kbytes = nu * rows * (prec == MAR_FP32 ? 4 : 8);
-    if (c->loc >= 0) return rows <= 3072 || (nu >= 32 && (prec == MAR_FP32 || ns >= 32));
-    return rows <= 3072 || (rows <= 4096 && kbytes <= (prec == MAR_FP32 ? 1.0e6 : 4.0e6));
+    // Where the line lies (ms per solve, one workgroup per seed / blocks; diamond cells and mixed-lattice regions). One
+    // compute unit streams its seed's basis four times per step, what does not fit in LDS from L2 and the last-level cache;
+    // the blocks stream all seeds' twice with the whole chip, and a block's time hardly falls with fewer seeds.
+    //  * up to 3072 rows always: FP32 nu = 30, 256 seeds 0.71 / 1.63 at 2048 rows; FP64 nu = 100 13.4 / 23.2 at 2048 and
+    //    21.0 / 27.7 at 3072. Nearly equal at 3072 rows and nu = 300 (FP32 256 seeds 104 / 106, FP64 8 seeds 73.5 / 74.4).
+    //    A single seed loses past 2 MB of basis there (FP64 nu = 200 31 / 23, nu = 300 73 / 46).
+    //  * to 4096 rows: FP32 nu = 30 (0.5 MB of basis) 1.07 / 1.49 with 8 seeds, nu = 60 4.9 / 5.1 with 256; FP64 nu = 30
+    //    1.6 to 2.1 / 1.6 to 2.0 up to 128 seeds; above 1.4 MB only past the 128 seeds of one block: nu = 100 9.9 / 7.4 with
+    //    1, 12.2 / 11.1 with 16, 17.7 / 16.4 with 128, 22.0 / 28.0 with 192.
+    //  * 8192 rows: FP32, 1024 seeds, nu = 30 13.0 / 11.9, nu = 100 116 / 98.
+    //  * local regions: a block of seeds streams the union of its regions, so the line lies further out. 6 hops (largest 908 rows)
+    //    FP32 nu = 100, 1024 seeds 7.3 / 84; 10 hops (3720) 5.9 / 8.3 with 8 seeds, 11.3 / 45 with 256; 12 hops (6284)
+    //    11.0 / 8.8 with 16, 12.7 / 11.7 with 64, 13.1 / 20.2 with 96. FP64, 10 hops: 13.0 / 10.6 with 32, 13.3 / 14.9 with
+    //    48. At nu = 12 and 12 hops 4.3 / 3.8.
+    const bool f32 = prec == MAR_FP32;
+    const double rows = 4.0 * g.nbcap, kbytes = nu * rows * (f32 ? 4 : 8);
+    if (rows <= 3072) return true;
+    if (c->loc >= 0) return nu >= 32 && (f32 ? rows <= 5120 || ns > 64 : ns > 32);
+    return rows <= 4096 && (f32 ? kbytes <= 1.0e6 : kbytes <= 1.4e6 || (kbytes <= 4.0e6 && ns > 128));
 }
 
 Plan plan_solve(const mar_ctx* c, int nu, mar_precision prec, mar_form form, int64_t n_seeds) {
