@@ -427,7 +427,14 @@ int choose_block(const mar_ctx* c, int nu, mar_precision prec, int64_t n_seeds, 
             B = block_cap(c, nu, prec, delayed);
         }
         // the least power of two that holds the seeds (blocks of 2 and 4 for one to three: a local region needs 4)
-        if (n_seeds > 0) B = std::min<int64_t>(B, n_seeds < 4 ? 2 * pow2_floor(n_seeds) : 2 * pow2_floor(n_seeds - 1));
+        if (n_seeds > 0) {
+            int64_t fit = n_seeds < 4 ? 2 * pow2_floor(n_seeds) : 2 * pow2_floor(n_seeds - 1);
+            // FP64, local regions: blocks of 8 have half the tiles of blocks of 16, too few for the chip up to about 16 hops
+            // (8 seeds, nu = 100, ms in blocks of 8 / 16: 10 hops 11.4 / 8.8, 12 hops 11.7 / 9.4, 16 hops 12.9 / 12.4, 20
+            // hops 15.0 / 20.1; nu = 30, 10 hops 1.85 / 1.69)
+            if (fit == 8 && prec == MAR_FP64 && c->loc >= 0 && c->loc <= 16) fit = 16;
+            B = std::min<int64_t>(B, fit);
+        }
         B = std::min(B, bmax);
     }
     return std::max(1, pow2_floor(B));
