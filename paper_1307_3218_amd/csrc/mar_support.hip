@@ -56,8 +56,8 @@ __global__ __launch_bounds__(WG) void k_sup_hop(int64_t nbrow, const int32_t* __
 // The whole search in one workgroup: distances, the rows reached in order (queue) and a bit per row reached, in LDS. Every
 // row's columns are read once, when the search reaches it (the pattern is symmetric), and the search ends with the last
 // row reached, however large hmax is. What bounds it is the latency of a level (a row's columns are read together): 40 us
-// for 256 seeds on 4096 block rows and 201 us on 32768, where a launch per level took about 4 us for each of nu + 5 levels
-// (165 us at nu = 30, 450 us at nu = 100).
+// for 256 seeds on 4096 block rows and up to 235 us on 32768, where a launch per level takes about 3 us for each of nu + 5
+// levels (150 us at nu = 30, 300 us at nu = 100).
 constexpr int SUP_WG = 1024;
 constexpr int64_t SUP_LDS_ROWS = 36 * 1024;   // 4 bytes and a bit per row within 160 KB
 
@@ -171,7 +171,12 @@ LaunchInfo launch_support(int64_t M, int64_t nbrow, const int32_t* brp, const in
                           int32_t* cnt, int32_t* list, int32_t* Dl, hipStream_t s) {
     const int64_t ntiles = (nbrow + bpt - 1) / bpt;
     const unsigned rw = (unsigned)((nbrow + WG - 1) / WG), tw = (unsigned)((ntiles + WG - 1) / WG);
-    if (nbrow <= SUP_LDS_ROWS && hmax < 0xffff) {
+    // One workgroup where its time with every row reached (about 20 us and 6.6 us per 1000 rows) is within that of the
+    // launches (about 40 us and 2.8 us per level). us, one workgroup / launches, 256 seeds spread over the cell, then 256
+    // consecutive ones: 32768 rows nu = 12 236 / 96 and 103 / 98, nu = 30 235 / 123 and 224 / 157, nu = 100 232 / 273 and
+    // 192 / 275; 16384 rows nu = 12 126 / 82 and 84 / 90, nu = 30 123 / 128 and 123 / 137; 4096 rows 45 / 52 and 33 / 48 at
+    // nu = 2, 48 / 150 and 54 / 144 at nu = 30.
+    if (nbrow <= SUP_LDS_ROWS && nbrow <= 3000 + 420 * (int64_t)hmax && hmax < 0xffff) {
         static std::atomic<uint64_t> done{0};
         allow_lds((const void*)k_sup_search, done, 160 * 1024 - 256);
         const size_t lds = (size_t)((nbrow + 31) / 32) * 4 + (size_t)nbrow * 4;
