@@ -482,20 +482,25 @@ __global__ __launch_bounds__(WG) void k_spmm_csr(int64_t nrow, const int32_t* __
     if (i0 < nrow) {
         const int hi = rp[i0 + 1];
         if constexpr (B >= VEC) {
-            for (int t = rp[i0]; t < hi; t += CH) {
+            int t = rp[i0];
+            for (; t + CH <= hi; t += CH) {
                 T a[CH], u[CH][VEC];
 #pragma unroll
                 for (int q = 0; q < CH; ++q) {
-                    const int tt = t + q < hi ? t + q : hi - 1;
-                    a[q] = val[tt];
-                    unpack(reinterpret_cast<const VT*>(X)[((int64_t)col[tt] * B + s0) / VEC], u[q]);
+                    a[q] = val[t + q];
+                    unpack(reinterpret_cast<const VT*>(X)[((int64_t)col[t + q] * B + s0) / VEC], u[q]);
                 }
 #pragma unroll
                 for (int q = 0; q < CH; ++q)
-                    if (t + q < hi) {
 #pragma unroll
-                        for (int i = 0; i < SW; ++i) acc[i] = fma(a[q], u[q][i], acc[i]);
-                    }
+                    for (int i = 0; i < SW; ++i) acc[i] = fma(a[q], u[q][i], acc[i]);
+            }
+            for (; t < hi; ++t) {
+                T u[VEC];
+                const T a = val[t];
+                unpack(reinterpret_cast<const VT*>(X)[((int64_t)col[t] * B + s0) / VEC], u);
+#pragma unroll
+                for (int i = 0; i < SW; ++i) acc[i] = fma(a, u[i], acc[i]);
             }
         } else {
             for (int t = rp[i0]; t < hi; ++t) {
@@ -544,24 +549,32 @@ __global__ __launch_bounds__(WG) void k_spmm2_csr(int64_t nrow, const int32_t* _
     for (int i = 0; i < VEC; ++i) ah[i] = as[i] = (T)0;
     if (i0 < nrow) {
         const int hi = rp[i0 + 1];
-        for (int t = rp[i0]; t < hi; t += CH) {
+        int t = rp[i0];
+        for (; t + CH <= hi; t += CH) {
             T h[CH], o[CH], u[CH][VEC];
 #pragma unroll
             for (int q = 0; q < CH; ++q) {
-                const int tt = t + q < hi ? t + q : hi - 1;
-                h[q] = hv[tt];
-                o[q] = sv[tt];
-                unpack(reinterpret_cast<const VT*>(X)[((int64_t)col[tt] * B + s0) / VEC], u[q]);
+                h[q] = hv[t + q];
+                o[q] = sv[t + q];
+                unpack(reinterpret_cast<const VT*>(X)[((int64_t)col[t + q] * B + s0) / VEC], u[q]);
             }
 #pragma unroll
             for (int q = 0; q < CH; ++q)
-                if (t + q < hi) {
 #pragma unroll
-                    for (int i = 0; i < VEC; ++i) {
-                        ah[i] = fma(h[q], u[q][i], ah[i]);
-                        as[i] = fma(o[q], u[q][i], as[i]);
-                    }
+                for (int i = 0; i < VEC; ++i) {
+                    ah[i] = fma(h[q], u[q][i], ah[i]);
+                    as[i] = fma(o[q], u[q][i], as[i]);
                 }
+        }
+        for (; t < hi; ++t) {
+            T u[VEC];
+            const T h = hv[t], o = sv[t];
+            unpack(reinterpret_cast<const VT*>(X)[((int64_t)col[t] * B + s0) / VEC], u);
+#pragma unroll
+            for (int i = 0; i < VEC; ++i) {
+                ah[i] = fma(h, u[i], ah[i]);
+                as[i] = fma(o, u[i], as[i]);
+            }
         }
         reinterpret_cast<VT*>(Y)[(i0 * B + s0) / VEC] = pack(ah);
         reinterpret_cast<VT*>(Z)[(i0 * B + s0) / VEC] = pack(as);
