@@ -447,8 +447,10 @@ struct SeedRun {
 };
 
 // The blocks of a delayed solve: as many of B0 seeds as are full, then narrower ones for the seeds that are left, whose
-// sweeps would otherwise run over the padding of a whole block. row_bytes: one vector.
-std::vector<SeedRun> seed_runs(const mar_ctx* c, int64_t n_seeds, int B0, int nu, double row_bytes, bool local) {
+// sweeps would otherwise run over the padding of a whole block. row_bytes: one vector. (The width of a block sets the
+// partition of its projection's sums, which in the FP32 form at large nu sets a column's error within its bar: nu = 300 on
+// 131072 rows 8.2e-7 in a block of 128, 9.5e-7 in one of 64.)
+std::vector<SeedRun> seed_runs(const mar_ctx* c, int64_t n_seeds, int B0, int nu, double row_bytes, bool f64, bool local) {
     std::vector<SeedRun> runs;
     constexpr int kMin = 16;   // below, a step's time hardly falls with the width
     // a pinned width stays; local regions and alternating blocks keep their number of blocks
@@ -467,9 +469,13 @@ std::vector<SeedRun> seed_runs(const mar_ctx* c, int64_t n_seeds, int B0, int nu
         const int64_t rest = left - half;
         const int fit2 = rest > 1 ? 2 * pow2_floor(rest - 1) : 1;
         // in two blocks the padding of fit - half - fit2 seeds is not swept (two passes over nu / 2 slabs on average, at
-        // 5.5 TB/s), but the small kernels and launches of a step (about 80 us) run twice
+        // 5.5 TB/s), but the small kernels and launches of a step run twice, and in FP64 the narrow blocks' sweeps are the
+        // less efficient ones. Measured, one block / two (ms): FP32 16384 rows nu = 60, 160 seeds (69 us saved per step)
+        // 12.6 / 11.5, 32768 rows nu = 30 (69) 4.50 / 4.58, 65536 rows nu = 30, 192 seeds (92) 7.19 / 7.08; FP64 16384
+        // rows nu = 100, 70 seeds (114) 32.3 / 35.2, 32768 rows nu = 100, 96 seeds (153) 52.1 / 53.5 and nu = 80, 70
+        // seeds (183) 32.9 / 30.3, 65536 rows nu = 40, 70 seeds (183) 11.8 / 11.4
         const double saved = (double)(fit - half - std::max(kMin, fit2)) * nu * row_bytes / 5.5e12;
-        if (fit > kMin && saved > 80e-6) {
+        if (fit > kMin && saved > (f64 ? 160e-6 : 80e-6)) {
             runs.push_back({half, half});
             left = rest;
         } else {
@@ -901,7 +907,7 @@ mar_status run_solve_delayed(mar_ctx* c, const int32_t* d_seeds, int64_t n_seeds
         if (sparse) g.part_cap = std::max<int64_t>(g.part_cap, g.grid_max * 3 * g.kg * B);
         return g;
     };
-    const std::vector<SeedRun> runs = seed_runs(c, n_seeds, B0, nu, (double)M * sizeof(T), local);
+    const std::vector<SeedRun> runs = seed_runs(c, n_seeds, B0, nu, (double)M * sizeof(T), sizeof(T) == 8, local);
     std::vector<Geo> geos;
     for (const SeedRun& r : runs) geos.push_back(geometry(r.B));
     if (geos.empty()) geos.push_back(geometry(B0));
