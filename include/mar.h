@@ -395,7 +395,9 @@ const char* mar_last_error(const mar_ctx* ctx);
  * events on the launch stream. mar_profile_collect synchronizes those events
  * and accumulates, per kernel class, the launch count, the summed event time
  * and the algorithmic bytes and flops (bytes: every operand read once and
- * every result written once, as the method requires). */
+ * every result written once, as the method requires). Solves that run one
+ * workgroup per seed (see MAR_FORM_BATCHED) have their whole Krylov phase, the
+ * products and projections included, in one kernel, counted in "cgs_upd". */
 enum { MAR_PROF_CLASSES = 16 };
 typedef struct {
     char name[24];

@@ -23,7 +23,9 @@ using mar::LaunchInfo;
 
 namespace {
 
-// One class per kernel variant, so that a class maps to one kernel symbol in a trace.
+// One class per kernel variant, so that a class maps to one kernel symbol in a trace. The classes fill the
+// MAR_PROF_CLASSES that callers' buffers hold, so the whole Krylov phase of one workgroup per seed (k_seed; k_es_dots on a
+// kept basis) counts as P_UPD.
 enum ProfClass {
     P_INIT = 0, P_SPMM, P_SPMM_DOT, P_PROJ2, P_PROJ1, P_UPD, P_REDUCE, P_NORM, P_APPEND, P_EIG, P_SUM,
     P_PROJR, P_UPD2, P_COEF, P_MU, P_SUPPORT, P_COUNT

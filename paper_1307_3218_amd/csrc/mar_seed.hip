@@ -637,11 +637,12 @@ static LaunchInfo launch_seed_t(const SeedGeom& g, const DevMat& H, const DevMat
         hipLaunchKernelGGL((k_seed<T, false>), dim3(g.grid), dim3(g.threads), g.lds, s, a);
     }
     li.wgs = g.grid;
-    // per seed: four sweeps over the basis vectors so far outside LDS, on the rows of its region (at most the listed
-    // ones), and the values of three products
+    // operands and results once: both matrices on the rows that the seeds can reach, the subspace matrices, the gathered
+    // rows, a kept basis (the basis itself stays in LDS and the caches: its sweeps there are not counted)
     const double rows = 4.0 * g.nbcap, el = sizeof(T);
-    const double out = std::max<double>(0.0, nu - std::floor((double)g.kbytes / (rows * el)));
-    li.bytes = (double)ns * rows * el * (2.0 * out * (out + 1.0) + out + 12.0 * nu * (double)H.nnz / (double)H.n);
+    const double part = std::min(1.0, (double)ns * g.nbcap / (double)H.n);
+    li.bytes = part * ((double)H.nnz * (32.0 * el + 4.0) + (double)H.n * 4.0) +
+               (double)ns * nu * (0.5 * (nu + 1.0) + max_row) * 8.0 + (keep ? (double)ns * nu * rows * el : 0.0);
     li.flops = (double)ns * rows * (5.0 * nu * (nu + 1.0) + 6.0 * nu * 4.0 * ((double)H.nnz / (double)H.n));
     return li;
 }

@@ -60,3 +60,18 @@ def test_fp32_regions_on_either_side_of_a_quarter_of_the_rows(regions):
     lst = np.arange(s.M // 2, s.M // 2 + 40, dtype=np.int32)
     assert _route(ctx, lst, 41, "fp32") == "seeds" and _route(ctx, lst, 41, "fp64") == "seeds"
     assert _route(ctx, lst, 42, "fp32") == "blocks" and _route(ctx, lst, 42, "fp64") == "seeds"
+
+
+def test_profiled_bytes_are_operands_and_results_once():
+    """256 rows, nu = 30, FP32: the blocks of H and S with their columns, the subspace matrices and the gathered rows."""
+    s = lattice.generate(2, 2, 2, seed=0)
+    ctx = mar.Context(s.H, s.S)
+    try:
+        ctx.profile(True)
+        ctx.solve(np.arange(256, dtype=np.int32), 30, -0.4, 0.1, precision="fp32")
+        p = ctx.profile_collect()["cgs_upd"]
+    finally:
+        ctx.close()
+    blocks, row = s.H.nnz // 16, int(np.diff(s.H.tocsr().indptr).max())
+    assert p["launches"] == 1
+    assert p["bytes"] == blocks * (2 * 16 * 4 + 4) + 64 * 4 + 256 * 30 * (31 / 2 + row) * 8
