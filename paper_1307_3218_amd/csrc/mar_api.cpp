@@ -546,10 +546,12 @@ bool use_seedwise(const mar_ctx* c, int nu, mar_precision prec, int64_t ns) {
     if (ns < 1 || !c->H.bsr || c->SH.nnz != c->H.nnz) return false;
     const mar::SeedGeom g = seed_geom(c, nu, prec, ns);
     if (!g.ok) return false;
-    // FP32 regions of fewer than 4 nu rows (the largest) stay with the blocks: there the last vectors are what rounding
-    // leaves of a nearly exhausted Krylov space, and any other order of the sums moves single entries of rho (mixed lattice,
-    // 3 hops, nu = 54: by 3e-3 of their root mean square, with errors against 64 bits of 1e-5 and 2e-6; 9.3 ms in blocks,
-    // 0.9 with a workgroup per seed). At up to a quarter of the rows they move by 1e-4 at most.
+    // FP32 regions of fewer than 4 nu rows (the largest) stay with the blocks, so that their results stay what they are:
+    // the last vectors are what rounding leaves of a nearly exhausted Krylov space, and any other order of the sums moves
+    // single entries of rho (mixed lattice, 3 hops, nu = 54: by 3e-3 of their root mean square; at up to a quarter of the
+    // rows by 1e-4 at most). It is not a matter of accuracy. Column errors against 64 bits over 1200 seeds, one workgroup
+    // per seed / blocks: 3 hops nu = 54 median 6e-8 / 9e-8, largest 2.5e-6 / 6.9e-6; nu = 41 6e-8 / 8e-8, 3.3e-5 / 5.7e-5;
+    // 4 hops nu = 48 6e-8 / 7e-8, 3.7e-5 / 8.6e-6. What the line costs: 3 hops, nu = 54 9.3 ms in blocks, 0.9.
     if (c->loc >= 0 && prec == MAR_FP32 && nu > region_blocks(c)) return false;
     // Where the line lies (ms per solve, one workgroup per seed / blocks; diamond cells and mixed-lattice regions). One
     // compute unit streams its seed's basis four times per step, what does not fit in LDS from L2 and the last-level cache;

@@ -816,8 +816,8 @@ __global__ __launch_bounds__(TRI_WG) void k_tri_big(EigExtra ex, const int32_t* 
 // recurrence's dependent chain is shorter), so the seeds of a launch share the chip: four to a workgroup, one on each
 // SIMD. All control is kept in scalar registers (the dimension, the block's ends and addresses are the same in every
 // lane) and the underflow check out of the loop: with masks, per-lane address products and selects a rotation took 350
-// cycles (nu = 30, 256 seeds: 193 us, now 152; nu = 100, 1024 seeds: 1.61 ms, now 1.23; nu = 300, 64 seeds: 12.5, now
-// 8.9).
+// cycles (nu = 30, 256 seeds: 193 us, now 151; nu = 100, 1024 seeds: 1.61 ms, now 1.19; nu = 300, 64 seeds: 12.5, now
+// 8.5).
 constexpr int QL_MAX_ITER = 60;   // iterations allowed per level (about two are needed)
 inline size_t ql_lds_bytes(int nu, int nr) { return (((size_t)nu * nr + 3 * (size_t)nu + 66) * 8 + 15) & ~(size_t)15; }
 __global__ __launch_bounds__(256) void k_ql(EigExtra ex, int nseeds, const int32_t* __restrict__ seeds, int nu,

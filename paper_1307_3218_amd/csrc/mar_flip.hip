@@ -21,9 +21,9 @@
 // applies its flip at once, since no other row of the colour reads the entries it changes (one barrier per colour), and
 // rows are padded (weight 0 at r[M] = 0) instead of branching on their length. Every sum runs in a fixed order, with
 // products and sums rounded separately (no fused multiply-add), so that every decision is reproducible. Measured at
-// M = 16384, 40 colours: 1.01 ms; 7.1 ms with r, H and S read through the caches in row order and three barriers per
-// colour; 1.22 ms with an address for every entry; rows requested two or three colours ahead, or 256 threads, were 5 to
-// 10 % slower.
+// M = 16384, 40 colours, the whole call: 1.12 ms (k_flip 0.9, k_flip_setup 0.02); 7.9 ms with r, H and S read through the
+// caches in row order and three barriers per colour. An address for every entry took k_flip a fifth longer; rows requested
+// two or three colours ahead, or 256 threads, 5 to 10 %.
 #include "mar_device.h"
 #include "mar_internal.h"
 

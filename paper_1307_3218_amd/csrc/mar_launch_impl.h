@@ -458,9 +458,10 @@ __global__ __launch_bounds__(WG) void k_spmm_list(int64_t nbrow, const int32_t* 
 }
 
 // Y = A X with A in CSR (patterns without 4x4 block structure). Thread = (row, seed group). What bounds it: the gather of
-// the rows of X from L2 (18 rows of 1 KB for one written, 8189 rows, FP64, 128 seeds: 10.7 us, 14 TB/s); the entries are
-// scalars where a row is a wavefront, and eight rows are in flight (one at a time took 15.2 us). H and S of one pattern
-// share the gather (k_spmm2_csr): 18.5 us with the norms for both, 10.7 + 12.5 apart.
+// the rows of X from L2 (18 rows of 1 KB for one written, 8189 rows, FP64, 128 seeds: 9.3 us, 16 TB/s); the entries are
+// scalars where a row is a wavefront, and eight rows are in flight (one at a time took 15.2 us), the remainder of a row one
+// by one (as a last eight with repeats and a condition per entry it took 10.7). H and S of one pattern share the gather
+// (k_spmm2_csr): 11.9 us with the norms for both.
 template <typename T, int B, int NDOT>
 __global__ __launch_bounds__(WG) void k_spmm_csr(int64_t nrow, const int32_t* __restrict__ rp,
                                                  const int32_t* __restrict__ col, const T* __restrict__ val,

@@ -19,7 +19,7 @@
 // which the bytes are a tenth); with part of the basis outside LDS the L2 and
 // last-level-cache reads of that part. Measured, whole Krylov phase: 0.14 ms
 // for 256 seeds of the 256-row cell (FP32, nu = 30; the blocks' launches took
-// 1.3 ms), 5.7 ms for 1024 seeds in regions of 6 hops (about 730 rows, FP32,
+// 1.3 ms), 5.5 ms for 1024 seeds in regions of 6 hops (564 to 908 rows, FP32,
 // nu = 100: 48 of 100 basis vectors in LDS; the blocks 78 ms), 8.3 ms for
 // 2048 seeds of a 2048-row cell (FP64, nu = 30: 6 of 30 vectors in LDS; 9.5 ms
 // with 4 in LDS and the wavefronts of a projection split over groups of
