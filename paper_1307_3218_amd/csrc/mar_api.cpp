@@ -1286,14 +1286,17 @@ mar_status run_seedwise(mar_ctx* c, const mar_request& r, hipStream_t s) {
     const double tau = sizeof(T) == 4 ? 1e-5 : 1e-12;
     // the FP32 form sums in FP64 at large subspace dimensions
     const bool acc64 = sizeof(T) == 4 && nu > mar::kUpdAcc64Nu;
-    const mar::SeedGeom g = seed_geom(c, nu, r.prec, n_seeds);
+    mar::SeedGeom g = seed_geom(c, nu, r.prec, n_seeds);
     const size_t per = (size_t)nu * (nu + std::max(1, c->max_row)) * 8;
     int64_t chunk = std::min<int64_t>(n_seeds, std::max<int64_t>(g.grid, (int64_t)(1e9 / (double)per)));
     SeedWs o = seed_workspace(c, r, g, chunk);
-    // shorter chunks in a caller's workspace, and under capture, where the context's cannot grow
-    const size_t room = c->ext_ws ? c->ext_bytes : !c->dry && captures(s) ? c->ws_bytes : SIZE_MAX;
-    while (o.bytes > room && chunk > 1) {
-        chunk = (chunk + 1) / 2;
+    // In a caller's workspace, and under capture, where the context's cannot grow: shorter chunks of seeds and fewer
+    // workgroups, each with its own part of the basis, whichever takes the larger half.
+    const bool capturing = !c->ext_ws && !c->dry && captures(s);
+    const size_t room = c->ext_ws ? c->ext_bytes : capturing ? c->ws_bytes : SIZE_MAX;
+    while (o.bytes > room && (chunk > 1 || (capturing && g.grid > 1))) {
+        if (capturing && g.grid > 1 && (chunk == 1 || o.h > room / 2)) g.grid = (g.grid + 1) / 2;
+        else chunk = (chunk + 1) / 2;
         o = seed_workspace(c, r, g, chunk);
     }
     const mar_status st = ensure_ws(c, o.bytes);
@@ -1406,9 +1409,13 @@ mar_status dispatch_solve(mar_ctx* c, const mar_request& r, const Plan& pl, hipS
                                "least %d seeds (block %d)", vec, pl.B));
     }
     mar_status st;
-    // (captured without room for one seed: the blocks may have it)
-    if (pl.seedwise && (c->ext_ws || c->dry || !captures(s) ||
-                        seed_workspace(c, r, seed_geom(c, r.nu, r.prec, r.n_seeds), 1).bytes <= c->ws_bytes))
+    bool seedwise = pl.seedwise;
+    if (seedwise && !c->ext_ws && !c->dry && captures(s)) {   // without room for one seed: the blocks may have it
+        mar::SeedGeom g = seed_geom(c, r.nu, r.prec, r.n_seeds);
+        g.grid = 1;
+        seedwise = seed_workspace(c, r, g, 1).bytes <= c->ws_bytes;
+    }
+    if (seedwise)
         return r.prec == MAR_FP32 ? run_seedwise<float>(c, r, s) : run_seedwise<double>(c, r, s);
     if (r.prec == MAR_FP32)
         st = pl.delayed ? run_solve_delayed<float>(c, r.d_seeds, r.n_seeds, r.nu, r.mu, r.kT, pl.B, pl.variant,

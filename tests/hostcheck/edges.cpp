@@ -5,6 +5,7 @@
 
 #include <cstdint>
 #include <cstdio>
+#include <cstdlib>
 #include <cstring>
 #include <map>
 #include <string>
@@ -145,6 +146,21 @@ int main(int argc, char** argv) {
                 if (a || b || hip_stub_launches() == before) return 1;
                 (void)hipGraphDestroy(g);
             }
+    } else if (what == "seed_counts_under_capture") {   // argv: seeds of both calls, the form
+        const int64_t warm = atoi(argv[3]), cap = atoi(argv[4]);
+        mar_tuning t;
+        memset(&t, 0, sizeof t);
+        t.upd_q = std::string(argv[5]) == "blocks" ? 4 : 0;
+        t.schedule = std::string(argv[5]) == "textbook" ? MAR_SCHED_TEXTBOOK : MAR_SCHED_AUTO;
+        (void)mar_set_tuning(s.c, &t);
+        for (mar_precision p : {MAR_FP32, MAR_FP64}) {
+            const mar_status a = solve(s, warm, 60, p, st);
+            (void)hipStreamBeginCapture(st, hipStreamCaptureModeGlobal);
+            const mar_status b = solve(s, cap, 60, p, st);
+            (void)hipStreamEndCapture(st, &g);
+            printf("warm %d, captured %d\n", (int)a, (int)b);
+            (void)hipGraphDestroy(g);
+        }
     } else if (what == "kept_basis_gives_way") {   // a later solve gets the memory that an eigen state's basis holds
         const mar_status a = eigen_state(s, s.M, 24, st);
         budget = 500ull << 20;

@@ -76,3 +76,34 @@ def test_more_seeds_captured_than_warmed(nu, prec):
                 assert torch.equal(out[k], want[k]), k
     finally:
         ctx.close()
+
+
+# the basis of FP64 nu = 60 on 1024 rows does not fit in LDS: 200 workgroups need more memory than 130 of the warm call
+@pytest.mark.parametrize("warm,seeds", [(130, 200), (100, 512)])
+def test_fewer_workgroups_under_capture(warm, seeds):
+    import torch
+    s = lattice.generate(4, 4, 2, seed=1)
+    lst = torch.arange(seeds, dtype=torch.int32, device="cuda")
+    want, out = _buffers(s.H, seeds), _buffers(s.H, seeds)
+    other = mar.Context(s.H, s.S)
+    try:
+        assert _seedwise(other, lambda: other.solve_async(lst, 60, -0.4, 0.1, "fp64", **want))
+    finally:
+        other.close()
+    ctx = mar.Context(s.H, s.S)
+    try:
+        ctx.solve_async(lst[:warm], 60, -0.4, 0.1, "fp64", **_buffers(s.H, warm))
+        torch.cuda.synchronize()
+        print(f"[fewer workgroups under capture: {warm}, {seeds}]", flush=True)
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g):
+            ctx.solve_async(lst, 60, -0.4, 0.1, "fp64", **out)
+        for _ in range(3):
+            for t in out.values():
+                t.zero_()
+            g.replay()
+            torch.cuda.synchronize()
+            for k in out:
+                assert torch.equal(out[k], want[k]), k
+    finally:
+        ctx.close()

@@ -60,8 +60,8 @@ def program(tmp_path_factory):
     return exe, str(tmp / "sys.bin")
 
 
-def _run(program, scenario):
-    r = subprocess.run([program[0], scenario, program[1]], capture_output=True, text=True, timeout=120)
+def _run(program, scenario, *args):
+    r = subprocess.run([program[0], scenario, program[1], *map(str, args)], capture_output=True, text=True, timeout=120)
     out = r.stdout + r.stderr
     print(out)
     assert r.returncode == 0 and "stub errors 0" in out, out
@@ -87,3 +87,10 @@ def test_basis_of_an_eigen_state_gives_way_to_a_later_solve(program):
 
 def test_eigen_state_without_room_for_the_pass_beside_the_kept_basis(program):
     assert "eigen state 0, on less memory 0" in _run(program, "kept_basis_without_room_for_the_pass")
+
+
+@pytest.mark.parametrize("form,warm,captured", [
+    ("seeds", 130, 200), ("seeds", 300, 1024)])
+def test_another_number_of_seeds_under_capture(program, form, warm, captured):
+    """One workgroup per seed, with more workgroups than in the warm call: the workspace of the warm call holds the captured one's."""
+    assert _run(program, "seed_counts_under_capture", warm, captured, form).count("warm 0, captured 0") == 2
