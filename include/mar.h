@@ -183,7 +183,10 @@ mar_status mar_solve(mar_ctx* ctx, const int32_t* seeds, int64_t n_seeds, int32_
  * d_nu_eff = -3 and NaN outputs (d_nu_eff must be non-NULL to see these). Scalar
  * arguments are validated as in mar_solve. The device workspace is owned by
  * the context and may be reallocated (hipMalloc) when nu, B, or the precision
- * grows; call once with the largest shapes before capturing. */
+ * grows; call once with the largest shapes before capturing. A captured solve
+ * of the batched form that needs more than the workspace (B not fixed by
+ * mar_set_tuning) runs in narrower blocks or one workgroup per seed, if those
+ * fit. */
 mar_status mar_solve_async(mar_ctx* ctx, const int32_t* d_seeds, int64_t n_seeds, int32_t nu,
                            double mu, double kT, mar_precision prec, mar_form form,
                            double* d_rho, double* d_e_band, double* d_e_seed, double* d_n_seed,

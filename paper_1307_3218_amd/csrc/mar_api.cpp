@@ -121,6 +121,7 @@ struct mar_ctx {
     char* ext_ws = nullptr;       // a caller's workspace for the current solve (nothing is allocated then)
     size_t ext_bytes = 0;
     bool ext_short = false;       // the current solve needs more than ext_bytes
+    bool fixed_ws = false;        // ext_ws is the context's own, which may not grow: the solve is captured
     char* ws_act = nullptr;       // the workspace the current solve runs on (ws or ext_ws)
     char* io = nullptr;
     size_t io_bytes = 0;
@@ -540,11 +541,11 @@ mar_status measure_regions(mar_ctx* c, mar_form form, hipStream_t s) {
     return MAR_OK;
 }
 
-// Whether a batched solve runs one workgroup per seed.
-bool use_seedwise(const mar_ctx* c, int nu, mar_precision prec, int64_t ns) {
+// Whether a batched solve can run one workgroup per seed, and its launch shape.
+bool can_seedwise(const mar_ctx* c, int nu, mar_precision prec, int64_t ns, mar::SeedGeom& g) {
     if (tuned_for_blocks(c->tune)) return false;
     if (ns < 1 || !c->H.bsr || c->SH.nnz != c->H.nnz) return false;
-    const mar::SeedGeom g = seed_geom(c, nu, prec, ns);
+    g = seed_geom(c, nu, prec, ns);
     if (!g.ok) return false;
     // FP32 regions of fewer than 4 nu rows (the largest) stay with the blocks, so that their results stay what they are:
     // the last vectors are what rounding leaves of a nearly exhausted Krylov space, and any other order of the sums moves
@@ -552,7 +553,13 @@ bool use_seedwise(const mar_ctx* c, int nu, mar_precision prec, int64_t ns) {
     // rows by 1e-4 at most). It is not a matter of accuracy. Column errors against 64 bits over 1200 seeds, one workgroup
     // per seed / blocks: 3 hops nu = 54 median 6e-8 / 9e-8, largest 2.5e-6 / 6.9e-6; nu = 41 6e-8 / 8e-8, 3.3e-5 / 5.7e-5;
     // 4 hops nu = 48 6e-8 / 7e-8, 3.7e-5 / 8.6e-6. What the line costs: 3 hops, nu = 54 9.3 ms in blocks, 0.9.
-    if (c->loc >= 0 && prec == MAR_FP32 && nu > region_blocks(c)) return false;
+    return c->loc < 0 || prec != MAR_FP32 || nu <= region_blocks(c);
+}
+
+// Whether it does.
+bool use_seedwise(const mar_ctx* c, int nu, mar_precision prec, int64_t ns) {
+    mar::SeedGeom g;
+    if (!can_seedwise(c, nu, prec, ns, g)) return false;
     // Where the line lies (ms per solve, one workgroup per seed / blocks; diamond cells and mixed-lattice regions). One
     // compute unit streams its seed's basis four times per step, what does not fit in LDS from L2 and the last-level cache;
     // the blocks stream all seeds' twice with the whole chip, and a block's time hardly falls with fewer seeds.
@@ -722,7 +729,8 @@ mar_status run_solve(mar_ctx* c, const int32_t* d_seeds, int64_t n_seeds, int nu
     // capturing, for the eigen-state passes, or with tuning two_streams 1 or 2.
     const int64_t n_blocks = (n_seeds + B - 1) / B;
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    const bool capturing = !c->dry && hipStreamIsCapturing(s, &cap) == hipSuccess && cap != hipStreamCaptureStatusNone;
+    const bool capturing = c->fixed_ws || (!c->dry && hipStreamIsCapturing(s, &cap) == hipSuccess &&
+                                           cap != hipStreamCaptureStatusNone);
     const bool eig_ovl = n_blocks >= 2 && !c->prof && !c->in_graph && !capturing && c->es.mode == 0 &&
                          (c->tune.two_streams == 0 || c->tune.two_streams == 3) && c->stream2;
     const size_t oH2 = take(eig_ovl ? (size_t)B * nu * nu * 8 : 0);
@@ -964,7 +972,8 @@ mar_status run_solve_delayed(mar_ctx* c, const int32_t* d_seeds, int64_t n_seeds
     for (const SeedRun& r : runs) n_blocks += (r.n + r.B - 1) / r.B;
     // a caller that captures its stream into a graph of its own gets every kernel on that stream
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    const bool capturing = !c->dry && hipStreamIsCapturing(s, &cap) == hipSuccess && cap != hipStreamCaptureStatusNone;
+    const bool capturing = c->fixed_ws || (!c->dry && hipStreamIsCapturing(s, &cap) == hipSuccess &&
+                                           cap != hipStreamCaptureStatusNone);
     // two_streams 0 picks: local regions of kTwoSetMinHops hops or more alternate two blocks (their short
     // per-step FP64 kernels and the eigensolve leave most of the chip idle: +18 % at 6 and 8 hops, +13 % at
     // 16, but -3 % at 5 and -13 % at 3), everything else one block at a time with the eigensolve on the
@@ -1290,12 +1299,11 @@ mar_status run_seedwise(mar_ctx* c, const mar_request& r, hipStream_t s) {
     const size_t per = (size_t)nu * (nu + std::max(1, c->max_row)) * 8;
     int64_t chunk = std::min<int64_t>(n_seeds, std::max<int64_t>(g.grid, (int64_t)(1e9 / (double)per)));
     SeedWs o = seed_workspace(c, r, g, chunk);
-    // In a caller's workspace, and under capture, where the context's cannot grow: shorter chunks of seeds and fewer
-    // workgroups, each with its own part of the basis, whichever takes the larger half.
-    const bool capturing = !c->ext_ws && !c->dry && captures(s);
-    const size_t room = c->ext_ws ? c->ext_bytes : capturing ? c->ws_bytes : SIZE_MAX;
-    while (o.bytes > room && (chunk > 1 || (capturing && g.grid > 1))) {
-        if (capturing && g.grid > 1 && (chunk == 1 || o.h > room / 2)) g.grid = (g.grid + 1) / 2;
+    // in a bounded workspace shorter chunks of seeds, and under capture also fewer workgroups, each with its own part of
+    // the basis, whichever takes the larger half
+    const size_t room = c->ext_ws ? c->ext_bytes : SIZE_MAX;
+    while (o.bytes > room && (chunk > 1 || (c->fixed_ws && g.grid > 1))) {
+        if (c->fixed_ws && g.grid > 1 && (chunk == 1 || o.h > room / 2)) g.grid = (g.grid + 1) / 2;
         else chunk = (chunk + 1) / 2;
         o = seed_workspace(c, r, g, chunk);
     }
@@ -1398,8 +1406,17 @@ mar_status check_request(mar_ctx* c, const mar_request& r) {
     return MAR_OK;
 }
 
+mar_status dispatch_within(mar_ctx* c, const mar_request& r, Plan pl, hipStream_t s, char* ws, size_t ws_bytes, bool& fits);
+
 // Enqueue one solve (validated) on stream s with a resolved plan.
 mar_status dispatch_solve(mar_ctx* c, const mar_request& r, const Plan& pl, hipStream_t s) {
+    if (c->ws && !c->ext_ws && !c->dry && !c->in_graph && captures(s)) {   // the workspace may not grow
+        bool fits = false;
+        c->fixed_ws = true;
+        const mar_status st = dispatch_within(c, r, pl, s, c->ws, c->ws_bytes, fits);
+        c->fixed_ws = false;
+        if (fits) return st;
+    }
     c->refused = false;
     if (c->loc >= 0) {
         const int vec = r.prec == MAR_FP32 ? 4 : 2;
@@ -1409,13 +1426,7 @@ mar_status dispatch_solve(mar_ctx* c, const mar_request& r, const Plan& pl, hipS
                                "least %d seeds (block %d)", vec, pl.B));
     }
     mar_status st;
-    bool seedwise = pl.seedwise;
-    if (seedwise && !c->ext_ws && !c->dry && captures(s)) {   // without room for one seed: the blocks may have it
-        mar::SeedGeom g = seed_geom(c, r.nu, r.prec, r.n_seeds);
-        g.grid = 1;
-        seedwise = seed_workspace(c, r, g, 1).bytes <= c->ws_bytes;
-    }
-    if (seedwise)
+    if (pl.seedwise)
         return r.prec == MAR_FP32 ? run_seedwise<float>(c, r, s) : run_seedwise<double>(c, r, s);
     if (r.prec == MAR_FP32)
         st = pl.delayed ? run_solve_delayed<float>(c, r.d_seeds, r.n_seeds, r.nu, r.mu, r.kT, pl.B, pl.variant,
@@ -1429,6 +1440,43 @@ mar_status dispatch_solve(mar_ctx* c, const mar_request& r, const Plan& pl, hipS
                                                     r.d_eps, r.d_weight, s)
                         : run_solve<double>(c, r.d_seeds, r.n_seeds, r.nu, r.mu, r.kT, pl.B, r.d_rho, r.d_e_band,
                                             r.d_e_seed, r.d_n_seed, r.d_nu_eff, r.d_eps, r.d_weight, s);
+    return st;
+}
+
+// The same on the workspace ws[0, ws_bytes), which a dry run sizes: with the batched form and no block size fixed by the
+// tuning the planned seed block is halved until it fits, also where one workgroup per seed was planned and did not. Under capture (c->fixed_ws) a plan of blocks may take one workgroup per seed, whose workspace is the smallest, when
+// half the block does not fit: a call with more seeds, on the other side of the line between the two, left the workspace.
+mar_status dispatch_within(mar_ctx* c, const mar_request& r, Plan pl, hipStream_t s, char* ws, size_t ws_bytes, bool& fits) {
+    const int min_b = c->loc >= 0 ? (r.prec == MAR_FP32 ? 4 : 2) : 1, planned = pl.B;
+    const bool shrink = r.form == MAR_FORM_BATCHED && c->tune.seed_block == 0;
+    bool other = c->fixed_ws && !pl.seedwise && shrink;
+    c->ext_ws = ws;
+    c->ext_bytes = ws_bytes;
+    mar_status st;
+    for (;;) {
+        mar::SeedGeom g;
+        c->ext_short = false;
+        c->dry = true;
+        st = dispatch_solve(c, r, pl, s);
+        c->dry = false;
+        if (st == MAR_OK || !c->ext_short) break;
+        if (pl.seedwise) {   // the blocks may still fit (not where an eigen state's basis is kept from this form)
+            if (c->es.K) break;
+            pl.seedwise = false;
+        } else if (other && (2 * pl.B <= planned || pl.B / 2 < min_b) && can_seedwise(c, r.nu, r.prec, r.n_seeds, g)) {
+            pl.seedwise = true;
+            other = false;
+        } else {
+            if (!shrink || pl.B / 2 < min_b) break;
+            pl.B /= 2;
+        }
+    }
+    fits = !c->ext_short;
+    if (st == MAR_OK) st = dispatch_solve(c, r, pl, s);
+    c->ext_ws = nullptr;
+    c->ext_bytes = 0;
+    c->ext_short = false;
+    c->ws_act = c->ws;
     return st;
 }
 
@@ -2402,9 +2450,7 @@ int ctx_device(const mar_ctx* c) { return c ? c->device : -1; }
 mar_status ctx_error(mar_ctx* c, mar_status st, const char* msg) { return set_err(c, st, msg); }
 
 // mar_solve_async on the workspace ws[0, ws_bytes) instead of the context's own:
-// nothing is allocated on the device. With the batched form and no block size
-// fixed by the tuning, the planned seed block is halved until the solve's
-// workspace fits (a dry run sizes it); per-kernel timing is suspended for the
+// nothing is allocated on the device; per-kernel timing is suspended for the
 // call (its events and tile logs would be created on demand).
 mar_status solve_async_ext(mar_ctx* c, const int32_t* d_seeds, int64_t n_seeds, int32_t nu, double mu, double kT,
                            mar_precision prec, mar_form form, double* d_rho, double* d_e_band, double* d_e_seed,
@@ -2421,31 +2467,10 @@ mar_status solve_async_ext(mar_ctx* c, const int32_t* d_seeds, int64_t n_seeds, 
                         d_eps, d_weight};
     hipStream_t s = (hipStream_t)hip_stream;
     if ((st = measure_regions(c, form, s)) != MAR_OK) return st;
-    Plan pl = plan_solve(c, nu, prec, form, n_seeds);
-    const int min_b = c->loc >= 0 ? (prec == MAR_FP32 ? 4 : 2) : 1;
-    const bool shrink = form == MAR_FORM_BATCHED && c->tune.seed_block == 0;
     const bool prof = c->prof;
+    bool fits;
     c->prof = false;
-    c->ext_ws = (char*)ws;
-    c->ext_bytes = ws_bytes;
-    for (;;) {
-        c->ext_short = false;
-        c->dry = true;
-        st = dispatch_solve(c, r, pl, s);
-        c->dry = false;
-        if (st == MAR_OK || !c->ext_short) break;
-        if (pl.seedwise) {   // the blocks may still fit
-            pl.seedwise = false;
-            continue;
-        }
-        if (!shrink || pl.B / 2 < min_b) break;
-        pl.B /= 2;
-    }
-    if (st == MAR_OK) st = dispatch_solve(c, r, pl, s);
-    c->ext_ws = nullptr;
-    c->ext_bytes = 0;
-    c->ext_short = false;
-    c->ws_act = c->ws;
+    st = dispatch_within(c, r, plan_solve(c, nu, prec, form, n_seeds), s, (char*)ws, ws_bytes, fits);
     c->prof = prof;
     return st;
 }

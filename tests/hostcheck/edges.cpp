@@ -148,14 +148,19 @@ int main(int argc, char** argv) {
             }
     } else if (what == "seed_counts_under_capture") {   // argv: seeds of both calls, the form
         const int64_t warm = atoi(argv[3]), cap = atoi(argv[4]);
-        mar_tuning t;
-        memset(&t, 0, sizeof t);
-        t.upd_q = std::string(argv[5]) == "blocks" ? 4 : 0;
-        t.schedule = std::string(argv[5]) == "textbook" ? MAR_SCHED_TEXTBOOK : MAR_SCHED_AUTO;
-        (void)mar_set_tuning(s.c, &t);
+        const std::string form = argv[5];
+        mar_tuning plain, t;
+        memset(&plain, 0, sizeof plain);
+        t = plain;
+        t.upd_q = form == "blocks" || form == "then_blocks" ? 4 : 0;
+        t.schedule = form == "textbook" ? MAR_SCHED_TEXTBOOK : MAR_SCHED_AUTO;
         for (mar_precision p : {MAR_FP32, MAR_FP64}) {
+            (void)mar_set_tuning(s.c, form == "then_blocks" ? &plain : &t);
+            (void)mar_set_local_region(s.c, -1);
             const mar_status a = solve(s, warm, 60, p, st);
+            (void)mar_set_tuning(s.c, &t);
             (void)hipStreamBeginCapture(st, hipStreamCaptureModeGlobal);
+            if (form == "then_region") (void)mar_set_local_region(s.c, 3);
             const mar_status b = solve(s, cap, 60, p, st);
             (void)hipStreamEndCapture(st, &g);
             printf("warm %d, captured %d\n", (int)a, (int)b);

@@ -90,7 +90,10 @@ def test_eigen_state_without_room_for_the_pass_beside_the_kept_basis(program):
 
 
 @pytest.mark.parametrize("form,warm,captured", [
-    ("seeds", 130, 200), ("seeds", 300, 1024)])
+    ("seeds", 130, 200), ("seeds", 300, 1024), ("blocks", 64, 100), ("blocks", 128, 255), ("blocks", 512, 300),
+    ("blocks", 256, 300), ("blocks", 256, 290), ("blocks", 1024, 140), ("textbook", 64, 100),
+    ("then_blocks", 200, 100), ("then_blocks", 130, 1024), ("then_region", 200, 100), ("then_region", 130, 20)])
 def test_another_number_of_seeds_under_capture(program, form, warm, captured):
-    """One workgroup per seed, with more workgroups than in the warm call: the workspace of the warm call holds the captured one's."""
+    """Counts that take the same block width or fewer than before, and a captured call in seed blocks after a warm one of
+    one workgroup per seed (then_*): the captured call runs in the workspace of the warm one."""
     assert _run(program, "seed_counts_under_capture", warm, captured, form).count("warm 0, captured 0") == 2
